@@ -328,6 +328,8 @@ def copy_calibration(nbytes: int, reps: int):
 
 
 
+EXHAUSTIVE = 4    # the scan that visits every pair, for batches of more than SMALL_M signals
+SMALL_M = 256     # (up to it the library's own choice is exhaustive)
 SCREEN = "f16-split MFMA screen, exact f32 direct-form recheck"
 DTYPE = "f16-split MFMA screen + f32 recheck"
 LATE_WINDOW = (81, 100)      # iterations timed on the grown network (stated run: 100)
@@ -342,8 +344,11 @@ def lock_modes(gsn, args):
 
 def tune(gsn, net, args):
     """Launch-configuration knobs from the command line (results never depend on them)."""
-    if args.variant:
-        net.tune(gsn.GSN_TUNE_VARIANT, args.variant)
+    # the metric counts evaluated signal-unit pairs, so batches that would take the search that
+    # leaves units out are timed with the exhaustive scan
+    variant = args.variant or (EXHAUSTIVE if net.params.m_max > SMALL_M else 0)
+    if variant:
+        net.tune(gsn.GSN_TUNE_VARIANT, variant)
     if args.split:
         net.tune(gsn.GSN_TUNE_SPLIT, args.split)
     if args.grab:
@@ -591,7 +596,8 @@ def main():
     ap.add_argument("--sweep-locks", default="set,winner",
                     help="with --sweep: comma-separated collision rules")
     ap.add_argument("--variant", type=int, default=0,
-                    help="find-winners kernel variant (GSN_TUNE_VARIANT; 0 = automatic)")
+                    help="find-winners kernel variant (GSN_TUNE_VARIANT; 0 = the exhaustive scan of "
+                    "the batch size)")
     ap.add_argument("--split", type=int, default=0,
                     help="unit chunks / partial rows of the scan (GSN_TUNE_SPLIT; 0 = automatic)")
     ap.add_argument("--grab", type=int, default=0,

@@ -338,16 +338,20 @@ void gsn_destroy(gsn_net* net);
 /* Launch-configuration knobs, for tests and measurement; results never depend on them.
  *   GSN_TUNE_SPLIT    units are split into this many chunks scanned by separate
  *                     workgroups and merged afterwards (0 = automatic, 1..GSN_MAX_SPLIT)
- *   GSN_TUNE_VARIANT  find-winners kernel: 0 = automatic (4), 1 = direct scan of every
+ *   GSN_TUNE_VARIANT  find-winners kernel: 0 = automatic (up to 256 signals the unit-parallel
+ *                     scan, 6; above, the search that leaves out blocks of units whose
+ *                     bounding box lies farther than the second nearest, unless
+ *                     GSN_TUNE_SPLIT asks for chunks: then 4), 1 = direct scan of every
  *                     distance, 2 = screened scan with the screen on the vector unit,
  *                     3 = screened scan with the screen on the matrix cores in binary32,
  *                     4 = the same screen on the matrix cores in split binary16, 5 = variant
  *                     4 with the unit batches dealt out dynamically (every wave takes
- *                     GSN_TUNE_GRAB batches at a time with an atomic counter) (every screen
+ *                     GSN_TUNE_GRAB batches at a time with an atomic counter) (variants 1-6
+ *                     evaluate or screen every signal-unit pair; every screen
  *                     carries a rigorous rounding margin; candidates are rechecked in the
  *                     binary32 direct form, so all variants return the same result)
  *   GSN_TUNE_GRAB     batches of 64 units per atomic grab of variant 5: 1..1024, 0 = default
- *   GSN_TUNE_REBUCKET staged find calls (variants 2-5) between rebuilds of the spatial order
+ *   GSN_TUNE_REBUCKET staged find calls (automatic and variants 2-5) between rebuilds of the spatial order
  *                     of the units (it is also rebuilt whenever N or the indices change):
  *                     1..4096, 0 = default (64)
  *   GSN_TUNE_GRID_ROUNDS  rounds of the GSN_LOCK_WINNER update of gsn_adapt and of the
@@ -374,7 +378,8 @@ int gsn_tune(gsn_net* net, int32_t key, int32_t value);
  *                     spans the kernel's own start to end (not the end-of-kernel cache
  *                     flush) and puts no marker on the stream, but costs the host tens of
  *                     microseconds per launch; the unstaged scans (variants 1 and 6, small
- *                     batches, whose steps are bound by launches) take a marker pair
+ *                     batches, whose steps are bound by launches) and the automatic search of
+ *                     larger batches take a marker pair
  *   GSN_T_FIND        all of gsn_find_winners
  *   GSN_T_RESOLVE, GSN_T_ADAPT, GSN_T_EDGES   all of the corresponding call
  *   GSN_T_UPDATE      the fused update of gsn_iterate (with GSN_LOCK_SET resolve, adapt

@@ -1,0 +1,529 @@
+// Find Winners over the units in spatial order, with whole blocks of units left out where a
+// bound shows that they hold neither of the two nearest (variant 7, the default for larger
+// batches).
+//
+// Order and blocks.  The units are gathered into the staging's spatial order (staging.hip)
+// as packed (x, y, z, index) records; every leaf of kLeaf = 64 consecutive records and every
+// block of kTop = 1,024 has its bounding box (pr_gather, from the positions of this call, so
+// the boxes are exact however old the order is; the order affects speed only).
+//
+// The bound needs no rounding margin.  With g_a = max(lo_a - s_a, s_a - hi_a, 0), each
+// difference rounded, and L = (g_x g_x + g_y g_y) + g_z g_z in the operation order of the
+// distance: for a unit w in the box w_a <= hi_a, so s_a - w_a >= s_a - hi_a, and rounding
+// to nearest is monotone, so |fl(s_a - w_a)| >= g_a (likewise below lo_a); products and sums
+// of non-negative numbers are monotone under rounding too, hence the computed distance of w
+// is >= L.  A box is left out only if L > B, B the computed distance of a real unit that is
+// at least the second smallest one: every unit that can enter the two nearest, ties by index
+// included, is in a box that is visited.  A comparison with NaN or between infinities never
+// leaves a box out.
+//
+// Search.  L lanes of a wave per signal.  The leaf around the signal's cell gives B; the lanes
+// test the outermost boxes, then the tops and the leaves of those that pass, each list
+// compacted in LDS, and evaluate the units of the leaves that pass (about six of 32 units on a
+// surface).  The kernel is bound by the vector unit for many signals (about 240 instructions a
+// signal) and by the chain of seven dependent loads for few.  At 200,000 units and 16,384
+// signals a find takes 9.3 us of gather and 14.5 us of search, where staging, the exhaustive
+// screen on the matrix cores and its merge took 125; at 100,000 and 65,536, 6.2 + 48 us where
+// they took 233.  One lane of a 64-unit leaf each, 16 lanes a signal and the boxes in two levels
+// measured 50 us for the former: the few signals with a poor first bound held up the launch,
+// hence the second attempt with a better bound, and finer cells in the unit order (64 a side,
+// cubes, instead of 32 fitted to the box).
+#include <type_traits>
+
+#include "gsn_internal.h"
+
+namespace gsn {
+namespace {
+
+constexpr int kLeaf = kPrunedLeaf;
+constexpr int kTop = kPrunedTop;
+constexpr int kFan = kTop / kLeaf;   // leaves of a top
+constexpr int32_t kWideBatch = 32768;   // signals up to which a signal gets 32 lanes, not 16
+constexpr unsigned long long kNone = ~0ull;
+
+__device__ __forceinline__ unsigned long long pack(float d, int32_t i) {
+  return (static_cast<unsigned long long>(__float_as_uint(d)) << 32) |
+         static_cast<uint32_t>(i);
+}
+
+// top-2 of two top-2 lists whose real keys are distinct (kNone may repeat)
+__device__ __forceinline__ void merge2(unsigned long long& a1, unsigned long long& a2,
+                                       unsigned long long b1, unsigned long long b2) {
+  const unsigned long long lo = min(a1, b1), hi = max(a1, b1);
+  a2 = min(hi, min(a2, b2));
+  a1 = lo;
+}
+
+// the value of another lane of the same 16-lane row
+template <int CTRL>
+__device__ __forceinline__ unsigned long long row_move(unsigned long long v) {
+  const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(v >> 32), CTRL, 0xf, 0xf, true);
+  return (static_cast<unsigned long long>(static_cast<uint32_t>(hi)) << 32) |
+         static_cast<uint32_t>(lo);
+}
+
+template <int CTRL>
+__device__ __forceinline__ void merge_row(unsigned long long& k1, unsigned long long& k2) {
+  const unsigned long long o1 = row_move<CTRL>(k1), o2 = row_move<CTRL>(k2);
+  merge2(k1, k2, o1, o2);
+}
+
+// top-2 over the L lanes of a group, in every lane (each step pairs lanes that hold the
+// lists of disjoint halves)
+template <int L>
+__device__ __forceinline__ void merge_group(unsigned long long& k1, unsigned long long& k2) {
+  merge_row<0xB1>(k1, k2);                       // quad_perm 1,0,3,2
+  merge_row<0x4E>(k1, k2);                       // quad_perm 2,3,0,1
+  merge_row<0x141>(k1, k2);                      // row_half_mirror
+  merge_row<0x140>(k1, k2);                      // row_mirror
+#pragma unroll
+  for (int off = 16; off < L; off <<= 1) {
+    const unsigned long long o1 = __shfl_xor(k1, off), o2 = __shfl_xor(k2, off);
+    merge2(k1, k2, o1, o2);
+  }
+}
+
+// minimum over the L lanes of a group, in every lane
+template <int L>
+__device__ __forceinline__ unsigned long long min_group(unsigned long long v) {
+  v = min(v, row_move<0xB1>(v));
+  v = min(v, row_move<0x4E>(v));
+  v = min(v, row_move<0x141>(v));
+  v = min(v, row_move<0x140>(v));
+#pragma unroll
+  for (int off = 16; off < L; off <<= 1) v = min(v, __shfl_xor(v, off));
+  return v;
+}
+
+__device__ __forceinline__ float gap(float s, float lo, float hi) {
+  return fmaxf(fmaxf(lo - s, s - hi), 0.0f);
+}
+
+__device__ __forceinline__ float box_bound(float sx, float sy, float sz, float4 lo, float4 hi) {
+  const float gx = gap(sx, lo.x, hi.x), gy = gap(sy, lo.y, hi.y), gz = gap(sz, lo.z, hi.z);
+  return (gx * gx + gy * gy) + gz * gz;
+}
+
+// ------------------------------------------------------------------- gather ----
+
+struct FMin { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
+struct FMax { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+
+template <int CTRL, typename Op>
+__device__ __forceinline__ float row_step(float v, Op op) {
+  return op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf,
+                                                       true)));
+}
+
+// over the 16 lanes of a row, in every lane
+template <typename Op>
+__device__ __forceinline__ float row_reduce(float v, Op op) {
+  v = row_step<0xB1>(v, op);
+  v = row_step<0x4E>(v, op);
+  v = row_step<0x141>(v, op);
+  return row_step<0x140>(v, op);
+}
+
+// over the kLeaf lanes that hold a leaf
+template <typename Op>
+__device__ __forceinline__ float leaf_reduce(float v, Op op) {
+  v = row_reduce(v, op);
+  return op(v, __shfl_xor(v, 16));
+}
+
+// One workgroup per top, half a wave per leaf.  The last leaf's slots past n hold NaN records
+// with index -1, whose keys are above every real one; leaves wholly past n are not written
+// (nobody reads them).
+__global__ __launch_bounds__(kTop) void pr_gather(const float* __restrict__ x,
+                                                  const float* __restrict__ y,
+                                                  const float* __restrict__ z, int32_t n,
+                                                  const int32_t* __restrict__ pidx,
+                                                  float4* __restrict__ pq,
+                                                  float4* __restrict__ leaf,
+                                                  float4* __restrict__ top,
+                                                  int32_t* __restrict__ sup,
+                                                  int32_t* __restrict__ sup_next,
+                                                  int32_t sup_words) {
+  __shared__ float red[kFan][6];
+  const int32_t pos = blockIdx.x * kTop + threadIdx.x;
+  const float inf = __builtin_huge_valf();
+  float lo[3] = {inf, inf, inf}, hi[3] = {-inf, -inf, -inf};
+  const int32_t lf = pos / kLeaf;
+  if (lf * kLeaf < n) {
+    float4 w = make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""),
+                           __int_as_float(-1));
+    if (pos < n) {
+      const int32_t i = min(max(pidx[pos], 0), n - 1);
+      w = make_float4(x[i], y[i], z[i], __int_as_float(i));
+      lo[0] = hi[0] = w.x;
+      lo[1] = hi[1] = w.y;
+      lo[2] = hi[2] = w.z;
+    }
+    pq[pos] = w;
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = leaf_reduce(lo[a], FMin());
+    hi[a] = leaf_reduce(hi[a], FMax());
+  }
+  const int wv = threadIdx.x / kLeaf;
+  if ((threadIdx.x & (kLeaf - 1)) == 0) {
+    if (lf * kLeaf < n) {
+      leaf[2 * lf] = make_float4(lo[0], lo[1], lo[2], 0.0f);
+      leaf[2 * lf + 1] = make_float4(hi[0], hi[1], hi[2], 0.0f);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      red[wv][a] = lo[a];
+      red[wv][3 + a] = hi[a];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    const int a = threadIdx.x;
+    float v = red[0][a];
+    for (int k = 1; k < kFan; ++k) v = a < 3 ? fminf(v, red[k][a]) : fmaxf(v, red[k][a]);
+    reinterpret_cast<float*>(&top[2 * blockIdx.x + (a < 3 ? 0 : 1)])[a % 3] = v;
+    int32_t* u = &sup[kSupWords * (blockIdx.x / kFan) + a];
+    if (a < 3) atomicMin(u, ord(v)); else atomicMax(u, ord(v));
+  }
+  // the other set, for the next call
+  if (blockIdx.x == 0)
+    for (int32_t i = threadIdx.x; i < sup_words; i += kTop)
+      sup_next[i] = i % kSupWords < 3 ? ord(inf) : ord(-inf);
+}
+
+// ------------------------------------------------------------------- search ----
+
+template <int CTRL>
+__device__ __forceinline__ float row_float(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+
+__device__ __forceinline__ void second_step(float& a1, float& a2, float b1, float b2) {
+  const float hi = fmaxf(a1, b1);
+  a1 = fminf(a1, b1);
+  a2 = fminf(hi, fminf(a2, b2));
+}
+
+// second smallest of the values of a group's lanes (two per lane, d1 <= d2; NaN left out)
+template <int L>
+__device__ __forceinline__ float second_of_group(float d1, float d2) {
+  const float inf = __builtin_huge_valf();
+  d1 = fminf(d1, inf);   // (a NaN in a maximum would hide the other value)
+  d2 = fminf(d2, inf);
+  second_step(d1, d2, row_float<0xB1>(d1), row_float<0xB1>(d2));
+  second_step(d1, d2, row_float<0x4E>(d1), row_float<0x4E>(d2));
+  second_step(d1, d2, row_float<0x141>(d1), row_float<0x141>(d2));
+  second_step(d1, d2, row_float<0x140>(d1), row_float<0x140>(d2));
+#pragma unroll
+  for (int off = 16; off < L; off <<= 1)
+    second_step(d1, d2, __shfl_xor(d1, off), __shfl_xor(d2, off));
+  return d2;
+}
+
+struct PrunedArgs {
+  const float4* pq;
+  const float4* leaf;
+  const float4* top;
+  const int32_t* sup;
+  int32_t n, nleaf, ntop;
+  const int32_t* off_u;
+  const float* bb;
+  const float* sig;
+  int32_t m;
+  int32_t *winner, *second;
+  float *d1, *d2;
+  ClaimArgs claim;
+  int do_claim;
+};
+
+// A signal with more passing tops or leaves than this has a poor first bound (a cell with no
+// units near it): the bound is improved and the boxes are tested again.
+constexpr int kFewTops = 12;
+constexpr int kFewLeaves = 16;
+// With more than this even then (units in many overlapping boxes, or nearly equidistant
+// ones), the boxes are visited one after another.
+constexpr int kMostTops = 32;
+constexpr int kMostLeaves = 64;
+
+template <int L>
+__global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
+  static_assert(L == 16 || L == 32 || L == 64, "whole rows of 16 lanes");
+  static_assert(kFan == 16, "one row of lanes tests the boxes of a node");
+  constexpr int kGroups = kBlock / L;
+  constexpr int kRows = L / 16;                     // nodes tested side by side
+  constexpr int kSide = L > kLeaf ? L / kLeaf : 1;  // leaves evaluated side by side
+  constexpr int kPer = kLeaf * kSide / L;           // units per lane
+  constexpr int kUnroll = 2;                        // nodes per row and step
+  __shared__ int32_t tops[kGroups][kMostTops + kUnroll * L];
+  __shared__ int32_t leaves[kGroups][kMostLeaves + kUnroll * L];
+  const int g = threadIdx.x / L, q = threadIdx.x % L;
+  const int row = q / 16, c = q % 16;
+  const int32_t j = blockIdx.x * kGroups + g;
+  if (j >= a.m) return;   // whole groups; nothing below spans groups
+  const float sx = a.sig[j], sy = a.sig[a.m + j], sz = a.sig[2 * a.m + j];
+  const int32_t nsup = (a.ntop + kFan - 1) / kFan;
+  const int sh = (threadIdx.x & 63) / L * L;     // first lane of the group in its wave
+  // a group's part of a ballot, its set bits and those before this lane's
+  using Bits = std::conditional_t<L == 64, unsigned long long, uint32_t>;
+  const Bits before = static_cast<Bits>((1ull << q) - 1);
+  auto bits = [&](bool p) -> Bits {
+    const unsigned long long b = __ballot(p);
+    if constexpr (L == 64) return b;
+    else {
+      const uint32_t half = static_cast<uint32_t>(sh < 32 ? b : b >> 32);
+      return L == 32 ? half : (half >> (sh & 31)) & 0xffffu;
+    }
+  };
+  auto count = [](Bits b) {
+    if constexpr (L == 64) return static_cast<int32_t>(__popcll(b));
+    else return static_cast<int32_t>(__popc(b));
+  };
+  auto first = [](Bits b) {
+    if constexpr (L == 64) return static_cast<int32_t>(__builtin_ctzll(b));
+    else return static_cast<int32_t>(__builtin_ctz(b));
+  };
+  auto below = [&](Bits b) { return count(b & before); };
+  unsigned long long k1 = kNone, k2 = kNone;
+  float bound = __builtin_huge_valf();
+  struct Units { float4 w[kPer]; };
+  // the group's units of leaf lf (with kSide > 1, lanes from kLeaf on take leaf lf2)
+  auto load_leaf = [&](int32_t lf, int32_t lf2) {
+    const int32_t l = kSide > 1 && q >= kLeaf ? lf2 : lf;
+    Units u;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) u.w[i] = a.pq[l * kLeaf + (i * L + q) % kLeaf];
+    return u;
+  };
+  auto eval = [&](const Units& u, bool both) {
+    bool entered = false;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const float dx = sx - u.w[i].x, dy = sy - u.w[i].y, dz = sz - u.w[i].z;
+      const float d = (dx * dx + dy * dy) + dz * dz;
+      if (!(d > bound) && (kSide == 1 || both || q < kLeaf)) {
+        const unsigned long long k = pack(d, __float_as_int(u.w[i].w));
+        entered |= k < k2;
+        k2 = min(k2, max(k1, k));
+        k1 = min(k1, k);
+      }
+    }
+    return entered;
+  };
+  // The second smallest distance of the group's units so far as the bound (the words of an
+  // empty place read as NaN, which the minima leave out).
+  auto tighten = [&]() {
+    float d1 = __uint_as_float(static_cast<uint32_t>(k1 >> 32));
+    float d2 = __uint_as_float(static_cast<uint32_t>(k2 >> 32));
+    bound = fminf(bound, second_of_group<L>(d1, d2));
+  };
+  auto box = [&](const float4* b, int32_t i) {
+    return box_bound(sx, sy, sz, b[2 * i], b[2 * i + 1]);
+  };
+  auto sup_box = [&](int32_t s) {
+    const int4 u = *reinterpret_cast<const int4*>(a.sup + kSupWords * s);
+    const int2 v = *reinterpret_cast<const int2*>(a.sup + kSupWords * s + 4);
+    return box_bound(sx, sy, sz, make_float4(unord(u.x), unord(u.y), unord(u.z), 0.0f),
+                     make_float4(unord(u.w), unord(v.x), unord(v.y), 0.0f));
+  };
+
+  // (the first supers' boxes are read beside the chain that gives the first bound)
+  const float first_sup = sup_box(min(q, nsup - 1));
+  // The leaf at the middle of the signal's cell gives the first bound; with no units in the
+  // cell, of the eight or 64 cells it is one of (consecutive in Morton order).
+  const int32_t key = stage_bucket(sx, sy, sz, a.bb);
+  int32_t r0 = a.off_u[key], r1 = a.off_u[key + 1];
+  {
+    const int32_t p0 = a.off_u[key & ~7], p1 = a.off_u[(key | 7) + 1];
+    const int32_t g0 = a.off_u[key & ~63], g1 = a.off_u[(key | 63) + 1];
+    if (r1 <= r0) {
+      r0 = p1 > p0 ? p0 : g0;
+      r1 = p1 > p0 ? p1 : g1;
+    }
+  }
+  const int32_t home = min(max((r0 + r1) / 2 / kLeaf, 0), a.nleaf - 1);
+  eval(load_leaf(home, home), false);
+  tighten();
+
+  int32_t nl = 0, skip = home, most_tops = kFewTops, most_leaves = kFewLeaves;
+  bool many;
+  for (int pass_no = 0;; ++pass_no) {
+    // the tops that pass, through the boxes of kFan of them
+    int32_t nt = 0;
+    for (int32_t s0 = 0; s0 < nsup && nt <= most_tops; s0 += L) {
+      const int32_t s = s0 + q;
+      const float ls = s0 == 0 ? first_sup : sup_box(min(s, nsup - 1));
+      Bits sm = bits(s < nsup && !(ls > bound));
+      while (sm != 0 && nt <= most_tops) {
+        // kUnroll supers per row at a time
+        int32_t t[kUnroll];
+        bool have[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          t[u] = 0;
+          have[u] = false;
+#pragma unroll
+          for (int r = 0; r < kRows; ++r) {
+            if (r == row) {
+              have[u] = sm != 0;
+              t[u] = (s0 + (sm != 0 ? first(sm) : 0)) * kFan + c;
+            }
+            sm &= sm - 1;
+          }
+          have[u] = have[u] && t[u] < a.ntop;
+        }
+        float lb[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) lb[u] = box(a.top, min(t[u], a.ntop - 1));
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const bool pass = have[u] && !(lb[u] > bound);
+          const Bits b = bits(pass);
+          if (pass) tops[g][nt + below(b)] = t[u];
+          nt += count(b);
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    many = nt > most_tops;
+
+    // their leaves that pass
+    nl = 0;
+    if (!many)
+      for (int32_t k = row; k < nt + row && !many; k += kUnroll * kRows) {
+        int32_t f[kUnroll];
+        float lb[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) f[u] = tops[g][min(k + u * kRows, nt - 1)] * kFan + c;
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) lb[u] = box(a.leaf, min(f[u], a.nleaf - 1));
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const bool pass = k + u * kRows < nt && f[u] < a.nleaf && f[u] != skip &&
+                            !(lb[u] > bound);
+          const Bits b = bits(pass);
+          if (pass) leaves[g][nl + below(b)] = f[u];
+          nl += count(b);
+        }
+        many = nl > most_leaves;
+      }
+    __builtin_amdgcn_wave_barrier();
+    if (!many || pass_no == 1) break;
+
+    // A better bound: the nearest leaves of the nearest top of the nearest super.  Then from
+    // an empty list (a leaf enters the list of the two nearest once).
+    auto nearest = [&](unsigned long long v) {
+      return static_cast<int32_t>(static_cast<uint32_t>(min_group<L>(v)));
+    };
+    unsigned long long best = kNone;
+    for (int32_t s = q; s < nsup; s += L) best = min(best, pack(sup_box(s), s));
+    const int32_t tn = min(nearest(best) * kFan + c, a.ntop - 1);
+    const int32_t fn = min(nearest(pack(box(a.top, tn), tn)) * kFan + c, a.nleaf - 1);
+    unsigned long long mine = pack(box(a.leaf, fn), fn);   // (each row holds all of them)
+    for (int i = 0; i < kFan; ++i) {
+      best = min_group<L>(mine);
+      if (best == kNone || __uint_as_float(static_cast<uint32_t>(best >> 32)) > bound) break;
+      if (mine == best) mine = kNone;
+      const int32_t lf = static_cast<int32_t>(static_cast<uint32_t>(best));
+      k1 = k2 = kNone;
+      eval(load_leaf(lf, lf), false);
+      tighten();
+    }
+    k1 = k2 = kNone;
+    skip = -1;
+    most_tops = kMostTops;
+    most_leaves = kMostLeaves;
+  }
+  if (!many) {
+    if (nl > 0) {
+      Units u = load_leaf(leaves[g][0], leaves[g][min(1, nl - 1)]);
+      int32_t e = kSide;
+      for (; e < nl; e += kSide) {
+        const Units v = load_leaf(leaves[g][e], leaves[g][min(e + 1, nl - 1)]);
+        eval(u, true);
+        u = v;
+      }
+      eval(u, e <= nl);
+    }
+  } else {
+    for (int32_t s = 0; s < nsup; ++s) {
+      if (sup_box(s) > bound) continue;
+      const int32_t t = s * kFan + c;
+      Bits tm =
+          bits(row == 0 && t < a.ntop && !(box(a.top, min(t, a.ntop - 1)) > bound));
+      while (tm != 0) {
+        const int32_t f0 = (s * kFan + first(tm)) * kFan;
+        tm &= tm - 1;
+        const int32_t lf = f0 + c;
+        Bits lm =
+            bits(row == 0 && lf < a.nleaf && !(box(a.leaf, min(lf, a.nleaf - 1)) > bound));
+        while (lm != 0) {
+          const int32_t l = f0 + first(lm);
+          lm &= lm - 1;
+          if (bits(eval(load_leaf(l, l), false)) != 0) tighten();
+        }
+      }
+    }
+  }
+  merge_group<L>(k1, k2);
+
+  const int32_t bw = static_cast<int32_t>(static_cast<uint32_t>(k1));
+  const int32_t sw = static_cast<int32_t>(static_cast<uint32_t>(k2));
+  const float dw = __uint_as_float(static_cast<uint32_t>(k1 >> 32));
+  if (q == 0) {
+    a.winner[j] = bw;
+    a.second[j] = sw;
+    a.d1[j] = dw;
+    a.d2[j] = __uint_as_float(static_cast<uint32_t>(k2 >> 32));
+  }
+  if (!a.do_claim) return;
+  const bool ok = pair_ok(bw, sw, a.claim.n);
+  if (a.claim.pend && q == 0) a.claim.pend[j] = ok ? 1 : 0;
+  if (!ok) {
+    if (q == 0) raise_error(a.claim.status, GSN_E_INVAL);
+    return;
+  }
+  const unsigned long long ck = signal_key(dw, j, a.claim.key_mode);
+  if (q == 0) {
+    atomicMin(&a.claim.lock[bw], ck);
+    if (!a.claim.winner_only) atomicMin(&a.claim.lock[sw], ck);
+  }
+  if (a.claim.winner_only) return;
+  for (int32_t k = a.claim.rp[bw] + q; k < a.claim.rp[bw + 1]; k += L)
+    atomicMin(&a.claim.lock[a.claim.col[k]], ck);
+}
+
+}  // namespace
+
+hipError_t launch_pruned_gather(const DevState& s, const StageBufs& b, int32_t n,
+                                int32_t n_max, int par, hipStream_t st) {
+  const int32_t words = sup_words(n_max);
+  pr_gather<<<(n + kTop - 1) / kTop, kTop, 0, st>>>(s.x, s.y, s.z, n, b.pidx, b.pq, b.leaf,
+                                                    b.top, b.sup + par * words,
+                                                    b.sup + (par ^ 1) * words, words);
+  return hipGetLastError();
+}
+
+hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t n_max, int par, const float* sig, int32_t m,
+                                int32_t* winner, int32_t* second, float* d1, float* d2,
+                                const ClaimArgs* claim, hipStream_t st, LaunchEvents ev) {
+  if (n < 2 || m < 1) return hipErrorInvalidValue;
+  const PrunedArgs a{b.pq, b.leaf, b.top, b.sup + par * sup_words(n_max), n, (n + kLeaf - 1) / kLeaf, (n + kTop - 1) / kTop,
+                     b.off_u, b.bb, sig, m, winner, second, d1, d2,
+                     claim ? *claim : ClaimArgs{}, claim ? 1 : 0};
+  auto go = [&](auto k, int lanes) {
+    const int per = kBlock / lanes;
+    launch_with(k, dim3((m + per - 1) / per), dim3(kBlock), st, ev, a);
+  };
+  // Two signals a wave while the waves of the batch fit the device about twice over (16,384
+  // signals, 200,000 units: 14.5 us against 16.9 with four; 2,999 signals, 37,501 units: 14.6
+  // against 16.6), four beyond, where the vector unit is busy and the reductions count (65,536
+  // signals, 100,000 units: 48.0 us against 50.3).
+  if (m <= kWideBatch) go(pr_search<32>, 32);
+  else go(pr_search<16>, 16);
+  return hipGetLastError();
+}
+
+}  // namespace gsn

@@ -126,9 +126,17 @@ int signals_per_lane(int32_t m) { return m >= 8192 ? 4 : (m >= 2048 ? 2 : 1); }
 
 FindConfig find_config(int32_t n, int32_t m, int cus, int want_split, int want_variant) {
   FindConfig c;
-  // small batches take the unit-parallel scan (no staging) unless a variant is asked for;
-  // variant 6 is only defined up to kSmallM signals (larger batches take variant 4)
-  c.variant = want_variant > 0 ? want_variant : (m <= kSmallM ? 6 : 4);
+  // small batches take the unit-parallel scan (no staging) and larger ones the pruned search
+  // unless a variant is asked for, or a split, which only the scans have; variant 6 is only
+  // defined up to kSmallM signals (larger batches take variant 4)
+  c.variant = want_variant > 0 ? want_variant
+              : m <= kSmallM   ? 6
+              : want_split > 0 ? 4
+                               : 7;
+  if (c.variant == 7) {
+    c.split = 0;
+    return c;
+  }
   if (c.variant == 6 && m > kSmallM) c.variant = 4;
   if (c.variant == 6) {
     c.split = 0;

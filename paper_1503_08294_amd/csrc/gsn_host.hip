@@ -172,6 +172,7 @@ struct gsn_net {
   int tune_grab;    // list entries per atomic of the dynamic scan
   int tune_rebucket;  // staged find calls between rebuilds of the spatial unit order
   int stage_parity;  // which set of signal histogram and cursors the next call uses
+  int sup_parity;    // which set of the pruned search's outer boxes the last gather wrote
   bool timing;
   uint32_t timing_mask;  // timers that record while timing is on (bit GSN_T_*)
   int32_t bucket_n;            // unit count at the last spatial bucketing (-1: none yet)
@@ -192,12 +193,12 @@ struct gsn_net {
     float *d1, *d2;
     uint8_t* accepted;
     int32_t n;
-    int cur, dpar, wpar, stage_parity;
+    int cur, dpar, wpar, stage_parity, sup_parity;
     bool rebuild_first;
     int tune_split, tune_variant, tune_grab, tune_rebucket, grid_rounds;
     // the host state the loop leaves
     bool rebuilt;   // the first find rebuilt the unit order (else finds_delta counts finds)
-    int cur_after, dpar_after, wpar_after, stage_parity_after;
+    int cur_after, dpar_after, wpar_after, stage_parity_after, sup_parity_after;
     int32_t finds_after, finds_delta, bucket_n_after;
     hipGraphExec_t exec;
     uint64_t used;
@@ -412,6 +413,7 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   net->tune_grab = kDefaultGrab;
   net->tune_rebucket = kRebucketEvery;
   net->stage_parity = 0;
+  net->sup_parity = 0;
   net->timing = false;
   net->timing_mask = (1u << GSN_T_COUNT) - 1;
   net->bucket_n = -1;
@@ -446,7 +448,8 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   hipStream_t st = as_stream(stream);
   hipError_t e = gsn::launch_init(net->s, 0, n0, params->n_max, st);
   if (e == hipSuccess)
-    e = gsn::launch_stage_init(gsn::carve_stage(net->s.scr, params->n_max, params->m_max), st);
+    e = gsn::launch_stage_init(gsn::carve_stage(net->s.scr, params->n_max, params->m_max),
+                               params->n_max, st);
   const size_t bytes = sizeof(float) * static_cast<size_t>(n0);
   if (e == hipSuccess && n0 > 0) {
     e = hipMemcpyAsync(net->s.x, init_xyz, bytes, hipMemcpyDefault, st);
@@ -506,15 +509,27 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
       rebucket = net->loop_rebuild == 1;
       net->loop_rebuild = -1;
     }
-    e = gsn::launch_stage(net->s, sb, net->n, sig, m, rebucket, net->stage_parity,
-                          cfg.variant, st);
-    net->stage_parity ^= 1;
+    if (cfg.variant == 7) {
+      e = rebucket ? gsn::launch_stage_order(net->s, sb, net->n, st) : hipSuccess;
+      net->sup_parity ^= 1;
+      if (e == hipSuccess)
+        e = gsn::launch_pruned_gather(net->s, sb, net->n, net->p.n_max, net->sup_parity, st);
+    } else {
+      e = gsn::launch_stage(net->s, sb, net->n, sig, m, rebucket, net->stage_parity,
+                            cfg.variant, st);
+      net->stage_parity ^= 1;
+    }
     if (rebucket) {
       net->bucket_n = net->n;
       net->finds_since_bucket = 0;
     }
     ++net->finds_since_bucket;
-    if (e == hipSuccess) {
+    if (e == hipSuccess && cfg.variant == 7) {
+      TimedRegion scan(net, GSN_T_FIND_SCAN, st);
+      e = gsn::launch_pruned_search(sb, net->n, net->p.n_max, net->sup_parity, sig, m, winner, second, d1, d2, claim, st);
+      scan.end();
+      if (claimed) *claimed = claim != nullptr;
+    } else if (e == hipSuccess) {
       LaunchTimer scan(net, GSN_T_FIND_SCAN);
       e = cfg.variant == 5   ? gsn::launch_scan_f16_dyn(net->s, sb, net->n, m, cfg.split,
                                                     net->tune_grab, st, scan.ev)
@@ -526,7 +541,7 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
                                                          st, scan.ev);
       scan.end(e == hipSuccess);
     }
-    if (e == hipSuccess) {
+    if (e == hipSuccess && cfg.variant != 7) {
       e = gsn::launch_stage_merge(net->s, sb, m, cfg.split, winner, second, d1, d2, claim, st);
       if (claimed) *claimed = claim != nullptr;
       if (order) *order = sb.sperm;  // the signals' spatial order of this call
@@ -804,7 +819,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     return g.sigs == sigs && g.m == m && g.count == count && g.winner == winner &&
            g.second == second && g.d1 == d1 && g.d2 == d2 && g.accepted == accepted &&
            g.n == net->n && g.cur == net->cur && g.dpar == net->dpar && g.wpar == net->wpar &&
-           g.stage_parity == net->stage_parity && g.rebuild_first == rebuild_first &&
+           g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity && g.rebuild_first == rebuild_first &&
            g.tune_split == net->tune_split && g.tune_variant == net->tune_variant &&
            g.tune_grab == net->tune_grab && g.tune_rebucket == net->tune_rebucket &&
            g.grid_rounds == net->grid_rounds;
@@ -823,6 +838,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.winner = winner; g.second = second; g.d1 = d1; g.d2 = d2; g.accepted = accepted;
     g.n = net->n; g.cur = net->cur; g.dpar = net->dpar; g.wpar = net->wpar;
     g.stage_parity = net->stage_parity;
+    g.sup_parity = net->sup_parity;
     g.rebuild_first = rebuild_first;
     g.tune_split = net->tune_split; g.tune_variant = net->tune_variant;
     g.tune_grab = net->tune_grab; g.tune_rebucket = net->tune_rebucket;
@@ -830,6 +846,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     // record the loop: the calls run on the host as usual (argument checks, state), their
     // launches go into the graph
     const int cur0 = net->cur, dpar0 = net->dpar, wpar0 = net->wpar, sp0 = net->stage_parity;
+    const int up0 = net->sup_parity;
     const int phase0 = net->phase;
     const int32_t bn0 = net->bucket_n, f0 = net->finds_since_bucket;
     (void)hipGetLastError();
@@ -856,6 +873,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     if (rc != GSN_OK || !exec) {
       // nothing ran: the handle is as before the call
       net->cur = cur0; net->dpar = dpar0; net->wpar = wpar0; net->stage_parity = sp0;
+      net->sup_parity = up0;
       net->phase = phase0;
       net->bucket_n = bn0; net->finds_since_bucket = f0;
       (void)hipGetLastError();
@@ -865,11 +883,13 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.rebuilt = rebuilt;
     g.cur_after = net->cur; g.dpar_after = net->dpar; g.wpar_after = net->wpar;
     g.stage_parity_after = net->stage_parity;
+    g.sup_parity_after = net->sup_parity;
     g.finds_after = net->finds_since_bucket;
     g.finds_delta = net->finds_since_bucket - f0;
     g.bucket_n_after = net->bucket_n;
     // the host state is back at the start until the graph is launched below
     net->cur = cur0; net->dpar = dpar0; net->wpar = wpar0; net->stage_parity = sp0;
+    net->sup_parity = up0;
     net->bucket_n = bn0; net->finds_since_bucket = f0;
     if (net->graphs.size() >= GSN_GRAPH_CACHE) {
       size_t old = 0;
@@ -888,6 +908,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   net->dpar = hit->dpar_after;
   net->wpar = hit->wpar_after;
   net->stage_parity = hit->stage_parity_after;
+  net->sup_parity = hit->sup_parity_after;
   if (hit->rebuilt) {
     net->finds_since_bucket = hit->finds_after;
     net->bucket_n = hit->bucket_n_after;
@@ -1115,13 +1136,14 @@ int gsn_import(gsn_net* net, int32_t n, const float* xyz, const float* err, int3
       fill_bytes(s.whi, 0, 8);
     }
     ok = ok && gsn::launch_stage_init(gsn::carve_stage(s.scr, net->p.n_max, net->p.m_max),
-                                      st) == hipSuccess;
+                                      net->p.n_max, st) == hipSuccess;
     ok = hipStreamSynchronize(st) == hipSuccess && ok;
     if (!ok) return GSN_E_HIP;
     net->n = n;
     net->dpar = 0;
     net->wpar = 0;
     net->stage_parity = 0;   // both histogram sets were cleared above
+    net->sup_parity = 0;     // and both sets of outer boxes
     net->phase = kReady;
     net->bucket_n = -1;
   } catch (const std::bad_alloc&) {

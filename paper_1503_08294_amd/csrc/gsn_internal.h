@@ -342,7 +342,22 @@ hipError_t launch_find_small_merge(const DevState& s, int32_t n, int32_t m, int3
                                    const ClaimArgs* claim, hipStream_t st);
 
 // Spatial staging of the screened scans (staging.hip).
-constexpr int kBuckets = 32 * 32 * 32;
+constexpr int kBuckets = 64 * 64 * 64;
+
+constexpr int kPrunedLeaf = 32;    // units per leaf of the pruned search
+constexpr int kPrunedTop = 512;    // units per block of leaves; sixteen of them share a box too
+constexpr int kSupWords = 8;       // words of such a box (lo, hi as ordered integers)
+inline int32_t sup_words(int32_t n_max) {
+  return kSupWords * (n_max / (16 * kPrunedTop) + 1);
+}
+// order-preserving map between binary32 and int32
+__device__ __forceinline__ int32_t ord(float f) {
+  const int32_t b = __float_as_int(f);
+  return b >= 0 ? b : b ^ 0x7fffffff;
+}
+__device__ __forceinline__ float unord(int32_t b) {
+  return __int_as_float(b >= 0 ? b : b ^ 0x7fffffff);
+}
 
 struct StageBufs {
   float4* pu;       // [ceil64(n_max)] units in bucket order: (x, y, z, |w|^2); slots from n
@@ -355,8 +370,9 @@ struct StageBufs {
   float* ssig;      // [3][m] the signals in sorted order (x, y, z rows of stride m)
   int32_t* stk;     // [m_max] rank of every signal inside its histogram bin (the ticket its
                     // count increment returned)
-  int32_t *hist_u, *off_u, *cur_u, *hist_s;  // [kBuckets + 1] each; the signal histogram
-                    // uses two sets of kBuckets / 8 in hist_s
+  int32_t *hist_u, *off_u, *cur_u;  // [kBuckets + 1] each
+  int32_t* hist_s;  // [2][kBuckets / 64] signal histograms
+  int32_t* hsum;    // [kBuckets / 1024] sums of the unit histogram's parts
   int32_t* acc;     // [16] bounding-box accumulators
   float* bb;        // [8] grid of the last unit bucketing: lo.xyz, cells per length.xyz
   int32_t* mag;     // [4] max |x|, |y|, |z|, |w|^2 of this call (float bits)
@@ -364,14 +380,39 @@ struct StageBufs {
   float* pm;        // [ceil(n_max / 64) * 256] units in matrix-core operand order
   uint4* pmh;       // [ceil(n_max / 64)][64 lanes][2 groups] scaled units split into binary16
                     // pairs, in the operand order of the 32x32x16 f16 product (16 B each)
+  float4* pq;       // [ceil64(n_max)] the pruned search's records in bucket order: (x, y, z,
+                    // index bits)
+  float4* leaf;     // [ceil(n_max / kPrunedLeaf)][2] bounding box (lo, hi) of every leaf
+  float4* top;      // [ceil(n_max / kPrunedTop)][2] and of every block of leaves
+  int32_t* sup;     // [2][sup_words(n_max)] and of every sixteen such blocks: two sets, taken
+                    // by successive gathers in turn, each clearing the other's
   int32_t* wctr;    // [wctr_count(m_max)] grab counters of the dynamic scan, zeroed by the
                     // seed kernel of every call: 8 lists per 64-signal block
 };
 // 8 counters per 64-signal block, for whole blocks of 256 signals
 inline int32_t wctr_count(int32_t m) { return 32 * ((m + 255) / 256); }
+// The cell of a point in the grid of the last unit bucketing (bb: lo.x lo.y lo.z inv.x inv.y
+// inv.z), as the Morton code of its three 6-bit coordinates.
+constexpr int kStageGrid = 64;
+__device__ __forceinline__ uint32_t spread6(uint32_t v) {
+  v &= 63u;
+  v = (v | (v << 8)) & 0x0300Fu;
+  v = (v | (v << 4)) & 0x030C3u;
+  v = (v | (v << 2)) & 0x09249u;
+  return v;
+}
+__device__ __forceinline__ uint32_t stage_cell(float p, float lo, float inv) {
+  const float t = fminf(fmaxf((p - lo) * inv, 0.0f), static_cast<float>(kStageGrid - 1));
+  return static_cast<uint32_t>(t);
+}
+__device__ __forceinline__ int32_t stage_bucket(float x, float y, float z, const float* bb) {
+  return static_cast<int32_t>(spread6(stage_cell(x, bb[0], bb[3])) |
+                              (spread6(stage_cell(y, bb[1], bb[4])) << 1) |
+                              (spread6(stage_cell(z, bb[2], bb[5])) << 2));
+}
 size_t stage_bytes(int32_t n_max, int32_t m_max);
 StageBufs carve_stage(void* base, int32_t n_max, int32_t m_max);
-hipError_t launch_stage_init(const StageBufs& b, hipStream_t st);
+hipError_t launch_stage_init(const StageBufs& b, int32_t n_max, hipStream_t st);
 // units n0 .. n1 - 1 appended to the spatial order (older indices unchanged)
 hipError_t launch_stage_append(const StageBufs& b, int32_t n0, int32_t n1, hipStream_t st);
 // parity alternates between calls (two sets of signal histogram and cursors)
@@ -407,6 +448,16 @@ hipError_t launch_scan_f16_dyn(const DevState& s, const StageBufs& b, int32_t n,
                                int split, int grab, hipStream_t st, LaunchEvents ev = {});
 hipError_t launch_scan_mfma(const DevState& s, const StageBufs& b, int32_t n, const float* sig,
                             int32_t m, int split, hipStream_t st, LaunchEvents ev = {});
+
+// The pruned search (find_pruned.hip, variant 7): the records and boxes of the present
+// positions in the unit order, then the two nearest of every signal with the claims of claim
+// (null: none).
+hipError_t launch_stage_order(const DevState& s, const StageBufs& b, int32_t n, hipStream_t st);
+hipError_t launch_pruned_gather(const DevState& s, const StageBufs& b, int32_t n,
+                                int32_t n_max, int par, hipStream_t st);
+hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t n_max, int par, const float* sig, int32_t m,
+                                int32_t* winner, int32_t* second, float* d1, float* d2,
+                                const ClaimArgs* claim, hipStream_t st, LaunchEvents ev = {});
 
 // The survivor tables of the one-pass winner-lock update (launch_winner_local) of parity par.
 struct WinnerTables {

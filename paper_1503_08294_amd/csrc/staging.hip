@@ -1,7 +1,7 @@
 // Spatial staging shared by the screened find-winners scans (see find_screened.hip for the
 // screen and its rounding bound).
 //
-// Unit order.  Units are counting-sorted by the Morton code of a 32^3 grid cell over their
+// Unit order.  Units are counting-sorted by the Morton code of a 64^3 grid of cubes over their
 // bounding box, and every find call gathers the current positions into that order as
 // packed (x, y, z, |w|^2) records.  The order only affects speed (every unit is still
 // visited for every signal), so it is rebuilt only when the host asks for it: after the
@@ -18,8 +18,8 @@
 namespace gsn {
 namespace {
 
-constexpr int kGrid = 32;
-constexpr int kSignalShift = 3;                        // signals ordered by bucket >> 3
+constexpr int kGrid = kStageGrid;
+constexpr int kSignalShift = 6;                        // signals ordered by bucket >> 6
 constexpr int kSignalBuckets = kBuckets >> kSignalShift;
 constexpr int kSeedWindow = 64;
 // operand layouts the gather writes besides the packed records: the binary32 matrix-core
@@ -28,37 +28,9 @@ constexpr int kLayoutF32 = 1;
 constexpr int kLayoutF16 = 2;
 constexpr int kSeedLanes = 16;
 
-__device__ __forceinline__ int32_t ord(float f) {
-  const int32_t b = __float_as_int(f);
-  return b >= 0 ? b : b ^ 0x7fffffff;
-}
-__device__ __forceinline__ float unord(int32_t b) {
-  return __int_as_float(b >= 0 ? b : b ^ 0x7fffffff);
-}
-
 // identities of the bounding-box accumulators: [0..2] ord(min), [3..5] ord(max)
 __device__ __forceinline__ int32_t acc_identity(int t) {
   return t < 3 ? ord(__builtin_huge_valf()) : ord(-__builtin_huge_valf());
-}
-
-__device__ __forceinline__ uint32_t spread5(uint32_t v) {
-  v &= 31u;
-  v = (v | (v << 8)) & 0x0300Fu;
-  v = (v | (v << 4)) & 0x030C3u;
-  v = (v | (v << 2)) & 0x09249u;
-  return v;
-}
-
-__device__ __forceinline__ uint32_t cell_of(float p, float lo, float inv) {
-  const float t = fminf(fmaxf((p - lo) * inv, 0.0f), static_cast<float>(kGrid - 1));
-  return static_cast<uint32_t>(t);
-}
-
-// bb: lo.x lo.y lo.z inv.x inv.y inv.z
-__device__ __forceinline__ int32_t bucket_of(float x, float y, float z, const float* bb) {
-  return static_cast<int32_t>(spread5(cell_of(x, bb[0], bb[3])) |
-                              (spread5(cell_of(y, bb[1], bb[4])) << 1) |
-                              (spread5(cell_of(z, bb[2], bb[5])) << 2));
 }
 
 __device__ __forceinline__ float norm2(float x, float y, float z) {
@@ -111,14 +83,16 @@ struct FMin { __device__ float operator()(float a, float b) const { return fminf
 struct FMax { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 
 // every histogram, offset and cursor array cleared; accumulators at their identities
-__global__ __launch_bounds__(kBlock) void st_init(StageBufs b) {
+__global__ __launch_bounds__(kBlock) void st_init(StageBufs b, int32_t supw) {
   const int32_t i = blockIdx.x * kBlock + threadIdx.x;
   if (i <= kBuckets) {
     b.hist_u[i] = 0;
-    b.hist_s[i] = 0;
     b.off_u[i] = 0;
     b.cur_u[i] = 0;
   }
+  if (i < 2 * kSignalBuckets) b.hist_s[i] = 0;
+  for (int32_t k = i; k < 2 * supw; k += gridDim.x * kBlock)
+    b.sup[k] = k % kSupWords < 3 ? ord(__builtin_huge_valf()) : ord(-__builtin_huge_valf());
   if (i < 16) b.acc[i] = i < 6 ? acc_identity(i) : 0;
   if (i < 8) b.bb[i] = 0.0f;
 }
@@ -161,10 +135,11 @@ __global__ __launch_bounds__(kBlock) void st_hist_units(const float* __restrict_
                                                         int32_t* __restrict__ hist_u) {
   __shared__ float sbb[6];
   if (threadIdx.x < 3) {
-    const float lo = unord(acc[threadIdx.x]);
-    const float hi = unord(acc[3 + threadIdx.x]);
-    sbb[threadIdx.x] = lo;
-    sbb[3 + threadIdx.x] = hi > lo ? static_cast<float>(kGrid) / (hi - lo) : 0.0f;
+    // cubes: one scale, from the longest side of the box
+    float side = 0.0f;
+    for (int k = 0; k < 3; ++k) side = fmaxf(side, unord(acc[3 + k]) - unord(acc[k]));
+    sbb[threadIdx.x] = unord(acc[threadIdx.x]);
+    sbb[3 + threadIdx.x] = side > 0.0f ? static_cast<float>(kGrid) / side : 0.0f;
     if (blockIdx.x == 0) {
       bb[threadIdx.x] = sbb[threadIdx.x];
       bb[3 + threadIdx.x] = sbb[3 + threadIdx.x];
@@ -174,88 +149,45 @@ __global__ __launch_bounds__(kBlock) void st_hist_units(const float* __restrict_
   __syncthreads();
   const int32_t i = blockIdx.x * kBlock + threadIdx.x;
   if (i < n) {
-    const int32_t k = bucket_of(x[i], y[i], z[i], sbb);
+    const int32_t k = stage_bucket(x[i], y[i], z[i], sbb);
     ukey[i] = k;
     atomicAdd(&hist_u[k], 1);
   }
 }
 
-// Inclusive prefix sum over a 1024-thread workgroup: wave shuffles, then the 16 wave
-// totals through LDS (two barriers).
-__device__ int32_t block_inclusive_scan(int32_t v, int32_t* total) {
-  __shared__ int32_t wsum[16];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int32_t a = __shfl_up(v, o);
-    if (lane >= o) v += a;
-  }
-  if (lane == 63) wsum[w] = v;
-  __syncthreads();
-  int32_t before = 0, all = 0;
-#pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int32_t x = wsum[k];
-    before += k < w ? x : 0;
-    all += x;
-  }
-  __syncthreads();
-  *total = all;
-  return v + before;
+// Exclusive scan of the unit histogram into off[] (off[kBuckets] = total) and cur[], clearing
+// it, in two launches of kBuckets / kScanPart workgroups: each sums its part, then each scans
+// its part from the sum of the parts before it.  The second also resets the bounding-box
+// accumulators.
+constexpr int kScanPart = 4 * kBlock;
+constexpr int kScanParts = kBuckets / kScanPart;
+static_assert(kScanParts == kBlock, "a thread per part");
+
+__global__ __launch_bounds__(kBlock) void st_scan_sum(const int32_t* __restrict__ hist,
+                                                      int32_t* __restrict__ hsum) {
+  __shared__ int32_t wt[kBlock / 64];
+  const int4 v = reinterpret_cast<const int4*>(hist)[blockIdx.x * kBlock + threadIdx.x];
+  const int32_t t = block_sum(v.x + v.y + v.z + v.w, wt);
+  if (threadIdx.x == 0) hsum[blockIdx.x] = t;
 }
 
-// One workgroup: exclusive scan of a histogram of B entries into off[] (off[B] = total)
-// and cur[], clearing the histogram.  Units (mode 0) also reset the bounding-box
-// accumulators.  Signals (mode 1) also reduce the gather's per-block magnitude maxima
-// (nmag blocks) into mag[].
-template <int B>
-__global__ __launch_bounds__(1024) void st_scan_hist(int32_t* __restrict__ hist,
-                                                     int32_t* __restrict__ off,
-                                                     int32_t* __restrict__ cur,
-                                                     int32_t* __restrict__ acc,
-                                                     const float* __restrict__ bmag,
-                                                     int32_t nmag, int32_t* __restrict__ mag,
-                                                     int mode) {
-  constexpr int per = B / 1024;
-  const int t = threadIdx.x;
-  int32_t v[per];
-  int32_t sum = 0;
-#pragma unroll
-  for (int i = 0; i < per; ++i) {
-    v[i] = hist[t * per + i];
-    sum += v[i];
-  }
-  int32_t total;
-  int32_t run = block_inclusive_scan(sum, &total) - sum;
-#pragma unroll
-  for (int i = 0; i < per; ++i) {
-    off[t * per + i] = run;
-    cur[t * per + i] = run;
-    hist[t * per + i] = 0;
-    run += v[i];
-  }
-  if (t == 1023) off[B] = total;
-  if (mode == 0 && t < 6) acc[t] = acc_identity(t);
-  if (mode == 1) {
-    float mg[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int32_t b = t; b < nmag; b += 1024)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) mg[k] = fmaxf(mg[k], bmag[4 * b + k]);
-    __shared__ float red[16][4];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) mg[k] = fmaxf(mg[k], __shfl_xor(mg[k], o));
-    if ((t & 63) == 0)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) red[t >> 6][k] = mg[k];
-    __syncthreads();
-    if (t < 4) {
-      float r = 0.0f;
-      for (int w = 0; w < 16; ++w) r = fmaxf(r, red[w][t]);
-      mag[t] = __float_as_int(r);
-    }
-  }
+__global__ __launch_bounds__(kBlock) void st_scan_write(int32_t* __restrict__ hist,
+                                                        const int32_t* __restrict__ hsum,
+                                                        int32_t* __restrict__ off,
+                                                        int32_t* __restrict__ cur,
+                                                        int32_t* __restrict__ acc) {
+  __shared__ int32_t wa[kBlock / 64], wb[kBlock / 64];
+  const int32_t b = blockIdx.x, t = threadIdx.x;
+  const int4 v = reinterpret_cast<const int4*>(hist)[b * kBlock + t];
+  const int32_t before = block_sum(t < b ? hsum[t] : 0, wa);
+  const int32_t sum = v.x + v.y + v.z + v.w;
+  const int32_t run = before + block_inclusive_scan(sum, wb) - sum;
+  const int4 o = make_int4(run, run + v.x, run + v.x + v.y, run + v.x + v.y + v.z);
+  reinterpret_cast<int4*>(off)[b * kBlock + t] = o;
+  reinterpret_cast<int4*>(cur)[b * kBlock + t] = o;
+  reinterpret_cast<int4*>(hist)[b * kBlock + t] = make_int4(0, 0, 0, 0);
+  if (b == kScanParts - 1 && t == kBlock - 1) off[kBuckets] = run + sum;
+  if (b == 0 && t < 6) acc[t] = acc_identity(t);
 }
 
 __global__ __launch_bounds__(kBlock) void st_scatter_units(int32_t n,
@@ -357,7 +289,7 @@ __global__ __launch_bounds__(kBlock) void st_gather(const float* __restrict__ x,
   } else {
     const int32_t j = (blockIdx.x - ub) * kBlock + threadIdx.x;
     if (j < m) {
-      const int32_t k = bucket_of(sig[j], sig[m + j], sig[2 * m + j], bb);
+      const int32_t k = stage_bucket(sig[j], sig[m + j], sig[2 * m + j], bb);
       skey[j] = k;
       // the count's old value is the signal's rank inside its bin (the order inside a bin
       // is immaterial)
@@ -608,7 +540,9 @@ size_t stage_bytes(int32_t n_max, int32_t m_max) {
   add(4 * mm);   // sperm
   add(4 * mm);   // seed
   add(12 * mm);  // ssig
-  for (int i = 0; i < 4; ++i) add(hb);  // hist/off/cur for units, hist for signals
+  for (int i = 0; i < 3; ++i) add(hb);  // hist/off/cur for units
+  add(8 * kSignalBuckets);              // hist for signals
+  add(4 * kScanParts);                  // hsum
   add(4 * 16);   // acc
   add(4 * 8);    // bb
   add(4 * 4);    // mag
@@ -616,6 +550,10 @@ size_t stage_bytes(int32_t n_max, int32_t m_max) {
   add(16 * ((nm + 63) / 64 * 64));  // pm
   add(32 * ((nm + 63) / 64 * 64));  // pmh
   add(4 * wctr_count(m_max));        // wctr
+  add(16 * nb64);                    // pq
+  add(32 * (nb64 / kPrunedLeaf));    // leaf
+  add(32 * (nm / kPrunedTop + 1));   // top
+  add(8 * static_cast<size_t>(sup_words(n_max)));  // sup
   return b;
 }
 
@@ -642,7 +580,8 @@ StageBufs carve_stage(void* base, int32_t n_max, int32_t m_max) {
   s.hist_u = reinterpret_cast<int32_t*>(take(hb));
   s.off_u = reinterpret_cast<int32_t*>(take(hb));
   s.cur_u = reinterpret_cast<int32_t*>(take(hb));
-  s.hist_s = reinterpret_cast<int32_t*>(take(hb));
+  s.hist_s = reinterpret_cast<int32_t*>(take(8 * kSignalBuckets));
+  s.hsum = reinterpret_cast<int32_t*>(take(4 * kScanParts));
   s.acc = reinterpret_cast<int32_t*>(take(4 * 16));
   s.bb = reinterpret_cast<float*>(take(4 * 8));
   s.mag = reinterpret_cast<int32_t*>(take(4 * 4));
@@ -650,6 +589,10 @@ StageBufs carve_stage(void* base, int32_t n_max, int32_t m_max) {
   s.pm = reinterpret_cast<float*>(take(16 * ((nm + 63) / 64 * 64)));
   s.pmh = reinterpret_cast<uint4*>(take(32 * ((nm + 63) / 64 * 64)));
   s.wctr = reinterpret_cast<int32_t*>(take(4 * wctr_count(m_max)));
+  s.pq = reinterpret_cast<float4*>(take(16 * nb64));
+  s.leaf = reinterpret_cast<float4*>(take(32 * (nb64 / kPrunedLeaf)));
+  s.top = reinterpret_cast<float4*>(take(32 * (nm / kPrunedTop + 1)));
+  s.sup = reinterpret_cast<int32_t*>(take(8 * static_cast<size_t>(sup_words(n_max))));
   return s;
 }
 
@@ -659,21 +602,27 @@ hipError_t launch_stage_append(const StageBufs& b, int32_t n0, int32_t n1, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_stage_init(const StageBufs& b, hipStream_t st) {
-  st_init<<<blocks(kBuckets + 1), kBlock, 0, st>>>(b);
+hipError_t launch_stage_init(const StageBufs& b, int32_t n_max, hipStream_t st) {
+  st_init<<<blocks(kBuckets + 1), kBlock, 0, st>>>(b, sup_words(n_max));
+  return hipGetLastError();
+}
+
+hipError_t launch_stage_order(const DevState& s, const StageBufs& b, int32_t n, hipStream_t st) {
+  const int nb = blocks(n);
+  st_bbox<<<std::min(nb, 64), kBlock, 0, st>>>(s.x, s.y, s.z, n, b.acc);
+  st_hist_units<<<nb, kBlock, 0, st>>>(s.x, s.y, s.z, n, b.acc, b.bb, b.ukey, b.hist_u);
+  st_scan_sum<<<kScanParts, kBlock, 0, st>>>(b.hist_u, b.hsum);
+  st_scan_write<<<kScanParts, kBlock, 0, st>>>(b.hist_u, b.hsum, b.off_u, b.cur_u, b.acc);
+  st_scatter_units<<<nb, kBlock, 0, st>>>(n, b.ukey, b.cur_u, b.pidx);
   return hipGetLastError();
 }
 
 hipError_t launch_stage(const DevState& s, const StageBufs& b, int32_t n, const float* sig,
                         int32_t m, bool rebucket, int parity, int variant, hipStream_t st) {
   const int layouts = variant == 3 ? kLayoutF32 : variant >= 4 ? kLayoutF16 : 0;
-  const int nb_u = blocks(n);
   if (rebucket) {
-    st_bbox<<<std::min(nb_u, 64), kBlock, 0, st>>>(s.x, s.y, s.z, n, b.acc);
-    st_hist_units<<<nb_u, kBlock, 0, st>>>(s.x, s.y, s.z, n, b.acc, b.bb, b.ukey, b.hist_u);
-    st_scan_hist<kBuckets><<<1, 1024, 0, st>>>(b.hist_u, b.off_u, b.cur_u, b.acc, nullptr, 0,
-                                              b.mag, 0);
-    st_scatter_units<<<nb_u, kBlock, 0, st>>>(n, b.ukey, b.cur_u, b.pidx);
+    const hipError_t e = launch_stage_order(s, b, n, st);
+    if (e != hipSuccess) return e;
   }
   const int nb_g = blocks((static_cast<int64_t>(n) + 63) & ~static_cast<int64_t>(63));
   // the signal histogram alternates between two sets by call parity; each call's gather

@@ -1,0 +1,77 @@
+"""The default search of larger batches (blocks of units left out by their bounding boxes)
+against the oracle, bit for bit: sizes around the edges of its leaves (32 units), blocks of
+leaves (512) and blocks of those (8,192), both lane counts, and inputs for which the first
+bound is poor or no bound helps."""
+import numpy as np
+import pytest
+
+from parity import Pair, assert_find_equal, assert_iter_equal
+
+pytestmark = pytest.mark.gpu
+
+
+def shape(kind, n, m, seed):
+    rng = np.random.default_rng(seed)
+    units = rng.standard_normal((3, n)).astype(np.float32)
+    sig = rng.standard_normal((3, m)).astype(np.float32)
+    if kind == "grid":          # exact ties and duplicated units
+        units = rng.integers(-3, 4, (3, n)).astype(np.float32)
+        sig = rng.integers(-3, 4, (3, m)).astype(np.float32)
+    elif kind == "clusters":    # cells with no units near the signals, far from any home
+        units = (units * 1e-3 + rng.integers(0, 2, (1, n)) * 50.0).astype(np.float32)
+        sig = (sig * 30.0 + 25.0).astype(np.float32)
+    elif kind == "sphere":      # every unit about equally far from the signals
+        units /= np.linalg.norm(units, axis=0, keepdims=True)
+        sig *= np.float32(1e-7)
+    elif kind == "line":        # flat boxes, one cell side of zero units
+        units[1:] = 0.5
+    elif kind == "overflow":    # distances past the binary32 range: all ties by index
+        units *= np.float32(3e19)
+        sig[:, ::3] *= np.float32(1e25)
+    if kind != "sphere":
+        k = min(n, m) // 3
+        sig[:, :k] = units[:, n - k:]
+    return units, np.ascontiguousarray(sig)
+
+
+@pytest.mark.parametrize("kind", ["random", "grid", "clusters", "sphere", "line", "overflow"])
+@pytest.mark.parametrize("n,m", [(2, 257), (31, 300), (32, 257), (33, 1_000), (511, 300),
+                                 (513, 999), (8_192, 257), (8_193, 301), (20_011, 700),
+                                 (700, 32_769)])
+def test_sizes_and_shapes(kind, n, m):
+    units, sig = shape(kind, n, m, n + m)
+    pair = Pair(units, m_max=m)
+    g, o = pair.find(sig)
+    assert_find_equal(g, o, f"{kind} n={n} m={m}")
+
+
+def test_units_far_from_their_place_in_the_order():
+    """Units that jump onto their signals (eps_b 1) between rebuilds of the spatial order: the
+    boxes are those of the present positions however old the order is, and each call's outer
+    boxes are its own."""
+    from paper_1503_08294_amd import gsn
+    rng = np.random.default_rng(5)
+    n, m = 9_000, 600
+    units = rng.standard_normal((3, n)).astype(np.float32)
+    pair = Pair(units, m_max=m, eps_b=1.0, eps_n=0.5, max_age=3)
+    pair.net.tune(gsn.GSN_TUNE_REBUCKET, 4096)
+    for t in range(12):
+        sig = (rng.standard_normal((3, m)) * (1.0 + 2.0 * (t % 4))).astype(np.float32)
+        g, o = pair.iterate(sig)
+        assert_iter_equal(g, o, f"iteration {t}")
+    pair.compare_state("end")
+
+
+def test_switching_between_the_search_and_the_scans():
+    """The staged scans and the search share the unit order and keep their own copies of the
+    positions: alternating them on one handle changes nothing."""
+    from paper_1503_08294_amd import gsn
+    rng = np.random.default_rng(6)
+    units = rng.standard_normal((3, 5_000)).astype(np.float32)
+    pair = Pair(units, m_max=2_000, lock_mode=1)
+    for t, variant in enumerate((0, 4, 0, 3, 4, 0, 0, 2, 5, 0)):
+        pair.net.tune(gsn.GSN_TUNE_VARIANT, variant)
+        sig = rng.standard_normal((3, 500 + 150 * t)).astype(np.float32)
+        g, o = pair.iterate(sig)
+        assert_iter_equal(g, o, f"call {t} variant {variant}")
+    pair.compare_state("end")
