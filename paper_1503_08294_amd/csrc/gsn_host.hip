@@ -1021,39 +1021,25 @@ int gsn_export(gsn_net* net, float* xyz, float* err, int32_t* edges, void* strea
   auto copy = [&](void* dst, const void* src, size_t bytes) {
     return hipMemcpyAsync(dst, src, bytes, hipMemcpyDefault, st) == hipSuccess;
   };
-  auto sync = [&]() { return hipStreamSynchronize(st) == hipSuccess; };
-  try {
-    bool ok = true;
-    if (xyz && n > 0)
-      ok = copy(xyz, net->s.x, 4 * n) && copy(xyz + n, net->s.y, 4 * n) &&
-           copy(xyz + 2 * n, net->s.z, 4 * n);
-    if (ok && err && n > 0) ok = copy(err, net->s.err, 4 * n);
-    if (!ok || !sync()) return GSN_E_HIP;
-    if (edges) {
-      std::vector<int32_t> rp(n + 1);
-      if (!copy(rp.data(), net->s.rp[net->cur], 4 * (n + 1)) || !sync()) return GSN_E_HIP;
-      const size_t half = static_cast<size_t>(rp[n]);
-      std::vector<int32_t> col(half), age(half);
-      if (half > 0 && (!copy(col.data(), net->s.col[net->cur], 4 * half) ||
-                       !copy(age.data(), net->s.age[net->cur], 4 * half) || !sync()))
-        return GSN_E_HIP;
-      const size_t e = half / 2;
-      std::vector<int32_t> out(3 * e);
-      size_t t = 0;
-      for (size_t u = 0; u < n; ++u)
-        for (int32_t k = rp[u]; k < rp[u + 1]; ++k)
-          if (static_cast<size_t>(col[k]) > u && t < e) {
-            out[t] = static_cast<int32_t>(u);
-            out[e + t] = col[k];
-            out[2 * e + t] = age[k];
-            ++t;
-          }
-      if (e > 0 && (!copy(edges, out.data(), 4 * 3 * e) || !sync())) return GSN_E_HIP;
-    }
-  } catch (const std::bad_alloc&) {
-    return GSN_E_CAPACITY;
+  // the edges are listed on the device, in the adjacency buffer that is not current (the next
+  // update overwrites it); the host needs their number for the copies
+  int32_t half = 0;
+  if (edges && !copy(&half, net->s.rp[net->cur] + n, sizeof(int32_t))) return GSN_E_HIP;
+  if (edges && hipStreamSynchronize(st) != hipSuccess) return GSN_E_HIP;
+  const int32_t e = std::min(half / 2, net->p.e_max);
+  if (e > 0 && gsn::launch_export_edges(net->s, net->cur, net->n, e, st) != hipSuccess)
+    return GSN_E_HIP;
+  bool ok = true;
+  if (xyz && n > 0)
+    ok = copy(xyz, net->s.x, 4 * n) && copy(xyz + n, net->s.y, 4 * n) &&
+         copy(xyz + 2 * n, net->s.z, 4 * n);
+  if (ok && err && n > 0) ok = copy(err, net->s.err, 4 * n);
+  if (ok && e > 0) {
+    const size_t ne = static_cast<size_t>(e);
+    const int32_t* uv = net->s.col[net->cur ^ 1];
+    ok = copy(edges, uv, 8 * ne) && copy(edges + 2 * ne, net->s.age[net->cur ^ 1], 4 * ne);
   }
-  return GSN_OK;
+  return hip_ok(hipStreamSynchronize(st)) == GSN_OK && ok ? GSN_OK : GSN_E_HIP;
 }
 
 int gsn_import(gsn_net* net, int32_t n, const float* xyz, const float* err, int32_t n_edges,

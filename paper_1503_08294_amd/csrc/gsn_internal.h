@@ -543,6 +543,10 @@ hipError_t launch_scan_blocks(int32_t* bsum, int32_t nb, int64_t cap, int32_t* o
                               int32_t* status, int32_t slot, hipStream_t st);
 hipError_t launch_init(const DevState& s, int cur, int32_t n0, int32_t n_max,
                        hipStream_t st);
+// The edges as three rows of `edges` entries (u, v, age), u < v ascending, in the adjacency
+// buffer that is not current: u and v in col[cur ^ 1], the ages in age[cur ^ 1].
+hipError_t launch_export_edges(const DevState& s, int cur, int32_t n, int32_t edges,
+                               hipStream_t st);
 hipError_t launch_remove(const DevState& s, int cur, int32_t n, int32_t n_max,
                          hipStream_t st);
 // Indexed find winners (find_grid.hip): the grid and the caller's grid workspace.
