@@ -20,14 +20,15 @@
 // Search.  L lanes of a wave per signal.  The leaf around the signal's cell gives B; the lanes
 // test the outermost boxes, then the tops and the leaves of those that pass, each list
 // compacted in LDS, and evaluate the units of the leaves that pass (about six of 32 units on a
-// surface).  The kernel is bound by the vector unit for many signals (about 240 instructions a
+// surface).  The kernel is bound by the vector unit for many signals (about 210 instructions a
 // signal) and by the chain of seven dependent loads for few.  At 200,000 units and 16,384
-// signals a find takes 9.3 us of gather and 14.5 us of search, where staging, the exhaustive
-// screen on the matrix cores and its merge took 125; at 100,000 and 65,536, 6.2 + 48 us where
-// they took 233.  One lane of a 64-unit leaf each, 16 lanes a signal and the boxes in two levels
-// measured 50 us for the former: the few signals with a poor first bound held up the launch,
-// hence the second attempt with a better bound, and finer cells in the unit order (64 a side,
-// cubes, instead of 32 fitted to the box).
+// signals an iteration's find takes 8 us of gather and 17 us of search with its claims, where
+// staging, the exhaustive screen on the matrix cores and its merge took 125; at 100,000 and
+// 65,536, 6 + 41 us where they took 231.  What it took: boxes in three levels with leaves of 32
+// units (88 us with 64 and two levels), cells in cubes, 64 a side (32 a side fitted to the box:
+// a quarter more leaves), and the tries below, without which the few signals with a poor first
+// bound (one unit in their cell, the next in Morton order far off) held up four launches in
+// ten by 12 to 40 us.  16 lanes a signal measured 26.3 and 43.6 us, 8 and 4 lanes more.
 #include <type_traits>
 
 #include "gsn_internal.h"
@@ -38,7 +39,7 @@ namespace {
 constexpr int kLeaf = kPrunedLeaf;
 constexpr int kTop = kPrunedTop;
 constexpr int kFan = kTop / kLeaf;   // leaves of a top
-constexpr int32_t kWideBatch = 32768;   // signals up to which a signal gets 32 lanes, not 16
+constexpr int32_t kWideBatch = 8192;    // signals up to which a signal gets a whole wave
 constexpr unsigned long long kNone = ~0ull;
 
 __device__ __forceinline__ unsigned long long pack(float d, int32_t i) {
@@ -239,18 +240,18 @@ struct PrunedArgs {
   int do_claim;
 };
 
-// A signal with more passing tops or leaves than this has a poor first bound (a cell with no
-// units near it): the bound is improved and the boxes are tested again.
-constexpr int kFewTops = 12;
-constexpr int kFewLeaves = 16;
-// With more than this even then (units in many overlapping boxes, or nearly equidistant
-// ones), the boxes are visited one after another.
-constexpr int kMostTops = 32;
+constexpr int kFewUnits = 3;     // a cell with fewer leaves the first bound to a larger one
+// A signal with more passing leaves than this has a poor bound: the nearest of those leaves
+// improves it and the boxes are tested again, up to kTries times in all; on the last try up to
+// kMostLeaves will do.
+constexpr int kFewLeaves = 40;
 constexpr int kMostLeaves = 64;
+constexpr int kMostTops = 32;
+constexpr int kTries = 4;
 
 template <int L>
 __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
-  static_assert(L == 16 || L == 32 || L == 64, "whole rows of 16 lanes");
+  static_assert(L == 32 || L == 64, "two or four rows of 16 lanes");
   static_assert(kFan == 16, "one row of lanes tests the boxes of a node");
   constexpr int kGroups = kBlock / L;
   constexpr int kRows = L / 16;                     // nodes tested side by side
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
   constexpr int kPer = kLeaf * kSide / L;           // units per lane
   constexpr int kUnroll = 2;                        // nodes per row and step
   __shared__ int32_t tops[kGroups][kMostTops + kUnroll * L];
-  __shared__ int32_t leaves[kGroups][kMostLeaves + kUnroll * L];
+  __shared__ int32_t leaves[kGroups][kMostLeaves];
   const int g = threadIdx.x / L, q = threadIdx.x % L;
   const int row = q / 16, c = q % 16;
   const int32_t j = blockIdx.x * kGroups + g;
@@ -273,8 +274,7 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
     const unsigned long long b = __ballot(p);
     if constexpr (L == 64) return b;
     else {
-      const uint32_t half = static_cast<uint32_t>(sh < 32 ? b : b >> 32);
-      return L == 32 ? half : (half >> (sh & 31)) & 0xffffu;
+      return static_cast<uint32_t>(sh == 0 ? b : b >> 32);
     }
   };
   auto count = [](Bits b) {
@@ -331,32 +331,33 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
 
   // (the first supers' boxes are read beside the chain that gives the first bound)
   const float first_sup = sup_box(min(q, nsup - 1));
-  // The leaf at the middle of the signal's cell gives the first bound; with no units in the
+  // The leaf at the middle of the signal's cell gives the first bound; with few units in the
   // cell, of the eight or 64 cells it is one of (consecutive in Morton order).
   const int32_t key = stage_bucket(sx, sy, sz, a.bb);
   int32_t r0 = a.off_u[key], r1 = a.off_u[key + 1];
   {
     const int32_t p0 = a.off_u[key & ~7], p1 = a.off_u[(key | 7) + 1];
     const int32_t g0 = a.off_u[key & ~63], g1 = a.off_u[(key | 63) + 1];
-    if (r1 <= r0) {
-      r0 = p1 > p0 ? p0 : g0;
-      r1 = p1 > p0 ? p1 : g1;
+    if (r1 - r0 < kFewUnits) {
+      const bool parent = p1 - p0 >= kFewUnits;
+      r0 = parent ? p0 : g0;
+      r1 = parent ? p1 : g1;
     }
   }
   const int32_t home = min(max((r0 + r1) / 2 / kLeaf, 0), a.nleaf - 1);
   eval(load_leaf(home, home), false);
   tighten();
 
-  int32_t nl = 0, skip = home, most_tops = kFewTops, most_leaves = kFewLeaves;
+  int32_t nl = 0, skip = home, tried = -1;
   bool many;
-  for (int pass_no = 0;; ++pass_no) {
+  for (int attempt = 1;; ++attempt) {
     // the tops that pass, through the boxes of kFan of them
     int32_t nt = 0;
-    for (int32_t s0 = 0; s0 < nsup && nt <= most_tops; s0 += L) {
+    for (int32_t s0 = 0; s0 < nsup && nt <= kMostTops; s0 += L) {
       const int32_t s = s0 + q;
       const float ls = s0 == 0 ? first_sup : sup_box(min(s, nsup - 1));
       Bits sm = bits(s < nsup && !(ls > bound));
-      while (sm != 0 && nt <= most_tops) {
+      while (sm != 0 && nt <= kMostTops) {
         // kUnroll supers per row at a time
         int32_t t[kUnroll];
         bool have[kUnroll];
@@ -387,54 +388,42 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
       }
     }
     __builtin_amdgcn_wave_barrier();
-    many = nt > most_tops;
+    const int32_t mt = min(nt, kMostTops);
 
-    // their leaves that pass
+    // their leaves that pass, and the nearest of them
     nl = 0;
-    if (!many)
-      for (int32_t k = row; k < nt + row && !many; k += kUnroll * kRows) {
-        int32_t f[kUnroll];
-        float lb[kUnroll];
+    unsigned long long near = kNone;
+    for (int32_t k = row; k < mt + row; k += kUnroll * kRows) {
+      int32_t f[kUnroll];
+      float lb[kUnroll];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) f[u] = tops[g][min(k + u * kRows, nt - 1)] * kFan + c;
+      for (int u = 0; u < kUnroll; ++u) f[u] = tops[g][min(k + u * kRows, mt - 1)] * kFan + c;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) lb[u] = box(a.leaf, min(f[u], a.nleaf - 1));
+      for (int u = 0; u < kUnroll; ++u) lb[u] = box(a.leaf, min(f[u], a.nleaf - 1));
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const bool pass = k + u * kRows < nt && f[u] < a.nleaf && f[u] != skip &&
-                            !(lb[u] > bound);
-          const Bits b = bits(pass);
-          if (pass) leaves[g][nl + below(b)] = f[u];
-          nl += count(b);
-        }
-        many = nl > most_leaves;
+      for (int u = 0; u < kUnroll; ++u) {
+        const bool pass = k + u * kRows < mt && f[u] < a.nleaf && f[u] != skip &&
+                          !(lb[u] > bound);
+        if (pass && f[u] != tried) near = min(near, pack(lb[u], f[u]));
+        const Bits b = bits(pass);
+        const int32_t at = nl + below(b);
+        if (pass && at < kMostLeaves) leaves[g][at] = f[u];
+        nl += count(b);
       }
-    __builtin_amdgcn_wave_barrier();
-    if (!many || pass_no == 1) break;
-
-    // A better bound: the nearest leaves of the nearest top of the nearest super.  Then from
-    // an empty list (a leaf enters the list of the two nearest once).
-    auto nearest = [&](unsigned long long v) {
-      return static_cast<int32_t>(static_cast<uint32_t>(min_group<L>(v)));
-    };
-    unsigned long long best = kNone;
-    for (int32_t s = q; s < nsup; s += L) best = min(best, pack(sup_box(s), s));
-    const int32_t tn = min(nearest(best) * kFan + c, a.ntop - 1);
-    const int32_t fn = min(nearest(pack(box(a.top, tn), tn)) * kFan + c, a.nleaf - 1);
-    unsigned long long mine = pack(box(a.leaf, fn), fn);   // (each row holds all of them)
-    for (int i = 0; i < kFan; ++i) {
-      best = min_group<L>(mine);
-      if (best == kNone || __uint_as_float(static_cast<uint32_t>(best >> 32)) > bound) break;
-      if (mine == best) mine = kNone;
-      const int32_t lf = static_cast<int32_t>(static_cast<uint32_t>(best));
-      k1 = k2 = kNone;
-      eval(load_leaf(lf, lf), false);
-      tighten();
     }
+    __builtin_amdgcn_wave_barrier();
+    many = nt > kMostTops || nl > kMostLeaves;
+    if (attempt == kTries || (!many && nl <= kFewLeaves)) break;
+
+    // (with each try the lists start again from nothing: a unit enters them once)
+    near = min_group<L>(near);
+    if (near == kNone) break;
+    tried = static_cast<int32_t>(static_cast<uint32_t>(near));
+    k1 = k2 = kNone;
+    eval(load_leaf(tried, tried), false);
+    tighten();
     k1 = k2 = kNone;
     skip = -1;
-    most_tops = kMostTops;
-    most_leaves = kMostLeaves;
   }
   if (!many) {
     if (nl > 0) {
@@ -517,12 +506,11 @@ hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t n_max, in
     const int per = kBlock / lanes;
     launch_with(k, dim3((m + per - 1) / per), dim3(kBlock), st, ev, a);
   };
-  // Two signals a wave while the waves of the batch fit the device about twice over (16,384
-  // signals, 200,000 units: 14.5 us against 16.9 with four; 2,999 signals, 37,501 units: 14.6
-  // against 16.6), four beyond, where the vector unit is busy and the reductions count (65,536
-  // signals, 100,000 units: 48.0 us against 50.3).
-  if (m <= kWideBatch) go(pr_search<32>, 32);
-  else go(pr_search<16>, 16);
+  // A wave per signal while the batch leaves waves free (8,192 signals, 50,000 units: 13.8 us
+  // against 14.7), two signals a wave beyond (16,384 signals, 200,000 units: 17.0 against 20.8;
+  // 65,536 signals, 100,000 units: 41.5 against 42.0).
+  if (m <= kWideBatch) go(pr_search<64>, 64);
+  else go(pr_search<32>, 32);
   return hipGetLastError();
 }
 

@@ -37,7 +37,7 @@ def shape(kind, n, m, seed):
 @pytest.mark.parametrize("kind", ["random", "grid", "clusters", "sphere", "line", "overflow"])
 @pytest.mark.parametrize("n,m", [(2, 257), (31, 300), (32, 257), (33, 1_000), (511, 300),
                                  (513, 999), (8_192, 257), (8_193, 301), (20_011, 700),
-                                 (700, 32_769)])
+                                 (700, 8_193)])
 def test_sizes_and_shapes(kind, n, m):
     units, sig = shape(kind, n, m, n + m)
     pair = Pair(units, m_max=m)
