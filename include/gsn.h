@@ -354,13 +354,14 @@ void gsn_destroy(gsn_net* net);
  *   GSN_TUNE_REBUCKET staged find calls (automatic and variants 2-5) between rebuilds of the spatial order
  *                     of the units (it is also rebuilt whenever N or the indices change):
  *                     1..4096, 0 = default (64)
- *   GSN_TUNE_GRID_ROUNDS  rounds of the GSN_LOCK_WINNER update of gsn_adapt and of the
- *                     GSN_LOCK_SET_GREEDY resolve launched over the whole device (each
- *                     skipped once fewer than 32 signals are pending) before the remaining
+ *   GSN_TUNE_GRID_ROUNDS  rounds of the GSN_LOCK_WINNER update of gsn_adapt (each skipped
+ *                     once fewer than 32 signals are pending) and of the GSN_LOCK_SET_GREEDY
+ *                     resolve launched over the whole device before the remaining
  *                     ones run in a single workgroup: 1..32, or 0 = automatic (winner lock:
  *                     u + u / 4 with u one more than the rounds the previous update could
  *                     have used grid-wide, i.e. the rounds that started with 32 or more
- *                     pending, from a pinned host copy of that count; greedy resolve: 4)
+ *                     pending, from a pinned host copy of that count; greedy resolve: 1 up to
+ *                     1,024 signals, else 3)
  * Returns GSN_E_INVAL for an unknown key or value. */
 enum { GSN_TUNE_SPLIT = 1, GSN_TUNE_VARIANT = 2, GSN_TUNE_GRID_ROUNDS = 3, GSN_TUNE_GRAB = 4,
        GSN_TUNE_REBUCKET = 5 };

@@ -489,7 +489,8 @@ hipError_t launch_edges(const DevState& s, int cur, int dpar, int32_t n, int32_t
                         hipStream_t st, int32_t* taken = nullptr);
 // Greedy lock-set resolve (resolve_greedy.hip): rounds of claims over L_j = {b, s} + N(b),
 // grid_rounds grid-wide, the rest in one workgroup.  Uses lock, extra (as the taken marks),
-// pend (signal states), rem and list.
+// pend (signal states: 0 rejected, 2 accepted at the end) and list.  accepted null: the states
+// are the result, and the update that follows writes the acceptance and counts it.
 // claimed: the find's merge made the first round's claims and set the signal states (the
 // lock words are all ones and the taken marks zero between calls, so there is no set-up
 // launch).
@@ -531,7 +532,7 @@ hipError_t launch_winner_local(const DevState& s, int cur, int par, int32_t n,
 // updates, taking the signals in the given order when order is not null (a permutation of
 // 0..m-1, e.g. the staging's spatial order); the rewrite into buffer cur ^ 1 with the error
 // decay (one launch up to kFoldBlocks blocks of units, else degree count, scan and write).
-// With given (the acceptance of the greedy resolve, whose accepted lock sets are disjoint
+// With given (the states of the greedy resolve, 2 for accepted, whose lock sets are disjoint
 // as well) there are no claims and no check: the accepted signals are applied.
 hipError_t launch_iterate_set(const DevState& s, int cur, int dpar, int32_t n, const float* sig,
                               int32_t m, const int32_t* winner, const int32_t* second,

@@ -166,9 +166,9 @@ struct FusedArgs {
   int32_t* apart;  // accepted signals of each workgroup (plain stores)
   int32_t* bdelta;  // change of the half-edge count of every block of kBlock units
   const int32_t* order;  // optional: the signals in a spatial order (a permutation of 0..m-1)
-  const uint8_t* given;  // optional: the acceptance decided already (the greedy resolve, whose
-                         // accepted lock sets are disjoint too): no lock word is read or
-                         // written and no statistic counted
+  const uint8_t* given;  // optional: the outcome decided already (the greedy resolve's states,
+                         // 2 for accepted, whose lock sets are disjoint too): no lock word is
+                         // read or written
 };
 
 // The fused kernels give each signal a group of kGroup lanes of one wave: lane q takes the
@@ -334,7 +334,7 @@ __global__ void fu_check_apply(FusedArgs a) {
   const int32_t j = p < a.m && a.order ? a.order[p] : p;
   bool ok = false;
   // (with the acceptance given, a rejected signal's group has nothing to load or do)
-  if (p < a.m && j >= 0 && j < a.m && (a.given == nullptr || a.given[j] != 0)) {
+  if (p < a.m && j >= 0 && j < a.m && (a.given == nullptr || a.given[j] == 2)) {
     const int32_t b = a.winner[j], s = a.second[j];
     const float dj = a.d1[j];
     const float sx = a.sig[j], sy = a.sig[a.m + j], sz = a.sig[2 * a.m + j];
@@ -390,7 +390,7 @@ __global__ void fu_check_apply(FusedArgs a) {
         visit(b, lb);
         if (!s_nb) visit(s, ls);
       }
-      ok = gv ? a.given[j] != 0 : group_bits(__ballot(!mine)) == 0;
+      ok = gv || group_bits(__ballot(!mine)) == 0;
       if (ok) {
         // move_unit's expression on positions already loaded
         auto move = [&](int32_t u, float eps, float px, float py, float pz) {
@@ -437,9 +437,9 @@ __global__ void fu_check_apply(FusedArgs a) {
         }
       }
     }
-    if (q == 0) a.accepted[j] = ok ? 1 : 0;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && a.given == nullptr)
+  if (p < a.m && j >= 0 && j < a.m && q == 0) a.accepted[j] = ok ? 1 : 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0)
     atomicAdd(&a.acc64[kA64Resolved], static_cast<unsigned long long>(a.m));
   // the workgroup's accepted count goes to its own word; the degree count that follows
   // adds them with one atomic (hundreds of same-address atomics at the end of this launch
@@ -837,8 +837,7 @@ hipError_t launch_iterate_set(const DevState& s, int cur, int dpar, int32_t n, c
   int32_t* bd = s.bdelta[dpar];
   int32_t* bd_next = s.bdelta[dpar ^ 1];
   const int gb = blocks(static_cast<int64_t>(m) * kGroup);
-  // the accepted counts go to the statistics unless the resolve that decided them counted
-  const int32_t* apart = m > 0 && !given ? s.apart : nullptr;
+  const int32_t* apart = m > 0 ? s.apart : nullptr;   // the accepted counts, for the statistics
   // after the greedy resolve its taken marks are cleared for the next call
   int32_t* taken = given ? s.extra : nullptr;
   if (m > 0) {
