@@ -2,11 +2,18 @@
 // applied to every signal of the batch.  A grid of cubes of side h over an axis-parallel
 // box holds the units, counting-sorted by cube every call (units move every iteration); the
 // winner and the second of a signal are searched among the units of its cube and the 26
-// neighbours, one lane per cube (a group of 32 lanes per signal, the lanes' top-2 keys
-// merged by shuffles), and signals whose 27 cubes hold fewer than two units get the
+// neighbours (a group of 32 lanes per signal, the lanes' top-2 keys
+// merged), and signals whose 27 cubes hold fewer than two units get the
 // exhaustive search.  Results equal the oracle's indexed search bit for bit: the same cell
 // function, the same direct-form distance, the same (d, index) order.  In exact mode the
 // 27-cube result is kept only where it is certified to be the exhaustive one.
+//
+// The build waits on atomics and on the number of its launches, the query on dependent loads.
+// The count's returned rank places a unit, so the scatter makes no atomic; the scan takes two
+// launches; and a query deals the units of the nine rows of three cubes (consecutive in the
+// sorted order) out to its 32 lanes, where a lane per cube left most lanes idle behind the
+// fullest cube.  At 200,000 units, 16,384 signals and 163,000 cubes (a side of 3.3 spacings): count
+// 12.8 -> 13.2 us, scan 11.1 -> 8.3, scatter 16.3 -> 5.5, query 35.7 -> 9.8, the call 83 -> 44.
 #include "gsn_internal.h"
 
 namespace gsn {
@@ -15,7 +22,10 @@ namespace {
 constexpr int kGroupLanes = 32;            // lanes per signal (27 cubes, 5 idle)
 constexpr int kQueryBlock = 256;           // 8 signals per workgroup
 constexpr int kFallbackBlocks = 256;
-constexpr unsigned long long kNoKey = ~0ull;
+constexpr int kScanPart = 4 * kBlock;      // cubes per workgroup of the scan
+constexpr int kRankBits = 8;               // of a unit's rank in its cube, beside its cube
+constexpr int32_t kRankMax = (1 << kRankBits) - 1;   // ranks from here on come from a cursor
+static_assert(GSN_MAX_GRID_CELLS <= (1 << (31 - kRankBits + 1)), "cube and rank in 32 bits");
 
 inline int blocks(int64_t n) { return static_cast<int>((n + kBlock - 1) / kBlock); }
 
@@ -38,11 +48,6 @@ __device__ __forceinline__ void cell_of(const GridArgs& g, float x, float y, flo
   c[0] = grid_axis(x, g.lo0, g.inv_h, g.d0);
   c[1] = grid_axis(y, g.lo1, g.inv_h, g.d1);
   c[2] = grid_axis(z, g.lo2, g.inv_h, g.d2);
-}
-
-// (d, index) key: the unsigned order of the key is the lexicographic order (d >= +0).
-__device__ __forceinline__ unsigned long long dkey(float d, int32_t i) {
-  return (static_cast<unsigned long long>(__float_as_uint(d)) << 32) | static_cast<uint32_t>(i);
 }
 
 __device__ __forceinline__ float direct_d(float sx, float sy, float sz, float wx, float wy,
@@ -104,94 +109,134 @@ __global__ void gx_count(int32_t n, const float* __restrict__ x, const float* __
   int32_t c[3];
   cell_of(g, x[u], y[u], z[u], c);
   const int32_t lin = (c[2] * g.d1 + c[1]) * g.d0 + c[0];
-  ucell[u] = lin;
-  atomicAdd(&cnt[lin], 1);
+  // the count's old value is the unit's rank in its cube (the order inside a cube is immaterial)
+  const int32_t rank = min(atomicAdd(&cnt[lin], 1), kRankMax);
+  ucell[u] = static_cast<int32_t>((static_cast<uint32_t>(lin) << kRankBits) |
+                                  static_cast<uint32_t>(rank));
 }
 
-__global__ void gx_bsum(int32_t cells, const int32_t* __restrict__ cnt,
-                        int32_t* __restrict__ bsum) {
-  __shared__ int32_t red[kBlock];
-  const int32_t c = blockIdx.x * kBlock + threadIdx.x;
-  red[threadIdx.x] = c < cells ? cnt[c] : 0;
-  __syncthreads();
-  for (int w = kBlock / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) bsum[blockIdx.x] = red[0];
+__device__ __forceinline__ int4 load_counts(const int32_t* __restrict__ cnt, int32_t c,
+                                            int32_t cells) {
+  if (c + 3 < cells) return *reinterpret_cast<const int4*>(cnt + c);
+  return make_int4(c < cells ? cnt[c] : 0, c + 1 < cells ? cnt[c + 1] : 0,
+                   c + 2 < cells ? cnt[c + 2] : 0, 0);
 }
 
-// start[c] = units in the cubes before c; cnt[c] becomes the scatter cursor start[c].
-__global__ void gx_start(int32_t cells, int32_t n, int32_t* __restrict__ cnt,
-                         const int32_t* __restrict__ boff, int32_t* __restrict__ start) {
-  __shared__ int32_t sc[kBlock];
-  const int32_t c = blockIdx.x * kBlock + threadIdx.x;
-  const int32_t v = c < cells ? cnt[c] : 0;
-  sc[threadIdx.x] = v;
-  __syncthreads();
-  for (int off = 1; off < kBlock; off <<= 1) {
-    const int32_t t = threadIdx.x >= off ? sc[threadIdx.x - off] : 0;
-    __syncthreads();
-    sc[threadIdx.x] += t;
-    __syncthreads();
-  }
-  if (c < cells) {
-    const int32_t s = boff[blockIdx.x] + sc[threadIdx.x] - v;
-    start[c] = s;
-    cnt[c] = s;
-  }
+__global__ __launch_bounds__(kBlock) void gx_bsum(int32_t cells, const int32_t* __restrict__ cnt,
+                                                  int32_t* __restrict__ bsum) {
+  __shared__ int32_t wt[kBlock / 64];
+  const int32_t c = (blockIdx.x * kBlock + threadIdx.x) * 4;
+  const int4 v = load_counts(cnt, c, cells);
+  const int32_t t = block_sum(v.x + v.y + v.z + v.w, wt);
+  if (threadIdx.x == 0) bsum[blockIdx.x] = t;
+}
+
+// start[c] = units in the cubes before c; cnt[c] becomes the cursor of the units of rank
+// kRankMax and up.  With fold, each workgroup sums the parts before its own itself.
+__global__ __launch_bounds__(kBlock) void gx_start(int32_t cells, int32_t n,
+                                                   int32_t* __restrict__ cnt,
+                                                   const int32_t* __restrict__ bsum, int32_t nb,
+                                                   int fold, int32_t* __restrict__ start) {
+  __shared__ int32_t red[2 * kBlock / 64];
+  __shared__ int32_t wt[kBlock / 64];
+  const int32_t c = (blockIdx.x * kBlock + threadIdx.x) * 4;
+  const int4 v = load_counts(cnt, c, cells);
+  int32_t before, total;
+  if (fold) fold_offsets(bsum, nb, red, &before, &total);
+  else before = bsum[blockIdx.x];
+  const int32_t sum = v.x + v.y + v.z + v.w;
+  const int32_t o0 = before + block_inclusive_scan(sum, wt) - sum;
+  const int32_t o[4] = {o0, o0 + v.x, o0 + v.x + v.y, o0 + v.x + v.y + v.z};
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (c + k < cells) {
+      start[c + k] = o[k];
+      cnt[c + k] = o[k] + kRankMax;
+    }
   if (c == 0) start[cells] = n;
 }
 
 __global__ void gx_scatter(int32_t n, const float* __restrict__ x, const float* __restrict__ y,
                            const float* __restrict__ z, const int32_t* __restrict__ ucell,
-                           int32_t* __restrict__ cursor, float4* __restrict__ sorted) {
+                           const int32_t* __restrict__ start, int32_t* __restrict__ cursor,
+                           float4* __restrict__ sorted) {
   const int32_t u = blockIdx.x * kBlock + threadIdx.x;
   if (u >= n) return;
-  const int32_t pos = atomicAdd(&cursor[ucell[u]], 1);
-  sorted[pos] = make_float4(x[u], y[u], z[u], __int_as_float(u));
+  const uint32_t w = static_cast<uint32_t>(ucell[u]);
+  const int32_t lin = static_cast<int32_t>(w >> kRankBits);
+  const int32_t rank = static_cast<int32_t>(w & kRankMax);
+  const float4 p = make_float4(x[u], y[u], z[u], __int_as_float(u));
+  const int32_t pos = rank < kRankMax ? start[lin] + rank : atomicAdd(&cursor[lin], 1);
+  if (pos >= 0 && pos < n) sorted[pos] = p;   // always true when counts match cubes
 }
 
-// 32 lanes per signal: lane q < 27 scans cube (cx + q % 3 - 1, cy + (q / 3) % 3 - 1,
-// cz + q / 9 - 1).  The lanes' top-2 keys and candidate counts are merged by shuffles
-// within the 32 lanes; fewer than two candidates (or, in exact mode, a result that cannot
-// be certified) sends the signal to the fallback list.
-__global__ void gx_query(const float* __restrict__ sig, int32_t m, GridArgs g,
-                         const int32_t* __restrict__ start, const float4* __restrict__ sorted,
-                         int32_t* __restrict__ winner, int32_t* __restrict__ second,
-                         float* __restrict__ d1, float* __restrict__ d2,
-                         int32_t* __restrict__ fb_list, int32_t* __restrict__ nfb) {
+// 32 lanes per signal.  Lane r < 9 reads the bounds of row r: the cubes (cx - 1 .. cx + 1,
+// cy + r % 3 - 1, cz + r / 3 - 1), consecutive in the sorted order.  The rows' units are
+// numbered through and unit i goes to lane i mod 32.  Fewer than two candidates (or, in exact
+// mode, a result that cannot be certified) sends the signal to the fallback list.
+__global__ __launch_bounds__(kQueryBlock) void gx_query(
+    const float* __restrict__ sig, int32_t m, GridArgs g, const int32_t* __restrict__ start,
+    const float4* __restrict__ sorted, int32_t* __restrict__ winner,
+    int32_t* __restrict__ second, float* __restrict__ d1, float* __restrict__ d2,
+    int32_t* __restrict__ fb_list, int32_t* __restrict__ nfb) {
+  constexpr int kRowsOf = 9;
+  __shared__ int32_t first[kQueryBlock / kGroupLanes][kRowsOf + 1];   // unit number of a row's first
+  __shared__ int32_t shift[kQueryBlock / kGroupLanes][kRowsOf];       // sorted slot - unit number
   const int32_t gt = blockIdx.x * kQueryBlock + threadIdx.x;
   const int32_t j = gt / kGroupLanes;
-  const int q = gt % kGroupLanes;
+  const int q = gt % kGroupLanes, gr = threadIdx.x / kGroupLanes;
   if (j >= m) return;  // whole groups: m groups fill the grid exactly up to the last block
   const float sx = sig[j], sy = sig[m + j], sz = sig[2 * m + j];
   int32_t c[3];
   cell_of(g, sx, sy, sz, c);
-  unsigned long long k1 = kNoKey, k2 = kNoKey;
-  int32_t found = 0;
-  if (q < 27) {
-    const int32_t cx = c[0] + q % 3 - 1, cy = c[1] + (q / 3) % 3 - 1, cz = c[2] + q / 9 - 1;
-    if (cx >= 0 && cx < g.d0 && cy >= 0 && cy < g.d1 && cz >= 0 && cz < g.d2) {
-      const int32_t lin = (cz * g.d1 + cy) * g.d0 + cx;
-      const int32_t a = start[lin], b = start[lin + 1];
-      found = b - a;
-      for (int32_t k = a; k < b; ++k) {
-        const float4 w = sorted[k];
-        top2_insert(dkey(direct_d(sx, sy, sz, w.x, w.y, w.z), __float_as_int(w.w)), k1, k2);
-      }
+  int32_t a = 0, len = 0;
+  if (q < kRowsOf) {
+    const int32_t cy = c[1] + q % 3 - 1, cz = c[2] + q / 3 - 1;
+    if (cy >= 0 && cy < g.d1 && cz >= 0 && cz < g.d2) {
+      const int32_t base = (cz * g.d1 + cy) * g.d0;
+      a = start[base + max(c[0] - 1, 0)];
+      len = start[base + min(c[0] + 1, g.d0 - 1) + 1] - a;
     }
   }
-  for (int off = kGroupLanes / 2; off > 0; off >>= 1) {
-    const unsigned long long o1 = __shfl_xor(k1, off, kGroupLanes);
-    const unsigned long long o2 = __shfl_xor(k2, off, kGroupLanes);
-    found += __shfl_xor(found, off, kGroupLanes);
-    // top two of {k1, k2, o1, o2} (each pair ascending, all keys distinct or none)
-    const unsigned long long lo = k1 < o1 ? k1 : o1, hi = k1 < o1 ? o1 : k1;
-    const unsigned long long rest = k2 < o2 ? k2 : o2;
-    k1 = lo;
-    k2 = hi < rest ? hi : rest;
+  int32_t inc = len;
+#pragma unroll
+  for (int o = 1; o < 16; o <<= 1) {
+    const int32_t v = __shfl_up(inc, o, kGroupLanes);
+    if (q >= o) inc += v;
   }
+  if (q < kRowsOf) {
+    first[gr][q] = inc - len;
+    shift[gr][q] = a - (inc - len);
+  }
+  if (q == kRowsOf) first[gr][kRowsOf] = inc;
+  __builtin_amdgcn_wave_barrier();
+  int32_t f[kRowsOf + 1];
+#pragma unroll
+  for (int r = 0; r <= kRowsOf; ++r) f[r] = first[gr][r];
+  const int32_t found = f[kRowsOf];
+  unsigned long long k1 = kNone, k2 = kNone;
+  // two units per step, their loads side by side (past the last one the last repeats)
+  for (int32_t i = q; i < found; i += 2 * kGroupLanes) {
+    float4 w[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int32_t ih = min(i + h * kGroupLanes, found - 1);
+      int32_t r = 0;
+#pragma unroll
+      for (int k = 1; k < kRowsOf; ++k) r += f[k] <= ih;
+      w[h] = sorted[ih + shift[gr][r]];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const unsigned long long k =
+          i + h * kGroupLanes < found
+              ? pack_key(direct_d(sx, sy, sz, w[h].x, w[h].y, w[h].z), __float_as_int(w[h].w))
+              : kNone;
+      k2 = min(k2, max(k1, k));
+      k1 = min(k1, k);
+    }
+  }
+  merge_group<kGroupLanes>(k1, k2);
   if (q != 0) return;
   if (found < 2 ||
       (g.exact && !certified(g, sx, sy, sz, c, __uint_as_float(static_cast<uint32_t>(k2 >> 32))))) {
@@ -217,9 +262,9 @@ __global__ void gx_fallback(const float* __restrict__ sig, int32_t m, int32_t n,
   for (int32_t e = blockIdx.x; e < count; e += gridDim.x) {
     const int32_t j = fb_list[e];
     const float sx = sig[j], sy = sig[m + j], sz = sig[2 * m + j];
-    unsigned long long k1 = kNoKey, k2 = kNoKey;
+    unsigned long long k1 = kNone, k2 = kNone;
     for (int32_t i = threadIdx.x; i < n; i += kBlock)
-      top2_insert(dkey(direct_d(sx, sy, sz, x[i], y[i], z[i]), i), k1, k2);
+      top2_insert(pack_key(direct_d(sx, sy, sz, x[i], y[i], z[i]), i), k1, k2);
     s1[threadIdx.x] = k1;
     s2[threadIdx.x] = k2;
     __syncthreads();
@@ -289,12 +334,16 @@ hipError_t launch_find_grid(const DevState& s, const GridBufs& gb, const GridSpe
                    spec.dims[0], spec.dims[1], spec.dims[2], spec.exact};
   gx_clear<<<std::min(blocks(cells), 1024), kBlock, 0, st>>>(gb.cnt, cells, gb.nfb);
   gx_count<<<blocks(n), kBlock, 0, st>>>(n, s.x, s.y, s.z, g, gb.ucell, gb.cnt);
-  const int nb = blocks(cells);
+  const int nb = static_cast<int>((cells + kScanPart - 1) / kScanPart);
   gx_bsum<<<nb, kBlock, 0, st>>>(cells, gb.cnt, gb.bsum);
-  hipError_t e = launch_scan_blocks(gb.bsum, nb, INT64_MAX, nullptr, s.status, -1, st);
-  if (e != hipSuccess) return e;
-  gx_start<<<nb, kBlock, 0, st>>>(cells, n, gb.cnt, gb.bsum, gb.start);
-  gx_scatter<<<blocks(n), kBlock, 0, st>>>(n, s.x, s.y, s.z, gb.ucell, gb.cnt, gb.sorted);
+  if (nb > kFoldBlocks) {
+    const hipError_t e = launch_scan_blocks(gb.bsum, nb, INT64_MAX, nullptr, s.status, -1, st);
+    if (e != hipSuccess) return e;
+  }
+  gx_start<<<nb, kBlock, 0, st>>>(cells, n, gb.cnt, gb.bsum, nb, nb <= kFoldBlocks ? 1 : 0,
+                                  gb.start);
+  gx_scatter<<<blocks(n), kBlock, 0, st>>>(n, s.x, s.y, s.z, gb.ucell, gb.start, gb.cnt,
+                                           gb.sorted);
   const int64_t lanes = static_cast<int64_t>(m) * kGroupLanes;
   gx_query<<<static_cast<int>((lanes + kQueryBlock - 1) / kQueryBlock), kQueryBlock, 0, st>>>(
       sig, m, g, gb.start, gb.sorted, winner, second, d1, d2, gb.fb_list, gb.nfb);

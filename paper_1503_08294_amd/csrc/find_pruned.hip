@@ -40,50 +40,6 @@ constexpr int kLeaf = kPrunedLeaf;
 constexpr int kTop = kPrunedTop;
 constexpr int kFan = kTop / kLeaf;   // leaves of a top
 constexpr int32_t kWideBatch = 8192;    // signals up to which a signal gets a whole wave
-constexpr unsigned long long kNone = ~0ull;
-
-__device__ __forceinline__ unsigned long long pack(float d, int32_t i) {
-  return (static_cast<unsigned long long>(__float_as_uint(d)) << 32) |
-         static_cast<uint32_t>(i);
-}
-
-// top-2 of two top-2 lists whose real keys are distinct (kNone may repeat)
-__device__ __forceinline__ void merge2(unsigned long long& a1, unsigned long long& a2,
-                                       unsigned long long b1, unsigned long long b2) {
-  const unsigned long long lo = min(a1, b1), hi = max(a1, b1);
-  a2 = min(hi, min(a2, b2));
-  a1 = lo;
-}
-
-// the value of another lane of the same 16-lane row
-template <int CTRL>
-__device__ __forceinline__ unsigned long long row_move(unsigned long long v) {
-  const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(v >> 32), CTRL, 0xf, 0xf, true);
-  return (static_cast<unsigned long long>(static_cast<uint32_t>(hi)) << 32) |
-         static_cast<uint32_t>(lo);
-}
-
-template <int CTRL>
-__device__ __forceinline__ void merge_row(unsigned long long& k1, unsigned long long& k2) {
-  const unsigned long long o1 = row_move<CTRL>(k1), o2 = row_move<CTRL>(k2);
-  merge2(k1, k2, o1, o2);
-}
-
-// top-2 over the L lanes of a group, in every lane (each step pairs lanes that hold the
-// lists of disjoint halves)
-template <int L>
-__device__ __forceinline__ void merge_group(unsigned long long& k1, unsigned long long& k2) {
-  merge_row<0xB1>(k1, k2);                       // quad_perm 1,0,3,2
-  merge_row<0x4E>(k1, k2);                       // quad_perm 2,3,0,1
-  merge_row<0x141>(k1, k2);                      // row_half_mirror
-  merge_row<0x140>(k1, k2);                      // row_mirror
-#pragma unroll
-  for (int off = 16; off < L; off <<= 1) {
-    const unsigned long long o1 = __shfl_xor(k1, off), o2 = __shfl_xor(k2, off);
-    merge2(k1, k2, o1, o2);
-  }
-}
 
 // minimum over the L lanes of a group, in every lane
 template <int L>
@@ -304,7 +260,7 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
       const float dx = sx - u.w[i].x, dy = sy - u.w[i].y, dz = sz - u.w[i].z;
       const float d = (dx * dx + dy * dy) + dz * dz;
       if (!(d > bound) && (kSide == 1 || both || q < kLeaf)) {
-        const unsigned long long k = pack(d, __float_as_int(u.w[i].w));
+        const unsigned long long k = pack_key(d, __float_as_int(u.w[i].w));
         entered |= k < k2;
         k2 = min(k2, max(k1, k));
         k1 = min(k1, k);
@@ -404,7 +360,7 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
       for (int u = 0; u < kUnroll; ++u) {
         const bool pass = k + u * kRows < mt && f[u] < a.nleaf && f[u] != skip &&
                           !(lb[u] > bound);
-        if (pass && f[u] != tried) near = min(near, pack(lb[u], f[u]));
+        if (pass && f[u] != tried) near = min(near, pack_key(lb[u], f[u]));
         const Bits b = bits(pass);
         const int32_t at = nl + below(b);
         if (pass && at < kMostLeaves) leaves[g][at] = f[u];

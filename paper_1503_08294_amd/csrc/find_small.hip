@@ -24,20 +24,6 @@ namespace {
 constexpr int kSmallTile = 1024;         // units per LDS tile
 constexpr int kSmallPerThread = 16;      // units per thread the chunking aims at (one tile
                                          // per workgroup, so one round of global loads)
-constexpr unsigned long long kNone = ~0ull;
-
-__device__ __forceinline__ unsigned long long pack(float d, int32_t i) {
-  return (static_cast<unsigned long long>(__float_as_uint(d)) << 32) |
-         static_cast<uint32_t>(i);
-}
-
-// top-2 of two top-2 lists whose real keys are distinct (kNone may repeat)
-__device__ __forceinline__ void merge2(unsigned long long& a1, unsigned long long& a2,
-                                       unsigned long long b1, unsigned long long b2) {
-  const unsigned long long lo = min(a1, b1), hi = max(a1, b1);
-  a2 = min(hi, min(a2, b2));
-  a1 = lo;
-}
 
 // distance of the second key, +inf while the list holds fewer than two units
 __device__ __forceinline__ float second_dist(unsigned long long k2) {
@@ -59,7 +45,7 @@ __device__ __forceinline__ float dist(float sx, float sy, float sz, float4 w) {
 __device__ __forceinline__ void consider(float d, int32_t i, unsigned long long& k1,
                                          unsigned long long& k2, float& d2f) {
   if (d < d2f || (d == d2f && k2 == kNone)) {
-    const unsigned long long key = pack(d, i);
+    const unsigned long long key = pack_key(d, i);
     const bool lt1 = key < k1;
     k2 = lt1 ? k1 : key;
     k1 = lt1 ? key : k1;

@@ -99,6 +99,53 @@ __device__ __forceinline__ unsigned long long signal_key(float d1, int32_t j, in
   return (static_cast<unsigned long long>(__float_as_uint(d1)) << 32) | lo;
 }
 
+// The two nearest as packed keys (bits(d) << 32) | index, whose unsigned order is the
+// lexicographic one of (d, index) for d >= +0; kNone in an empty place.
+constexpr unsigned long long kNone = ~0ull;
+
+__device__ __forceinline__ unsigned long long pack_key(float d, int32_t i) {
+  return (static_cast<unsigned long long>(__float_as_uint(d)) << 32) |
+         static_cast<uint32_t>(i);
+}
+
+// top-2 of two ascending top-2 lists whose real keys are distinct (kNone may repeat)
+__device__ __forceinline__ void merge2(unsigned long long& a1, unsigned long long& a2,
+                                       unsigned long long b1, unsigned long long b2) {
+  const unsigned long long lo = min(a1, b1), hi = max(a1, b1);
+  a2 = min(hi, min(a2, b2));
+  a1 = lo;
+}
+
+// the value of another lane of the same 16-lane row
+template <int CTRL>
+__device__ __forceinline__ unsigned long long row_move(unsigned long long v) {
+  const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(v >> 32), CTRL, 0xf, 0xf, true);
+  return (static_cast<unsigned long long>(static_cast<uint32_t>(hi)) << 32) |
+         static_cast<uint32_t>(lo);
+}
+
+template <int CTRL>
+__device__ __forceinline__ void merge_row(unsigned long long& k1, unsigned long long& k2) {
+  const unsigned long long o1 = row_move<CTRL>(k1), o2 = row_move<CTRL>(k2);
+  merge2(k1, k2, o1, o2);
+}
+
+// top-2 over the L lanes of a group, in every lane (each step pairs lanes that hold the
+// lists of disjoint halves)
+template <int L>   // 16, 32 or 64
+__device__ __forceinline__ void merge_group(unsigned long long& k1, unsigned long long& k2) {
+  merge_row<0xB1>(k1, k2);                       // quad_perm 1,0,3,2
+  merge_row<0x4E>(k1, k2);                       // quad_perm 2,3,0,1
+  merge_row<0x141>(k1, k2);                      // row_half_mirror
+  merge_row<0x140>(k1, k2);                      // row_mirror
+#pragma unroll
+  for (int off = 16; off < L; off <<= 1) {
+    const unsigned long long o1 = __shfl_xor(k1, off), o2 = __shfl_xor(k2, off);
+    merge2(k1, k2, o1, o2);
+  }
+}
+
 // Adds the threads of this workgroup for which `pred` holds to *ctr with one atomic per
 // workgroup (same-address atomics from thousands of waves queue up at the cache).  Every
 // thread of the workgroup calls it (it holds a barrier); `acc` is an LDS word that was

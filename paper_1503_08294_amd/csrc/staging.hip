@@ -303,19 +303,6 @@ __global__ __launch_bounds__(kBlock) void st_gather(const float* __restrict__ x,
 }
 
 
-__device__ __forceinline__ unsigned long long pack(float d, int32_t i) {
-  return (static_cast<unsigned long long>(__float_as_uint(d)) << 32) |
-         static_cast<uint32_t>(i);
-}
-
-// top-2 of two top-2 lists of distinct keys
-__device__ __forceinline__ void merge2(unsigned long long& a1, unsigned long long& a2,
-                                       unsigned long long b1, unsigned long long b2) {
-  const unsigned long long lo = min(a1, b1), hi = max(a1, b1);
-  a2 = min(hi, min(a2, b2));
-  a1 = lo;
-}
-
 // Places the signals in bucket order and computes their seed bounds, in one launch.  Every
 // workgroup scans the signal histogram (kSignalBuckets bins, zeroed by the previous call) in
 // LDS itself, so the bins' offsets need no launch of their own; a signal's sorted position is
@@ -369,7 +356,7 @@ __global__ __launch_bounds__(kBlock) void st_place_seed(
         const int32_t r = lo + q + i * kSeedLanes;
         const float dx = sx - wu[i].x, dy = sy - wu[i].y, dz = sz - wu[i].z;
         const unsigned long long kk =
-            r < hi ? pack((dx * dx + dy * dy) + dz * dz, r) : ~0ull;
+            r < hi ? pack_key((dx * dx + dy * dy) + dz * dz, r) : ~0ull;
         merge2(k1, k2, kk, ~0ull);
       }
     }
