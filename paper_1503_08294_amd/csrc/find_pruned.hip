@@ -31,7 +31,7 @@
 // ten by 12 to 40 us.  16 lanes a signal measured 26.3 and 43.6 us, 8 and 4 lanes more.
 #include <type_traits>
 
-#include "gsn_internal.h"
+#include "pruned_gather.h"
 
 namespace gsn {
 namespace {
@@ -64,91 +64,9 @@ __device__ __forceinline__ float box_bound(float sx, float sy, float sz, float4 
 
 // ------------------------------------------------------------------- gather ----
 
-struct FMin { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
-struct FMax { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
-
-template <int CTRL, typename Op>
-__device__ __forceinline__ float row_step(float v, Op op) {
-  return op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf,
-                                                       true)));
-}
-
-// over the 16 lanes of a row, in every lane
-template <typename Op>
-__device__ __forceinline__ float row_reduce(float v, Op op) {
-  v = row_step<0xB1>(v, op);
-  v = row_step<0x4E>(v, op);
-  v = row_step<0x141>(v, op);
-  return row_step<0x140>(v, op);
-}
-
-// over the kLeaf lanes that hold a leaf
-template <typename Op>
-__device__ __forceinline__ float leaf_reduce(float v, Op op) {
-  v = row_reduce(v, op);
-  return op(v, __shfl_xor(v, 16));
-}
-
-// One workgroup per top, half a wave per leaf.  The last leaf's slots past n hold NaN records
-// with index -1, whose keys are above every real one; leaves wholly past n are not written
-// (nobody reads them).
-__global__ __launch_bounds__(kTop) void pr_gather(const float* __restrict__ x,
-                                                  const float* __restrict__ y,
-                                                  const float* __restrict__ z, int32_t n,
-                                                  const int32_t* __restrict__ pidx,
-                                                  float4* __restrict__ pq,
-                                                  float4* __restrict__ leaf,
-                                                  float4* __restrict__ top,
-                                                  int32_t* __restrict__ sup,
-                                                  int32_t* __restrict__ sup_next,
-                                                  int32_t sup_words) {
-  __shared__ float red[kFan][6];
-  const int32_t pos = blockIdx.x * kTop + threadIdx.x;
-  const float inf = __builtin_huge_valf();
-  float lo[3] = {inf, inf, inf}, hi[3] = {-inf, -inf, -inf};
-  const int32_t lf = pos / kLeaf;
-  if (lf * kLeaf < n) {
-    float4 w = make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""),
-                           __int_as_float(-1));
-    if (pos < n) {
-      const int32_t i = min(max(pidx[pos], 0), n - 1);
-      w = make_float4(x[i], y[i], z[i], __int_as_float(i));
-      lo[0] = hi[0] = w.x;
-      lo[1] = hi[1] = w.y;
-      lo[2] = hi[2] = w.z;
-    }
-    pq[pos] = w;
-  }
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    lo[a] = leaf_reduce(lo[a], FMin());
-    hi[a] = leaf_reduce(hi[a], FMax());
-  }
-  const int wv = threadIdx.x / kLeaf;
-  if ((threadIdx.x & (kLeaf - 1)) == 0) {
-    if (lf * kLeaf < n) {
-      leaf[2 * lf] = make_float4(lo[0], lo[1], lo[2], 0.0f);
-      leaf[2 * lf + 1] = make_float4(hi[0], hi[1], hi[2], 0.0f);
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      red[wv][a] = lo[a];
-      red[wv][3 + a] = hi[a];
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < 6) {
-    const int a = threadIdx.x;
-    float v = red[0][a];
-    for (int k = 1; k < kFan; ++k) v = a < 3 ? fminf(v, red[k][a]) : fmaxf(v, red[k][a]);
-    reinterpret_cast<float*>(&top[2 * blockIdx.x + (a < 3 ? 0 : 1)])[a % 3] = v;
-    int32_t* u = &sup[kSupWords * (blockIdx.x / kFan) + a];
-    if (a < 3) atomicMin(u, ord(v)); else atomicMax(u, ord(v));
-  }
-  // the other set, for the next call
-  if (blockIdx.x == 0)
-    for (int32_t i = threadIdx.x; i < sup_words; i += kTop)
-      sup_next[i] = i % kSupWords < 3 ? ord(inf) : ord(-inf);
+__global__ __launch_bounds__(kBlock) void pr_gather(GatherArgs g) {
+  __shared__ float red[kGatherRed];
+  gather_top(g, blockIdx.x, red);
 }
 
 // ------------------------------------------------------------------- search ----
@@ -442,20 +360,25 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
 
 }  // namespace
 
-hipError_t launch_pruned_gather(const DevState& s, const StageBufs& b, int32_t n,
-                                int32_t n_max, int par, hipStream_t st) {
+GatherArgs pruned_gather_args(const DevState& s, const StageBufs& b, int32_t n, int32_t slots,
+                              int32_t n_max, int par) {
   const int32_t words = sup_words(n_max);
-  pr_gather<<<(n + kTop - 1) / kTop, kTop, 0, st>>>(s.x, s.y, s.z, n, b.pidx, b.pq, b.leaf,
-                                                    b.top, b.sup + par * words,
-                                                    b.sup + (par ^ 1) * words, words);
+  return GatherArgs{s.x, s.y, s.z, b.pidx, b.pq, b.leaf, b.top, b.sup + par * words,
+                    b.sup + (par ^ 1) * words, n, slots, (slots + kTop - 1) / kTop, words};
+}
+
+hipError_t launch_pruned_gather(const GatherArgs& g, hipStream_t st) {
+  pr_gather<<<g.tops, kBlock, 0, st>>>(g);
   return hipGetLastError();
 }
 
-hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t n_max, int par, const float* sig, int32_t m,
+hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t slots, int32_t n_max, int par,
+                                const float* sig, int32_t m,
                                 int32_t* winner, int32_t* second, float* d1, float* d2,
                                 const ClaimArgs* claim, hipStream_t st, LaunchEvents ev) {
   if (n < 2 || m < 1) return hipErrorInvalidValue;
-  const PrunedArgs a{b.pq, b.leaf, b.top, b.sup + par * sup_words(n_max), n, (n + kLeaf - 1) / kLeaf, (n + kTop - 1) / kTop,
+  const PrunedArgs a{b.pq, b.leaf, b.top, b.sup + par * sup_words(n_max), n, (slots + kLeaf - 1) / kLeaf,
+                     (slots + kTop - 1) / kTop,
                      b.off_u, b.bb, sig, m, winner, second, d1, d2,
                      claim ? *claim : ClaimArgs{}, claim ? 1 : 0};
   auto go = [&](auto k, int lanes) {

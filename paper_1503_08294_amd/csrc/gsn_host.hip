@@ -176,7 +176,13 @@ struct gsn_net {
   int tune_grab;    // list entries per atomic of the dynamic scan
   int tune_rebucket;  // staged find calls between rebuilds of the spatial unit order
   int stage_parity;  // which set of signal histogram and cursors the next call uses
-  int sup_parity;    // which set of the pruned search's outer boxes the last gather wrote
+  // the pruned search's records: which set of outer boxes the last gather wrote, whether that
+  // gather saw the present positions in the present unit order, and whether growth changed the
+  // units since the last update (then the next update does not gather ahead)
+  int sup_parity;
+  bool staged;
+  bool grew;
+  bool searched;     // the last find took the pruned search
   bool timing;
   uint32_t timing_mask;  // timers that record while timing is on (bit GSN_T_*)
   int32_t bucket_n;            // unit count at the last spatial bucketing (-1: none yet)
@@ -198,9 +204,10 @@ struct gsn_net {
     uint8_t* accepted;
     int32_t n;
     int cur, dpar, wpar, stage_parity, sup_parity;
-    bool rebuild_first;
+    bool rebuild_first, staged, grew;
     int tune_split, tune_variant, tune_grab, tune_rebucket, grid_rounds;
     // the host state the loop leaves
+    bool staged_after;
     bool rebuilt;   // the first find rebuilt the unit order (else finds_delta counts finds)
     int cur_after, dpar_after, wpar_after, stage_parity_after, sup_parity_after;
     int32_t finds_after, finds_delta, bucket_n_after;
@@ -365,6 +372,8 @@ int grow_step(gsn_net* net, int32_t count, int32_t* inserted_out, hipStream_t st
     if (rc) return rc;
     net->n = kept;
     net->bucket_n = -1;  // indices changed
+    net->staged = false;
+    net->grew = true;
   }
   int32_t inserted = 0;
   if (count > 0 && net->n >= 1 && net->n < net->p.n_max) {
@@ -376,6 +385,8 @@ int grow_step(gsn_net* net, int32_t count, int32_t* inserted_out, hipStream_t st
     const int32_t n_before = net->n;
     net->n += inserted;
     if (inserted) {
+      net->staged = false;
+      net->grew = true;
       // new units take the next indices: they join the spatial order at its end (the
       // periodic rebucketing restores locality); after a removal the order is rebuilt
       if (net->bucket_n == n_before) {
@@ -423,6 +434,9 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   net->tune_rebucket = kRebucketEvery;
   net->stage_parity = 0;
   net->sup_parity = 0;
+  net->staged = false;
+  net->grew = false;
+  net->searched = false;
   net->timing = false;
   net->timing_mask = (1u << GSN_T_COUNT) - 1;
   net->bucket_n = -1;
@@ -498,6 +512,7 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
   hipStream_t st = as_stream(stream);
   const gsn::FindConfig cfg =
       gsn::find_config(net->n, m, net->cus, net->tune_split, net->tune_variant);
+  net->searched = cfg.variant == 7;
   TimedRegion all(net, GSN_T_FIND, st);
   hipError_t e;
   if (cfg.variant == 6) {
@@ -520,13 +535,18 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
     }
     if (cfg.variant == 7) {
       e = rebucket ? gsn::launch_stage_order(net->s, sb, net->n, st) : hipSuccess;
-      net->sup_parity ^= 1;
-      if (e == hipSuccess)
-        e = gsn::launch_pruned_gather(net->s, sb, net->n, net->p.n_max, net->sup_parity, st);
+      if (e == hipSuccess && (rebucket || !net->staged)) {
+        net->sup_parity ^= 1;
+        e = gsn::launch_pruned_gather(
+            gsn::pruned_gather_args(net->s, sb, net->n, net->n, net->p.n_max, net->sup_parity),
+            st);
+        net->staged = true;
+      }
     } else {
       e = gsn::launch_stage(net->s, sb, net->n, sig, m, rebucket, net->stage_parity,
                             cfg.variant, st);
       net->stage_parity ^= 1;
+      if (rebucket) net->staged = false;   // a new order, gathered for the scans alone
     }
     if (rebucket) {
       net->bucket_n = net->n;
@@ -535,7 +555,7 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
     ++net->finds_since_bucket;
     if (e == hipSuccess && cfg.variant == 7) {
       TimedRegion scan(net, GSN_T_FIND_SCAN, st);
-      e = gsn::launch_pruned_search(sb, net->n, net->p.n_max, net->sup_parity, sig, m, winner, second, d1, d2, claim, st);
+      e = gsn::launch_pruned_search(sb, net->n, net->n, net->p.n_max, net->sup_parity, sig, m, winner, second, d1, d2, claim, st);
       scan.end();
       if (claimed) *claimed = claim != nullptr;
     } else if (e == hipSuccess) {
@@ -573,6 +593,23 @@ int update_impl(gsn_net* net, const float* sig, int32_t m, const int32_t* winner
                 bool claimed, const int32_t* order) {
   hipStream_t st = as_stream(stream);
   const int64_t half_cap = 2 * static_cast<int64_t>(net->p.e_max);
+  // The update moves units.  Its last launch gathers them for the next search if this find took
+  // the search and the next one is due to use the same units in the same order.
+  const bool ahead = net->searched && net->staged && !net->grew && m > 0 && gsn::update_gathers(net->n) &&
+                     (net->capturing || net->finds_since_bucket < net->tune_rebucket);
+  net->staged = false;
+  net->grew = false;
+  gsn::GatherArgs ga{};
+  if (ahead)
+    ga = gsn::pruned_gather_args(
+        net->s, gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max), net->n, net->n,
+        net->p.n_max, net->sup_parity ^ 1);
+  const gsn::GatherArgs* gather = ahead ? &ga : nullptr;
+  auto gathered = [&]() {
+    if (!ahead) return;
+    net->sup_parity ^= 1;
+    net->staged = true;
+  };
   if (net->p.lock_mode == 1) {
     if (m == 0) {
       int rc = gsn_resolve_conflicts(net, m, winner, second, d1, accepted, stream);
@@ -595,9 +632,11 @@ int update_impl(gsn_net* net, const float* sig, int32_t m, const int32_t* winner
     const gsn::WinnerStep w{sig, m, winner, second, d1, accepted, net->p.key_mode,
                             net->p.eps_b, net->p.eps_n, net->p.err_beta, net->p.max_age, 0, 0,
                             half_cap, nullptr, net->p.n_max};
-    const hipError_t e = gsn::launch_winner_local(net->s, net->cur, net->wpar, net->n, w, st);
+    const hipError_t e =
+        gsn::launch_winner_local(net->s, net->cur, net->wpar, net->n, w, st, gather);
     t.end();
     if (e != hipSuccess) return GSN_E_HIP;
+    gathered();
     net->cur ^= 1;
     net->wpar ^= 1;
     net->phase = kReady;
@@ -619,9 +658,10 @@ int update_impl(gsn_net* net, const float* sig, int32_t m, const int32_t* winner
   const hipError_t e = gsn::launch_iterate_set(
       net->s, net->cur, net->dpar, net->n, sig, m, winner, second, d1, accepted,
       net->p.key_mode, net->p.eps_b, net->p.eps_n, net->p.err_beta, net->p.max_age, half_cap,
-      greedy || claimed, order, st, greedy ? net->s.pend : nullptr);
+      greedy || claimed, order, st, greedy ? net->s.pend : nullptr, gather);
   t.end();
   if (e != hipSuccess) return GSN_E_HIP;
+  gathered();
   net->cur ^= 1;
   net->dpar ^= 1;
   net->phase = kReady;
@@ -660,6 +700,7 @@ int find_grid_impl(gsn_net* net, const gsn_grid* grid, void* grid_ws, size_t gri
   if (m > 0 && (!sig || !winner || !second || !d1 || !d2)) return GSN_E_INVAL;
   net->phase = kFound;
   if (m == 0) return GSN_OK;
+  net->searched = false;
   hipStream_t st = as_stream(stream);
   gsn::GridSpec spec{};
   for (int a = 0; a < 3; ++a) {
@@ -734,6 +775,7 @@ int gsn_adapt(gsn_net* net, const float* sig, int32_t m, const int32_t* winner,
   if (net->phase != kResolved) return GSN_E_STATE;
   if (m > 0 && (!sig || !winner || !second || !d1 || !accepted)) return GSN_E_INVAL;
   net->phase = kAdapted;
+  net->staged = false;
   hipStream_t st = as_stream(stream);
   TimedRegion t(net, GSN_T_ADAPT, st);
   hipError_t e;
@@ -827,7 +869,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     return g.sigs == sigs && g.m == m && g.count == count && g.winner == winner &&
            g.second == second && g.d1 == d1 && g.d2 == d2 && g.accepted == accepted &&
            g.n == net->n && g.cur == net->cur && g.dpar == net->dpar && g.wpar == net->wpar &&
-           g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity && g.rebuild_first == rebuild_first &&
+           g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity && g.rebuild_first == rebuild_first && g.staged == net->staged && g.grew == net->grew &&
            g.tune_split == net->tune_split && g.tune_variant == net->tune_variant &&
            g.tune_grab == net->tune_grab && g.tune_rebucket == net->tune_rebucket &&
            g.grid_rounds == net->grid_rounds;
@@ -848,6 +890,8 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.stage_parity = net->stage_parity;
     g.sup_parity = net->sup_parity;
     g.rebuild_first = rebuild_first;
+    g.staged = net->staged;
+    g.grew = net->grew;
     g.tune_split = net->tune_split; g.tune_variant = net->tune_variant;
     g.tune_grab = net->tune_grab; g.tune_rebucket = net->tune_rebucket;
     g.grid_rounds = net->grid_rounds;
@@ -855,6 +899,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     // launches go into the graph
     const int cur0 = net->cur, dpar0 = net->dpar, wpar0 = net->wpar, sp0 = net->stage_parity;
     const int up0 = net->sup_parity;
+    const bool staged0 = net->staged, grew0 = net->grew;
     const int phase0 = net->phase;
     const int32_t bn0 = net->bucket_n, f0 = net->finds_since_bucket;
     (void)hipGetLastError();
@@ -882,6 +927,8 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
       // nothing ran: the handle is as before the call
       net->cur = cur0; net->dpar = dpar0; net->wpar = wpar0; net->stage_parity = sp0;
       net->sup_parity = up0;
+      net->staged = staged0;
+      net->grew = grew0;
       net->phase = phase0;
       net->bucket_n = bn0; net->finds_since_bucket = f0;
       (void)hipGetLastError();
@@ -892,12 +939,15 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.cur_after = net->cur; g.dpar_after = net->dpar; g.wpar_after = net->wpar;
     g.stage_parity_after = net->stage_parity;
     g.sup_parity_after = net->sup_parity;
+    g.staged_after = net->staged;
     g.finds_after = net->finds_since_bucket;
     g.finds_delta = net->finds_since_bucket - f0;
     g.bucket_n_after = net->bucket_n;
     // the host state is back at the start until the graph is launched below
     net->cur = cur0; net->dpar = dpar0; net->wpar = wpar0; net->stage_parity = sp0;
     net->sup_parity = up0;
+    net->staged = staged0;
+    net->grew = grew0;
     net->bucket_n = bn0; net->finds_since_bucket = f0;
     if (net->graphs.size() >= GSN_GRAPH_CACHE) {
       size_t old = 0;
@@ -917,6 +967,8 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   net->wpar = hit->wpar_after;
   net->stage_parity = hit->stage_parity_after;
   net->sup_parity = hit->sup_parity_after;
+  net->staged = hit->staged_after;
+  net->grew = false;
   if (hit->rebuilt) {
     net->finds_since_bucket = hit->finds_after;
     net->bucket_n = hit->bucket_n_after;
@@ -1140,6 +1192,8 @@ int gsn_import(gsn_net* net, int32_t n, const float* xyz, const float* err, int3
     net->sup_parity = 0;     // and both sets of outer boxes
     net->phase = kReady;
     net->bucket_n = -1;
+    net->staged = false;
+    net->grew = false;
   } catch (const std::bad_alloc&) {
     return GSN_E_CAPACITY;
   }

@@ -497,12 +497,22 @@ hipError_t launch_scan_mfma(const DevState& s, const StageBufs& b, int32_t n, co
                             int32_t m, int split, hipStream_t st, LaunchEvents ev = {});
 
 // The pruned search (find_pruned.hip, variant 7): the records and boxes of the present
-// positions in the unit order, then the two nearest of every signal with the claims of claim
-// (null: none).
+// positions in the unit order (of `slots` places, some of them empty after a removal), then the
+// two nearest of every signal with the claims of claim (null: none).  par: which set of outer
+// boxes; successive gathers alternate.
+struct GatherArgs {
+  const float *x, *y, *z;
+  const int32_t* pidx;
+  float4 *pq, *leaf, *top;
+  int32_t *sup, *sup_next;
+  int32_t n, slots, tops, sup_words;   // tops: workgroups of the gather
+};
+GatherArgs pruned_gather_args(const DevState& s, const StageBufs& b, int32_t n, int32_t slots,
+                              int32_t n_max, int par);
 hipError_t launch_stage_order(const DevState& s, const StageBufs& b, int32_t n, hipStream_t st);
-hipError_t launch_pruned_gather(const DevState& s, const StageBufs& b, int32_t n,
-                                int32_t n_max, int par, hipStream_t st);
-hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t n_max, int par, const float* sig, int32_t m,
+hipError_t launch_pruned_gather(const GatherArgs& g, hipStream_t st);
+hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t slots, int32_t n_max, int par,
+                                const float* sig, int32_t m,
                                 int32_t* winner, int32_t* second, float* d1, float* d2,
                                 const ClaimArgs* claim, hipStream_t st, LaunchEvents ev = {});
 
@@ -572,8 +582,10 @@ hipError_t launch_winner_update(const DevState& s, int cur, int32_t n, const Win
 // tables: the moves with the new degrees, and the rows, written into buffer cur ^ 1 with the
 // error decay (grid_rounds and feedback are not used).  Consecutive calls must alternate
 // par.
+// gather (not null): the last launch also gathers the units for the next search.
 hipError_t launch_winner_local(const DevState& s, int cur, int par, int32_t n,
-                               const WinnerStep& w, hipStream_t st);
+                               const WinnerStep& w, hipStream_t st,
+                               const GatherArgs* gather = nullptr);
 // The lock-set resolve, adaptation and edge update of one iteration: the claims (unless the
 // find's merge made them, claimed = true); the check fused with the accepted signals'
 // updates, taking the signals in the given order when order is not null (a permutation of
@@ -586,7 +598,11 @@ hipError_t launch_iterate_set(const DevState& s, int cur, int dpar, int32_t n, c
                               const float* d1, uint8_t* accepted, int key_mode, float eps_b,
                               float eps_n, float beta, int32_t max_age, int64_t half_cap,
                               bool claimed, const int32_t* order, hipStream_t st,
-                              const uint8_t* given = nullptr);
+                              const uint8_t* given = nullptr,
+                              const GatherArgs* gather = nullptr);
+// Whether the last launch of an update of n units can gather for the next search (the rewrite
+// without a separate count).
+inline bool update_gathers(int32_t n) { return (n + kBlock - 1) / kBlock <= kFoldBlocks; }
 hipError_t launch_scan_blocks(int32_t* bsum, int32_t nb, int64_t cap, int32_t* out_total,
                               int32_t* status, int32_t slot, hipStream_t st);
 hipError_t launch_init(const DevState& s, int cur, int32_t n0, int32_t n_max,

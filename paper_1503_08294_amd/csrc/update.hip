@@ -9,7 +9,7 @@
 // equals any sequential order (a group of eight lanes per signal).  The adjacency is a symmetric CSR (row_ptr, col, age per half-edge),
 // rows ascending by neighbour; the edge update modifies ages in place, then rewrites a
 // compacted CSR into the other buffer (count -> scan -> scatter).
-#include "gsn_internal.h"
+#include "pruned_gather.h"
 
 namespace gsn {
 namespace {
@@ -615,7 +615,10 @@ __global__ void ed_write(int32_t n, const int32_t* __restrict__ rp,
 // own row's live entries and request, a block scan places the rows, and the row is written
 // as in ed_write.  Also the error decay (err not null), the per-workgroup accepted counts of
 // the fused check (apart not null, workgroup 0), and zeroing of the other delta array for
-// the next update (every workgroup its own entry).
+// the next update (every workgroup its own entry).  Workgroups past nb gather the units, whose
+// positions are final here, for the next search: both parts wait on loads, so beside each other
+// they take little longer than one (200,000 units: 11.5 us for both, 8.0 and 8.1 one after
+// the other; the winner rule at 100,000: 13.6, 12.0 and 5.8).
 __global__ void ed_rewrite(int32_t n, const int32_t* __restrict__ rp,
                            const int32_t* __restrict__ col, const int32_t* __restrict__ age,
                            int32_t* __restrict__ ins, const int32_t* __restrict__ bdelta,
@@ -624,10 +627,16 @@ __global__ void ed_rewrite(int32_t n, const int32_t* __restrict__ rp,
                            int32_t* __restrict__ status, int32_t nb, int64_t cap,
                            float* __restrict__ err, float beta,
                            const int32_t* __restrict__ apart, int32_t napart,
-                           unsigned long long* __restrict__ acc, int32_t* __restrict__ taken) {
+                           unsigned long long* __restrict__ acc, int32_t* __restrict__ taken,
+                           GatherArgs gather) {
   __shared__ int32_t wt[kBlock / 64];
   __shared__ int32_t wa[kBlock / 64];
   __shared__ int32_t red[2 * kBlock / 64];
+  __shared__ float gred[kGatherRed];
+  if (static_cast<int32_t>(blockIdx.x) >= nb) {   // (gather.tops workgroups beside the rewrite's)
+    gather_top(gather, static_cast<int32_t>(blockIdx.x) - nb, gred);
+    return;
+  }
   const int32_t u = blockIdx.x * kBlock + threadIdx.x;
   const bool in = u < n;
   // the row (slots past its end repeat the last entry), the request, the error and the old
@@ -815,7 +824,7 @@ hipError_t launch_edges(const DevState& s, int cur, int dpar, int32_t n, int32_t
   if (nb <= kFoldBlocks) {
     ed_rewrite<<<nb, kBlock, 0, st>>>(n, s.rp[cur], s.col[cur], s.age[cur], s.ins, bd, bd_next,
                                       s.rp[nxt], s.col[nxt], s.age[nxt], s.status, nb, half_cap,
-                                      nullptr, 1.0f, nullptr, 0, nullptr, taken);
+                                      nullptr, 1.0f, nullptr, 0, nullptr, taken, GatherArgs{});
     return hipGetLastError();
   }
   ed_count<<<nb, kBlock, 0, st>>>(n, s.rp[cur], s.age[cur], s.ins, s.cnt, s.bsum, nullptr,
@@ -832,7 +841,7 @@ hipError_t launch_iterate_set(const DevState& s, int cur, int dpar, int32_t n, c
                               const float* d1, uint8_t* accepted, int key_mode, float eps_b,
                               float eps_n, float beta, int32_t max_age, int64_t half_cap,
                               bool claimed, const int32_t* order, hipStream_t st,
-                              const uint8_t* given) {
+                              const uint8_t* given, const GatherArgs* gather) {
   const int nxt = cur ^ 1;
   int32_t* bd = s.bdelta[dpar];
   int32_t* bd_next = s.bdelta[dpar ^ 1];
@@ -854,9 +863,11 @@ hipError_t launch_iterate_set(const DevState& s, int cur, int dpar, int32_t n, c
   if (n == 0) return hipGetLastError();
   const int nb = blocks(n);
   if (nb <= kFoldBlocks) {
-    ed_rewrite<<<nb, kBlock, 0, st>>>(n, s.rp[cur], s.col[cur], s.age[cur], s.ins, bd, bd_next,
-                                      s.rp[nxt], s.col[nxt], s.age[nxt], s.status, nb, half_cap,
-                                      s.err, beta, apart, gb, s.acc64 + kA64Accepted, taken);
+    const GatherArgs g = gather ? *gather : GatherArgs{};
+    ed_rewrite<<<nb + g.tops, kBlock, 0, st>>>(
+        n, s.rp[cur], s.col[cur], s.age[cur], s.ins, bd, bd_next, s.rp[nxt], s.col[nxt],
+        s.age[nxt], s.status, nb, half_cap, s.err, beta, apart, gb, s.acc64 + kA64Accepted, taken,
+        g);
     return hipGetLastError();
   }
   ed_count<<<nb, kBlock, 0, st>>>(n, s.rp[cur], s.age[cur], s.ins, s.cnt, s.bsum, s.err, beta,

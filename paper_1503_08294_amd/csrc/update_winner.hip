@@ -21,7 +21,7 @@
 // which hold most of the survivors, are grid-wide launches; the few survivors left then go
 // through the remaining rounds inside one workgroup, so that the whole update is enqueued
 // without the host waiting to learn how many rounds it takes.
-#include "gsn_internal.h"
+#include "pruned_gather.h"
 
 namespace gsn {
 namespace {
@@ -847,9 +847,16 @@ __global__ __launch_bounds__(kBlock) void wu_apply(LocalArgs a) {
 // Per unit: its row after the update at the offset of the scanned lengths, ascending (the
 // neighbours before the update keep their order, each new edge is put in its place); and
 // the other parity's tables cleared.  out_total receives the number of half-edges.
-__global__ __launch_bounds__(kBlock) void wu_write(LocalArgs a, int32_t* out_total) {
+// Workgroups past nb gather the units (final here) for the next search.
+__global__ __launch_bounds__(kBlock) void wu_write(LocalArgs a, int32_t* out_total,
+                                                   GatherArgs gather) {
   __shared__ int32_t wt[kBlock / 64];
   __shared__ int32_t red[2 * kBlock / 64];
+  __shared__ float gred[kGatherRed];
+  if (static_cast<int32_t>(blockIdx.x) >= a.nb) {
+    gather_top(gather, static_cast<int32_t>(blockIdx.x) - a.nb, gred);
+    return;
+  }
   const int32_t x = blockIdx.x * kBlock + threadIdx.x;
   const int32_t c = x < a.n ? a.cnt[x] : 0;
   int32_t boff;
@@ -864,7 +871,7 @@ __global__ __launch_bounds__(kBlock) void wu_write(LocalArgs a, int32_t* out_tot
   }
   const int32_t inc = block_inclusive_scan(c, wt);
   const int32_t hi_o = a.whi[a.par ^ 1];
-  const int32_t stride = static_cast<int32_t>(gridDim.x) * kBlock;
+  const int32_t stride = a.nb * kBlock;
   for (int32_t u = x; u < hi_o; u += stride) {
     a.wkey_o[2 * u] = ~0ull;
     a.wflag_o[u] = 0;
@@ -953,7 +960,8 @@ WinnerTables winner_tables(const DevState& s, int par, int32_t n_max) {
 }
 
 hipError_t launch_winner_local(const DevState& s, int cur, int par, int32_t n,
-                               const WinnerStep& w, hipStream_t st) {
+                               const WinnerStep& w, hipStream_t st,
+                               const GatherArgs* gather) {
   const int nxt = cur ^ 1;
   const int po = par ^ 1;
   const size_t nm = static_cast<size_t>(w.n_max);
@@ -971,7 +979,8 @@ hipError_t launch_winner_local(const DevState& s, int cur, int par, int32_t n,
                                             -1, st);
     if (e != hipSuccess) return e;
   }
-  wu_write<<<nb, kBlock, 0, st>>>(a, s.rp[nxt] + n);
+  const GatherArgs g = gather ? *gather : GatherArgs{};
+  wu_write<<<nb + g.tops, kBlock, 0, st>>>(a, s.rp[nxt] + n, g);
   return hipGetLastError();
 }
 

@@ -75,3 +75,62 @@ def test_switching_between_the_search_and_the_scans():
         g, o = pair.iterate(sig)
         assert_iter_equal(g, o, f"call {t} variant {variant}")
     pair.compare_state("end")
+
+
+@pytest.mark.parametrize("lock_mode", [0, 1, 2])
+def test_records_follow_every_change_of_the_units(lock_mode):
+    """The update leaves the records for the next search, so whatever else moves, adds, removes
+    or replaces units must not let an older record be used: separate calls, the index, growth
+    with removal, an import, small batches, a recorded loop and two finds in a row, mixed."""
+    import torch
+    from paper_1503_08294_amd import gsn
+    rng = np.random.default_rng(40 + lock_mode)
+    n, m = 3_000, 400
+    units = rng.standard_normal((3, n)).astype(np.float32)
+    pair = Pair(units, n_max=n + 64, e_max=8 * n, m_max=m, eps_b=0.4, eps_n=0.05, max_age=2,
+                lock_mode=lock_mode)
+    pair.net.tune(gsn.GSN_TUNE_REBUCKET, 7)
+    lo, h, dims = [-5.0] * 3, 0.5, [20] * 3
+    grid = gsn.make_grid(lo, h, dims)
+    ws = pair.net.grid_workspace(grid)
+
+    def batch(k=m):
+        return rng.standard_normal((3, k)).astype(np.float32)
+
+    for t in range(1, 31):
+        what = ("fused", "steps", "grow", "small", "index", "twice", "import", "loop")[
+            int(rng.integers(0, 8))]
+        sig = batch(60 if what == "small" else m)
+        if what in ("fused", "small"):
+            assert_iter_equal(*pair.iterate(sig), f"{t} {what}")
+        elif what == "steps":
+            assert_iter_equal(*pair.iterate(sig, calls="steps"), f"{t} {what}")
+        elif what == "grow":
+            assert_iter_equal(*pair.iterate(sig, t, t, True), f"{t} {what}")
+        elif what == "index":
+            dev = pair.to_dev(sig)
+            pair.net.find_winners_grid(dev, grid, ws)
+            acc = pair.net.update(dev).cpu().numpy()
+            ow, osec, od1, od2 = pair.orc.find_winners_grid(sig, lo, h, dims)[:4]
+            oacc = pair.orc.resolve_conflicts(ow, osec, od1)
+            pair.orc.adapt(sig, ow, osec, od1, oacc)
+            pair.orc.update_edges(ow, osec, oacc)
+            np.testing.assert_array_equal(acc, oacc, err_msg=f"{t} {what}")
+        elif what == "twice":
+            for _ in range(2):
+                assert_find_equal(*pair.find(batch()), f"{t} {what}")
+        elif what == "import":
+            s = pair.orc.export()
+            s["xyz"] = (s["xyz"] * np.float32(1.1)).astype(np.float32)
+            pair.net.import_state(torch.from_numpy(s["xyz"]), torch.from_numpy(s["err"]),
+                                  torch.from_numpy(s["edges"]))
+            pair.orc.import_state(s["xyz"], s["err"], s["edges"])
+        else:
+            sigs = [batch() for _ in range(3)]
+            dev = pair.to_dev(np.stack(sigs))
+            g = [x.cpu().numpy() for x in pair.net.iterate_loop(dev)]
+            for x in sigs:
+                o = pair.orc.iterate(x, 0, 0, False)
+            assert_iter_equal(g, o, f"{t} {what}")
+        pair.compare_state(f"{t} {what}")
+    assert pair.net.check() == 0
