@@ -341,7 +341,9 @@ void gsn_destroy(gsn_net* net);
  *   GSN_TUNE_VARIANT  find-winners kernel: 0 = automatic (up to 256 signals the unit-parallel
  *                     scan, 6; above, the search that leaves out blocks of units whose
  *                     bounding box lies farther than the second nearest, unless
- *                     GSN_TUNE_SPLIT asks for chunks: then 4), 1 = direct scan of every
+ *                     GSN_TUNE_SPLIT asks for chunks: then 4; smaller batches take that
+ *                     search too once gsn_iterate has run several of them on the same units),
+ *                     1 = direct scan of every
  *                     distance, 2 = screened scan with the screen on the vector unit,
  *                     3 = screened scan with the screen on the matrix cores in binary32,
  *                     4 = the same screen on the matrix cores in split binary16, 5 = variant
@@ -351,9 +353,10 @@ void gsn_destroy(gsn_net* net);
  *                     carries a rigorous rounding margin; candidates are rechecked in the
  *                     binary32 direct form, so all variants return the same result)
  *   GSN_TUNE_GRAB     batches of 64 units per atomic grab of variant 5: 1..1024, 0 = default
- *   GSN_TUNE_REBUCKET staged find calls (automatic and variants 2-5) between rebuilds of the spatial order
- *                     of the units (it is also rebuilt whenever N or the indices change):
- *                     1..4096, 0 = default (64)
+ *   GSN_TUNE_REBUCKET staged find calls (automatic and variants 2-5) between rebuilds of the
+ *                     spatial order of the units (batches of up to 256 signals count by their
+ *                     signals instead; units inserted or removed keep it until too many of its
+ *                     places are empty): 1..4096, 0 = default (64)
  *   GSN_TUNE_GRID_ROUNDS  rounds of the GSN_LOCK_WINNER update of gsn_adapt (each skipped
  *                     once fewer than 32 signals are pending) and of the GSN_LOCK_SET_GREEDY
  *                     resolve launched over the whole device before the remaining

@@ -82,13 +82,21 @@ __global__ void gr_remap(int32_t n, const int32_t* __restrict__ newid,
   }
 }
 
+// The positions and errors at their new ids; and the unit order (slots places, none if null)
+// renumbered, with -1 in the places of the removed units, so that a removal does not cost a new
+// order (48 us at 50,000 units).
 __global__ void gr_copyback(int32_t n, int32_t n_max, const float* __restrict__ tmp,
                             float* __restrict__ x, float* __restrict__ y,
                             float* __restrict__ z, float* __restrict__ err,
-                            int32_t* __restrict__ status) {
+                            int32_t* __restrict__ status, const int32_t* __restrict__ newid,
+                            int32_t* __restrict__ order, int32_t slots) {
   const int32_t i = blockIdx.x * kBlock + threadIdx.x;
   const int32_t kept = status[kStKept];
   if (i == 0) status[kStOrphans] = 0;
+  if (i < slots) {
+    const int32_t u = order[i];
+    order[i] = u >= 0 && u < n ? newid[u] : -1;
+  }
   if (i >= n) return;
   if (i < kept) {
     x[i] = tmp[i];
@@ -838,8 +846,8 @@ __global__ __launch_bounds__(1024) void gr_insert_spec(
 
 }  // namespace
 
-hipError_t launch_remove(const DevState& s, int cur, int32_t n, int32_t n_max,
-                         hipStream_t st) {
+hipError_t launch_remove(const DevState& s, int cur, int32_t n, int32_t n_max, int32_t* order,
+                         int32_t slots, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const int nxt = cur ^ 1;
   const int nb = blocks(n);
@@ -850,7 +858,8 @@ hipError_t launch_remove(const DevState& s, int cur, int32_t n, int32_t n_max,
                                     s.z, s.err, s.tmp, s.orphan, s.status);
   gr_remap<<<nb, kBlock, 0, st>>>(n, s.cnt, s.rp[cur], s.col[cur], s.age[cur], s.col[nxt],
                                   s.age[nxt]);
-  gr_copyback<<<nb, kBlock, 0, st>>>(n, n_max, s.tmp, s.x, s.y, s.z, s.err, s.status);
+  gr_copyback<<<std::max(nb, blocks(slots)), kBlock, 0, st>>>(
+      n, n_max, s.tmp, s.x, s.y, s.z, s.err, s.status, s.cnt, order, slots);
   return hipGetLastError();
 }
 

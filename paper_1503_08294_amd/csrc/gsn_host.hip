@@ -154,6 +154,11 @@ using gsn::DevState;
 
 enum Phase { kReady = 0, kFound = 1, kResolved = 2, kAdapted = 3 };
 constexpr int kRebucketEvery = 64;     // default calls between rebuilds of the unit order
+// Iterations of small batches on the same units after which they take the pruned search: its
+// order and records cost about 60 us once, and then an iteration of a recorded loop takes less
+// (64 signals on 100,000 units 18.3 us against 24.6, 256 19.4 against 41.9, one 15.1 against
+// 15.7; 256 on 1,000 units 16.4 against 18.0).
+constexpr int32_t kSmallRun = 8;
 constexpr int kDefaultGrab = 4;        // batches per grab of the dynamic scan
 constexpr int kDefaultGridRounds = 6;  // before any update has reported back
 // Grid-wide rounds of the greedy lock-set resolve: one while the last workgroup has a thread per
@@ -183,10 +188,15 @@ struct gsn_net {
   bool staged;
   bool grew;
   bool searched;     // the last find took the pruned search
+  bool foreign;      // a caller recorded a staged find: its graph may run at any time and
+                     // rewrite the records, so each find makes its own
   bool timing;
   uint32_t timing_mask;  // timers that record while timing is on (bit GSN_T_*)
-  int32_t bucket_n;            // unit count at the last spatial bucketing (-1: none yet)
-  int32_t finds_since_bucket;
+  int32_t bucket_n;            // units in the spatial order (-1: none, or not these units)
+  int32_t slots;               // its places: more than units after a removal
+  int32_t finds_since_bucket;  // staged finds of more than kSmallM signals since it was made
+  int64_t small_signals;       // signals of the smaller ones
+  int32_t small_run;           // smaller iterations since the units were last replaced or grew
   int grid_rounds;             // grid-wide rounds of the winner-lock update (0: automatic)
   int32_t* feedback;           // pinned host word: the last update's grid rounds used
   int32_t* feedback_dev;       // its device address, stored by the update's last kernel
@@ -205,9 +215,12 @@ struct gsn_net {
     int32_t n;
     int cur, dpar, wpar, stage_parity, sup_parity;
     bool rebuild_first, staged, grew;
+    int32_t slots, small_run;
     int tune_split, tune_variant, tune_grab, tune_rebucket, grid_rounds;
     // the host state the loop leaves
     bool staged_after;
+    int32_t slots_after;
+    int64_t small_after, small_delta;
     bool rebuilt;   // the first find rebuilt the unit order (else finds_delta counts finds)
     int cur_after, dpar_after, wpar_after, stage_parity_after, sup_parity_after;
     int32_t finds_after, finds_delta, bucket_n_after;
@@ -364,16 +377,21 @@ int grow_step(gsn_net* net, int32_t count, int32_t* inserted_out, hipStream_t st
   int rc = read_status_slot(net, gsn::kStOrphans, &orphans, st);
   if (rc) return rc;
   if (orphans > 0) {
-    if (gsn::launch_remove(net->s, net->cur, net->n, net->p.n_max, st) != hipSuccess)
+    const bool ordered = net->bucket_n == net->n;
+    const gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
+    if (gsn::launch_remove(net->s, net->cur, net->n, net->p.n_max, ordered ? sb.pidx : nullptr,
+                           ordered ? net->slots : 0, st) != hipSuccess)
       return GSN_E_HIP;
     net->cur ^= 1;
     int32_t kept = 0;
     rc = read_status_slot(net, gsn::kStKept, &kept, st);
     if (rc) return rc;
     net->n = kept;
-    net->bucket_n = -1;  // indices changed
+    // the order was renumbered with the units; many empty places are worth a new one
+    net->bucket_n = ordered && net->slots - kept <= kept / 8 ? kept : -1;
     net->staged = false;
     net->grew = true;
+    net->small_run = 0;
   }
   int32_t inserted = 0;
   if (count > 0 && net->n >= 1 && net->n < net->p.n_max) {
@@ -387,12 +405,16 @@ int grow_step(gsn_net* net, int32_t count, int32_t* inserted_out, hipStream_t st
     if (inserted) {
       net->staged = false;
       net->grew = true;
+      net->small_run = 0;
       // new units take the next indices: they join the spatial order at its end (the
-      // periodic rebucketing restores locality); after a removal the order is rebuilt
-      if (net->bucket_n == n_before) {
+      // periodic rebucketing restores locality)
+      if (net->bucket_n == n_before &&
+          net->slots + inserted <= gsn::stage_slots(net->p.n_max)) {
         const gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
-        if (gsn::launch_stage_append(sb, n_before, net->n, st) != hipSuccess) return GSN_E_HIP;
+        if (gsn::launch_stage_append(sb, n_before, net->n, net->slots, st) != hipSuccess)
+          return GSN_E_HIP;
         net->bucket_n = net->n;
+        net->slots += inserted;
       } else {
         net->bucket_n = -1;
       }
@@ -437,10 +459,14 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   net->staged = false;
   net->grew = false;
   net->searched = false;
+  net->foreign = false;
   net->timing = false;
   net->timing_mask = (1u << GSN_T_COUNT) - 1;
   net->bucket_n = -1;
   net->finds_since_bucket = 0;
+  net->slots = 0;
+  net->small_signals = 0;
+  net->small_run = 0;
   net->grid_rounds = 0;
   net->graph_clock = 0;
   net->loop_records = 0;
@@ -495,6 +521,15 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
 
 namespace {
 
+// Whether a staged find of m signals, or one of `count` of them in a row, is due to rebuild the
+// unit order: when there is none of these units, every tune_rebucket finds, and, for small
+// batches, which move few units, about once for as many signals as units.
+bool order_due(const gsn_net* net, int32_t m, int64_t count) {
+  if (net->bucket_n != net->n) return true;
+  if (m > gsn::kSmallM) return net->finds_since_bucket + count > net->tune_rebucket;
+  return net->small_signals + m * count > std::max(net->n, 64 * gsn::kSmallM);
+}
+
 // gsn_find_winners; with claim not null the merge of the staged scans also makes the
 // lock-set claims of every signal, and *claimed says whether it did (the direct scan's
 // merge does not).
@@ -510,9 +545,29 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
   net->phase = kFound;
   if (m == 0) return GSN_OK;
   hipStream_t st = as_stream(stream);
-  const gsn::FindConfig cfg =
+  gsn::FindConfig cfg =
       gsn::find_config(net->n, m, net->cus, net->tune_split, net->tune_variant);
-  net->searched = cfg.variant == 7;
+  // Recorded by the caller (not by gsn_iterate_loop, which tracks what its graph leaves): the
+  // launches run later and perhaps often, so they may not rely on records or an order that
+  // are in place now, and leave the handle's account of them alone.
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (!net->capturing && hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    cs = hipStreamCaptureStatusNone;
+  }
+  const bool recorded = cs != hipStreamCaptureStatusNone;
+  if (recorded) net->staged = false;
+  // A small batch takes the search too where its records are at hand, or, in an iteration,
+  // after enough iterations on the same units.
+  const bool small = m <= gsn::kSmallM;
+  if (cfg.variant == 6 && net->tune_variant == 0 && !recorded) {
+    if (claim) net->small_run = std::min(net->small_run + 1, kSmallRun);
+    if (net->foreign) net->small_run = 0;
+    if ((net->staged && net->bucket_n == net->n) || (claim && net->small_run >= kSmallRun))
+      cfg.variant = 7;
+  }
+  if (recorded && cfg.variant >= 2 && cfg.variant != 6) net->foreign = true;
+  net->searched = cfg.variant == 7 && !net->foreign;
   TimedRegion all(net, GSN_T_FIND, st);
   hipError_t e;
   if (cfg.variant == 6) {
@@ -527,35 +582,41 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
     }
   } else if (cfg.variant >= 2) {
     const gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
-    // the unit order is rebuilt when the network changed and every kRebucketEvery calls
-    bool rebucket = net->bucket_n != net->n || net->finds_since_bucket >= net->tune_rebucket;
+    // the unit order is rebuilt when the network changed and every kRebucketEvery calls (the
+    // scans, unlike the search, take no order with empty places)
+    bool rebucket = order_due(net, m, 1) || (cfg.variant != 7 && net->slots != net->n);
     if (net->loop_rebuild >= 0) {  // the first staged find of a recorded loop
       rebucket = net->loop_rebuild == 1;
       net->loop_rebuild = -1;
     }
     if (cfg.variant == 7) {
       e = rebucket ? gsn::launch_stage_order(net->s, sb, net->n, st) : hipSuccess;
+      if (rebucket) net->slots = net->n;
       if (e == hipSuccess && (rebucket || !net->staged)) {
         net->sup_parity ^= 1;
         e = gsn::launch_pruned_gather(
-            gsn::pruned_gather_args(net->s, sb, net->n, net->n, net->p.n_max, net->sup_parity),
+            gsn::pruned_gather_args(net->s, sb, net->n, net->slots, net->p.n_max,
+                                    net->sup_parity),
             st);
-        net->staged = true;
+        net->staged = !net->foreign;
       }
     } else {
       e = gsn::launch_stage(net->s, sb, net->n, sig, m, rebucket, net->stage_parity,
                             cfg.variant, st);
       net->stage_parity ^= 1;
       if (rebucket) net->staged = false;   // a new order, gathered for the scans alone
+      if (rebucket) net->slots = net->n;
     }
     if (rebucket) {
-      net->bucket_n = net->n;
+      net->bucket_n = recorded ? -1 : net->n;
       net->finds_since_bucket = 0;
+      net->small_signals = 0;
     }
-    ++net->finds_since_bucket;
+    if (small) net->small_signals += m;
+    else ++net->finds_since_bucket;
     if (e == hipSuccess && cfg.variant == 7) {
       TimedRegion scan(net, GSN_T_FIND_SCAN, st);
-      e = gsn::launch_pruned_search(sb, net->n, net->n, net->p.n_max, net->sup_parity, sig, m, winner, second, d1, d2, claim, st);
+      e = gsn::launch_pruned_search(sb, net->n, net->slots, net->p.n_max, net->sup_parity, sig, m, winner, second, d1, d2, claim, st);
       scan.end();
       if (claimed) *claimed = claim != nullptr;
     } else if (e == hipSuccess) {
@@ -596,13 +657,13 @@ int update_impl(gsn_net* net, const float* sig, int32_t m, const int32_t* winner
   // The update moves units.  Its last launch gathers them for the next search if this find took
   // the search and the next one is due to use the same units in the same order.
   const bool ahead = net->searched && net->staged && !net->grew && m > 0 && gsn::update_gathers(net->n) &&
-                     (net->capturing || net->finds_since_bucket < net->tune_rebucket);
+                     (net->capturing || !order_due(net, m, 1));
   net->staged = false;
   net->grew = false;
   gsn::GatherArgs ga{};
   if (ahead)
     ga = gsn::pruned_gather_args(
-        net->s, gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max), net->n, net->n,
+        net->s, gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max), net->n, net->slots,
         net->p.n_max, net->sup_parity ^ 1);
   const gsn::GatherArgs* gather = ahead ? &ga : nullptr;
   auto gathered = [&]() {
@@ -862,14 +923,17 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   hipStream_t st = as_stream(stream);
   // the unit order is rebuilt at the first iteration if the usual rule would rebuild it
   // anywhere inside the loop (after that the usual rule applies, from a fresh count)
-  const bool rebuild_first =
-      net->bucket_n != net->n || net->finds_since_bucket + count > net->tune_rebucket;
+  const bool rebuild_first = order_due(net, m, count);
+  // (small batches decide at the first iteration whether they take the search)
+  if (m > 0 && m <= gsn::kSmallM)
+    net->small_run = std::min<int32_t>(net->small_run + count, kSmallRun);
   using LoopGraph = gsn_net::LoopGraph;
   auto same = [&](const LoopGraph& g) {
     return g.sigs == sigs && g.m == m && g.count == count && g.winner == winner &&
            g.second == second && g.d1 == d1 && g.d2 == d2 && g.accepted == accepted &&
            g.n == net->n && g.cur == net->cur && g.dpar == net->dpar && g.wpar == net->wpar &&
-           g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity && g.rebuild_first == rebuild_first && g.staged == net->staged && g.grew == net->grew &&
+           g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity && g.rebuild_first == rebuild_first && g.staged == net->staged && g.grew == net->grew && g.slots == net->slots &&
+           g.small_run == net->small_run &&
            g.tune_split == net->tune_split && g.tune_variant == net->tune_variant &&
            g.tune_grab == net->tune_grab && g.tune_rebucket == net->tune_rebucket &&
            g.grid_rounds == net->grid_rounds;
@@ -892,6 +956,8 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.rebuild_first = rebuild_first;
     g.staged = net->staged;
     g.grew = net->grew;
+    g.slots = net->slots;
+    g.small_run = net->small_run;
     g.tune_split = net->tune_split; g.tune_variant = net->tune_variant;
     g.tune_grab = net->tune_grab; g.tune_rebucket = net->tune_rebucket;
     g.grid_rounds = net->grid_rounds;
@@ -900,6 +966,8 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     const int cur0 = net->cur, dpar0 = net->dpar, wpar0 = net->wpar, sp0 = net->stage_parity;
     const int up0 = net->sup_parity;
     const bool staged0 = net->staged, grew0 = net->grew;
+    const int32_t slots0 = net->slots;
+    const int64_t small0 = net->small_signals;
     const int phase0 = net->phase;
     const int32_t bn0 = net->bucket_n, f0 = net->finds_since_bucket;
     (void)hipGetLastError();
@@ -929,6 +997,8 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
       net->sup_parity = up0;
       net->staged = staged0;
       net->grew = grew0;
+      net->slots = slots0;
+      net->small_signals = small0;
       net->phase = phase0;
       net->bucket_n = bn0; net->finds_since_bucket = f0;
       (void)hipGetLastError();
@@ -940,6 +1010,9 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.stage_parity_after = net->stage_parity;
     g.sup_parity_after = net->sup_parity;
     g.staged_after = net->staged;
+    g.slots_after = net->slots;
+    g.small_after = net->small_signals;
+    g.small_delta = net->small_signals - small0;
     g.finds_after = net->finds_since_bucket;
     g.finds_delta = net->finds_since_bucket - f0;
     g.bucket_n_after = net->bucket_n;
@@ -948,6 +1021,8 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     net->sup_parity = up0;
     net->staged = staged0;
     net->grew = grew0;
+    net->slots = slots0;
+    net->small_signals = small0;
     net->bucket_n = bn0; net->finds_since_bucket = f0;
     if (net->graphs.size() >= GSN_GRAPH_CACHE) {
       size_t old = 0;
@@ -969,6 +1044,8 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   net->sup_parity = hit->sup_parity_after;
   net->staged = hit->staged_after;
   net->grew = false;
+  net->slots = hit->slots_after;
+  net->small_signals = hit->rebuilt ? hit->small_after : net->small_signals + hit->small_delta;
   if (hit->rebuilt) {
     net->finds_since_bucket = hit->finds_after;
     net->bucket_n = hit->bucket_n_after;
@@ -1192,8 +1269,10 @@ int gsn_import(gsn_net* net, int32_t n, const float* xyz, const float* err, int3
     net->sup_parity = 0;     // and both sets of outer boxes
     net->phase = kReady;
     net->bucket_n = -1;
+    net->slots = 0;
     net->staged = false;
     net->grew = false;
+    net->small_run = 0;
   } catch (const std::bad_alloc&) {
     return GSN_E_CAPACITY;
   }

@@ -460,8 +460,11 @@ __device__ __forceinline__ int32_t stage_bucket(float x, float y, float z, const
 size_t stage_bytes(int32_t n_max, int32_t m_max);
 StageBufs carve_stage(void* base, int32_t n_max, int32_t m_max);
 hipError_t launch_stage_init(const StageBufs& b, int32_t n_max, hipStream_t st);
-// units n0 .. n1 - 1 appended to the spatial order (older indices unchanged)
-hipError_t launch_stage_append(const StageBufs& b, int32_t n0, int32_t n1, hipStream_t st);
+// places the unit order has room for
+inline int32_t stage_slots(int32_t n_max) { return (n_max + 63) / 64 * 64; }
+// units n0 .. n1 - 1 appended to the spatial order from its place at (older indices unchanged)
+hipError_t launch_stage_append(const StageBufs& b, int32_t n0, int32_t n1, int32_t at,
+                               hipStream_t st);
 // parity alternates between calls (two sets of signal histogram and cursors)
 hipError_t launch_stage(const DevState& s, const StageBufs& b, int32_t n, const float* sig,
                         int32_t m, bool rebucket, int parity, int variant, hipStream_t st);
@@ -611,8 +614,9 @@ hipError_t launch_init(const DevState& s, int cur, int32_t n0, int32_t n_max,
 // buffer that is not current: u and v in col[cur ^ 1], the ages in age[cur ^ 1].
 hipError_t launch_export_edges(const DevState& s, int cur, int32_t n, int32_t edges,
                                hipStream_t st);
-hipError_t launch_remove(const DevState& s, int cur, int32_t n, int32_t n_max,
-                         hipStream_t st);
+// order (of slots places; null and 0 for none): the unit order, renumbered, -1 for the removed
+hipError_t launch_remove(const DevState& s, int cur, int32_t n, int32_t n_max, int32_t* order,
+                         int32_t slots, hipStream_t st);
 // Indexed find winners (find_grid.hip): the grid and the caller's grid workspace.
 struct GridSpec {
   float lo[3];

@@ -201,12 +201,12 @@ __global__ __launch_bounds__(kBlock) void st_scatter_units(int32_t n,
 }
 
 // Units added at the end (indices n0 .. n1 - 1, every older index unchanged) join the
-// order at its end: the scan still visits every unit, only their place is not spatial until
-// the next bucketing.
-__global__ __launch_bounds__(kBlock) void st_append(int32_t n0, int32_t n1,
+// order at its end (its first free place is at): every unit is still visited, only their place
+// is not spatial until the next bucketing.
+__global__ __launch_bounds__(kBlock) void st_append(int32_t n0, int32_t n1, int32_t at,
                                                     int32_t* __restrict__ pidx) {
-  const int32_t i = n0 + blockIdx.x * kBlock + threadIdx.x;
-  if (i < n1) pidx[i] = i;
+  const int32_t i = blockIdx.x * kBlock + threadIdx.x;
+  if (i < n1 - n0) pidx[at + i] = n0 + i;
 }
 
 // ------------------------------------------------------------- every call ----
@@ -583,9 +583,10 @@ StageBufs carve_stage(void* base, int32_t n_max, int32_t m_max) {
   return s;
 }
 
-hipError_t launch_stage_append(const StageBufs& b, int32_t n0, int32_t n1, hipStream_t st) {
+hipError_t launch_stage_append(const StageBufs& b, int32_t n0, int32_t n1, int32_t at,
+                               hipStream_t st) {
   if (n1 <= n0) return hipSuccess;
-  st_append<<<blocks(n1 - n0), kBlock, 0, st>>>(n0, n1, b.pidx);
+  st_append<<<blocks(n1 - n0), kBlock, 0, st>>>(n0, n1, at, b.pidx);
   return hipGetLastError();
 }
 

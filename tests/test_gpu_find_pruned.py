@@ -134,3 +134,36 @@ def test_records_follow_every_change_of_the_units(lock_mode):
             assert_iter_equal(g, o, f"{t} {what}")
         pair.compare_state(f"{t} {what}")
     assert pair.net.check() == 0
+
+
+@pytest.mark.parametrize("m", [64, 600])
+def test_a_find_recorded_by_the_caller(m):
+    """A find captured into the caller's own graph while records of the units are at hand,
+    replayed after iterations that move them, between eager finds and iterations."""
+    import torch
+    rng = np.random.default_rng(m)
+    n = 4_000
+    units = rng.standard_normal((3, n)).astype(np.float32)
+    pair = Pair(units, m_max=600, eps_b=0.5, eps_n=0.1, max_age=3)
+
+    def step():
+        assert_iter_equal(*pair.iterate(rng.standard_normal((3, 600)).astype(np.float32)))
+
+    sig = pair.to_dev(rng.standard_normal((3, m)).astype(np.float32))
+    for _ in range(3):
+        step()
+    graph = torch.cuda.CUDAGraph()
+    pair.net.find_winners(sig)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        got = pair.net.find_winners(sig)
+    for t in range(4):
+        new = rng.standard_normal((3, m)).astype(np.float32)
+        sig.copy_(pair.to_dev(new))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_find_equal([x.cpu().numpy() for x in got], pair.orc.find_winners(new), f"{t}")
+        assert_find_equal(*pair.find(new), f"{t} eager")
+        step()
+        step()
+    pair.compare_state("end")
