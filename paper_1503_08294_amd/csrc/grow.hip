@@ -111,6 +111,21 @@ __global__ void gr_copyback(int32_t n, int32_t n_max, const float* __restrict__ 
   }
 }
 
+// The status words, and the error window's sum, into the host's mailbox (pinned, mapped): one
+// small launch and the stream's synchronization instead of a copy for each word.
+__global__ void gr_report(const int32_t* __restrict__ status,
+                          const unsigned long long* __restrict__ acc64, GrowMail* mail) {
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&mail->orphans, status[kStOrphans], __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&mail->inserted, status[kStInserted], __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&mail->kept, status[kStKept], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(&mail->window, acc64[kA64Window], __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
 // ------------------------------------------------------------------ insertion ----
 // GNG insertion (Sec. 2.1): q = the unit of largest error, f = the neighbour of q of
 // largest error (ties to the lower index for both), a unit r = N at their midpoint, the edge
@@ -264,6 +279,10 @@ __global__ __launch_bounds__(1024) void gr_insert(int32_t n0, int32_t count, int
   __shared__ unsigned long long red[16];
   __shared__ int32_t s_q, s_f, s_added, s_long;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  if (status[kStOrphans] > 0) {   // units to remove first: nothing inserted
+    if (t == 0) status[kStInserted] = 0;
+    return;
+  }
   int32_t nseg = (n0 + len - 1) / len;
   for (int32_t i = t; i < nseg; i += 1024) sk[i] = seg[i];
   __syncthreads();
@@ -559,6 +578,10 @@ __global__ __launch_bounds__(1024) void gr_insert_spec(
   __shared__ int32_t list[3 * kSpecPool];
   __shared__ int32_t s_bin, s_k, s_cnt, s_lbad, s_lzero, s_total, s_e2, s_ok;
   const int t = threadIdx.x, w = t >> 6, lane = t & 63;
+  if (status[kStOrphans] > 0) {   // units to remove first: nothing inserted
+    if (t == 0) status[kStInserted] = 0;
+    return;
+  }
   int32_t nseg = (n0 + len - 1) / len;
   for (int32_t i = t; i < nseg; i += 1024) sk[i] = seg[i];
   __syncthreads();
@@ -845,6 +868,11 @@ __global__ __launch_bounds__(1024) void gr_insert_spec(
 }
 
 }  // namespace
+
+hipError_t launch_grow_report(const DevState& s, GrowMail* mail, hipStream_t st) {
+  gr_report<<<1, 64, 0, st>>>(s.status, s.acc64, mail);
+  return hipGetLastError();
+}
 
 hipError_t launch_remove(const DevState& s, int cur, int32_t n, int32_t n_max, int32_t* order,
                          int32_t slots, hipStream_t st) {

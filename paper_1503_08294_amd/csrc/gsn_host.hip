@@ -159,6 +159,9 @@ constexpr int kRebucketEvery = 64;     // default calls between rebuilds of the 
 // (64 signals on 100,000 units 18.3 us against 24.6, 256 19.4 against 41.9, one 15.1 against
 // 15.7; 256 on 1,000 units 16.4 against 18.0).
 constexpr int32_t kSmallRun = 8;
+// A new order is due once more than one unit in this many joined at its end (a growing run of 1.5 M
+// signals: the search 8.7 us an iteration, new orders 0.7; 20.8 with one every 64 finds).
+constexpr int kAppendedPart = 16;
 constexpr int kDefaultGrab = 4;        // batches per grab of the dynamic scan
 constexpr int kDefaultGridRounds = 6;  // before any update has reported back
 // Grid-wide rounds of the greedy lock-set resolve: one while the last workgroup has a thread per
@@ -194,12 +197,15 @@ struct gsn_net {
   uint32_t timing_mask;  // timers that record while timing is on (bit GSN_T_*)
   int32_t bucket_n;            // units in the spatial order (-1: none, or not these units)
   int32_t slots;               // its places: more than units after a removal
+  int32_t appended;            // of these, units that joined at its end
   int32_t finds_since_bucket;  // staged finds of more than kSmallM signals since it was made
   int64_t small_signals;       // signals of the smaller ones
   int32_t small_run;           // smaller iterations since the units were last replaced or grew
   int grid_rounds;             // grid-wide rounds of the winner-lock update (0: automatic)
   int32_t* feedback;           // pinned host word: the last update's grid rounds used
   int32_t* feedback_dev;       // its device address, stored by the update's last kernel
+  gsn::GrowMail* mail;         // pinned too, beside it: what growth waits for
+  gsn::GrowMail* mail_dev;
   void* scratch_dev;           // device address of the no-allocation grid workspace
   std::vector<hipEvent_t> pool;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> rec[GSN_T_COUNT];
@@ -215,11 +221,11 @@ struct gsn_net {
     int32_t n;
     int cur, dpar, wpar, stage_parity, sup_parity;
     bool rebuild_first, staged, grew;
-    int32_t slots, small_run;
+    int32_t slots, appended, small_run;
     int tune_split, tune_variant, tune_grab, tune_rebucket, grid_rounds;
     // the host state the loop leaves
     bool staged_after;
-    int32_t slots_after;
+    int32_t slots_after, appended_after;
     int64_t small_after, small_delta;
     bool rebuilt;   // the first find rebuilt the unit order (else finds_delta counts finds)
     int cur_after, dpar_after, wpar_after, stage_parity_after, sup_parity_after;
@@ -370,54 +376,63 @@ int read_acc64(gsn_net* net, int slot, int64_t* out, hipStream_t st) {
   return GSN_OK;
 }
 
+// Waits for the stream and for the words growth decides by (in net->mail afterwards).
+int read_mail(gsn_net* net, hipStream_t st) {
+  if (gsn::launch_grow_report(net->s, net->mail_dev, st) != hipSuccess) return GSN_E_HIP;
+  return hip_ok(hipStreamSynchronize(st));
+}
+
+int insert_units(gsn_net* net, int32_t count, hipStream_t st) {
+  return hip_ok(gsn::launch_insert(net->s, net->cur, net->n, count, net->p.err_alpha,
+                                   net->p.n_max, 2 * static_cast<int64_t>(net->p.e_max), st));
+}
+
 // Between iterations: remove the units orphaned since the last call, then up to `count` GNG
-// insertions one after another (while N < n_max).  Syncs to learn the new unit count.
+// insertions one after another (while N < n_max).  Syncs to learn the new unit count: once
+// where no unit waits to be removed, which is nearly always so (the insertion is launched
+// without knowing, and does nothing if one does).
 int grow_step(gsn_net* net, int32_t count, int32_t* inserted_out, hipStream_t st) {
-  int32_t orphans = 0;
-  int rc = read_status_slot(net, gsn::kStOrphans, &orphans, st);
+  auto can_insert = [&]() { return count > 0 && net->n >= 1 && net->n < net->p.n_max; };
+  bool tried = can_insert();
+  int rc = tried ? insert_units(net, count, st) : GSN_OK;
+  if (!rc) rc = read_mail(net, st);
   if (rc) return rc;
-  if (orphans > 0) {
+  if (net->mail->orphans > 0) {
     const bool ordered = net->bucket_n == net->n;
     const gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
     if (gsn::launch_remove(net->s, net->cur, net->n, net->p.n_max, ordered ? sb.pidx : nullptr,
                            ordered ? net->slots : 0, st) != hipSuccess)
       return GSN_E_HIP;
     net->cur ^= 1;
-    int32_t kept = 0;
-    rc = read_status_slot(net, gsn::kStKept, &kept, st);
-    if (rc) return rc;
+    if ((rc = read_mail(net, st))) return rc;
+    const int32_t kept = net->mail->kept;
     net->n = kept;
     // the order was renumbered with the units; many empty places are worth a new one
     net->bucket_n = ordered && net->slots - kept <= kept / 8 ? kept : -1;
     net->staged = false;
     net->grew = true;
     net->small_run = 0;
+    tried = can_insert();
+    if (tried && ((rc = insert_units(net, count, st)) || (rc = read_mail(net, st)))) return rc;
   }
-  int32_t inserted = 0;
-  if (count > 0 && net->n >= 1 && net->n < net->p.n_max) {
-    if (gsn::launch_insert(net->s, net->cur, net->n, count, net->p.err_alpha, net->p.n_max,
-                           2 * static_cast<int64_t>(net->p.e_max), st) != hipSuccess)
-      return GSN_E_HIP;
-    rc = read_status_slot(net, gsn::kStInserted, &inserted, st);
-    if (rc) return rc;
+  const int32_t inserted = tried ? net->mail->inserted : 0;
+  if (inserted) {
     const int32_t n_before = net->n;
     net->n += inserted;
-    if (inserted) {
-      net->staged = false;
-      net->grew = true;
-      net->small_run = 0;
-      // new units take the next indices: they join the spatial order at its end (the
-      // periodic rebucketing restores locality)
-      if (net->bucket_n == n_before &&
-          net->slots + inserted <= gsn::stage_slots(net->p.n_max)) {
-        const gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
-        if (gsn::launch_stage_append(sb, n_before, net->n, net->slots, st) != hipSuccess)
-          return GSN_E_HIP;
-        net->bucket_n = net->n;
-        net->slots += inserted;
-      } else {
-        net->bucket_n = -1;
-      }
+    net->staged = false;
+    net->grew = true;
+    net->small_run = 0;
+    // new units take the next indices: they join the spatial order at its end (the
+    // periodic rebucketing restores locality)
+    if (net->bucket_n == n_before && net->slots + inserted <= gsn::stage_slots(net->p.n_max)) {
+      const gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
+      if (gsn::launch_stage_append(sb, n_before, net->n, net->slots, st) != hipSuccess)
+        return GSN_E_HIP;
+      net->bucket_n = net->n;
+      net->slots += inserted;
+      net->appended += inserted;
+    } else {
+      net->bucket_n = -1;
     }
   }
   if (inserted_out) *inserted_out = inserted;
@@ -465,6 +480,7 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   net->bucket_n = -1;
   net->finds_since_bucket = 0;
   net->slots = 0;
+  net->appended = 0;
   net->small_signals = 0;
   net->small_run = 0;
   net->grid_rounds = 0;
@@ -474,10 +490,15 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   net->capturing = false;
   net->loop_rebuild = -1;
   net->feedback = nullptr;
-  if (hipHostMalloc(reinterpret_cast<void**>(&net->feedback), sizeof(int32_t)) != hipSuccess) {
+  // one pinned allocation: the feedback word, then the growth mailbox
+  constexpr size_t kMailAt = 64;
+  if (hipHostMalloc(reinterpret_cast<void**>(&net->feedback), kMailAt + sizeof(gsn::GrowMail)) !=
+      hipSuccess) {
     delete net;
     return GSN_E_HIP;
   }
+  net->mail = reinterpret_cast<gsn::GrowMail*>(reinterpret_cast<char*>(net->feedback) + kMailAt);
+  *net->mail = gsn::GrowMail{};
   *net->feedback = kDefaultGridRounds - 1;
   net->feedback_dev = nullptr;
   // set-up of the no-allocation entry point on this device (null if the lookup failed;
@@ -488,6 +509,8 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
     gsn_destroy(net);
     return GSN_E_HIP;
   }
+  net->mail_dev = reinterpret_cast<gsn::GrowMail*>(
+      reinterpret_cast<char*>(net->feedback_dev) + kMailAt);
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) == hipSuccess &&
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
@@ -526,6 +549,8 @@ namespace {
 // batches, which move few units, about once for as many signals as units.
 bool order_due(const gsn_net* net, int32_t m, int64_t count) {
   if (net->bucket_n != net->n) return true;
+  // units appended far from their place are in the way of every signal
+  if (static_cast<int64_t>(net->appended) * kAppendedPart > net->n) return true;
   if (m > gsn::kSmallM) return net->finds_since_bucket + count > net->tune_rebucket;
   return net->small_signals + m * count > std::max(net->n, 64 * gsn::kSmallM);
 }
@@ -611,6 +636,7 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
       net->bucket_n = recorded ? -1 : net->n;
       net->finds_since_bucket = 0;
       net->small_signals = 0;
+      net->appended = 0;
     }
     if (small) net->small_signals += m;
     else ++net->finds_since_bucket;
@@ -932,7 +958,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     return g.sigs == sigs && g.m == m && g.count == count && g.winner == winner &&
            g.second == second && g.d1 == d1 && g.d2 == d2 && g.accepted == accepted &&
            g.n == net->n && g.cur == net->cur && g.dpar == net->dpar && g.wpar == net->wpar &&
-           g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity && g.rebuild_first == rebuild_first && g.staged == net->staged && g.grew == net->grew && g.slots == net->slots &&
+           g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity && g.rebuild_first == rebuild_first && g.staged == net->staged && g.grew == net->grew && g.slots == net->slots && g.appended == net->appended &&
            g.small_run == net->small_run &&
            g.tune_split == net->tune_split && g.tune_variant == net->tune_variant &&
            g.tune_grab == net->tune_grab && g.tune_rebucket == net->tune_rebucket &&
@@ -957,6 +983,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.staged = net->staged;
     g.grew = net->grew;
     g.slots = net->slots;
+    g.appended = net->appended;
     g.small_run = net->small_run;
     g.tune_split = net->tune_split; g.tune_variant = net->tune_variant;
     g.tune_grab = net->tune_grab; g.tune_rebucket = net->tune_rebucket;
@@ -966,7 +993,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     const int cur0 = net->cur, dpar0 = net->dpar, wpar0 = net->wpar, sp0 = net->stage_parity;
     const int up0 = net->sup_parity;
     const bool staged0 = net->staged, grew0 = net->grew;
-    const int32_t slots0 = net->slots;
+    const int32_t slots0 = net->slots, appended0 = net->appended;
     const int64_t small0 = net->small_signals;
     const int phase0 = net->phase;
     const int32_t bn0 = net->bucket_n, f0 = net->finds_since_bucket;
@@ -998,6 +1025,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
       net->staged = staged0;
       net->grew = grew0;
       net->slots = slots0;
+      net->appended = appended0;
       net->small_signals = small0;
       net->phase = phase0;
       net->bucket_n = bn0; net->finds_since_bucket = f0;
@@ -1011,6 +1039,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.sup_parity_after = net->sup_parity;
     g.staged_after = net->staged;
     g.slots_after = net->slots;
+    g.appended_after = net->appended;
     g.small_after = net->small_signals;
     g.small_delta = net->small_signals - small0;
     g.finds_after = net->finds_since_bucket;
@@ -1022,6 +1051,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     net->staged = staged0;
     net->grew = grew0;
     net->slots = slots0;
+    net->appended = appended0;
     net->small_signals = small0;
     net->bucket_n = bn0; net->finds_since_bucket = f0;
     if (net->graphs.size() >= GSN_GRAPH_CACHE) {
@@ -1045,6 +1075,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   net->staged = hit->staged_after;
   net->grew = false;
   net->slots = hit->slots_after;
+  net->appended = hit->appended_after;
   net->small_signals = hit->rebuilt ? hit->small_after : net->small_signals + hit->small_delta;
   if (hit->rebuilt) {
     net->finds_since_bucket = hit->finds_after;
@@ -1108,10 +1139,10 @@ int gsn_run_schedule(gsn_net* net, const float* cloud, int64_t n_points,
       return rc;
     res->inserted += inserted;
     if (wcount >= sc->qe_window) {
-      int64_t sum = 0;
-      if ((rc = read_acc64(net, gsn::kA64Window, &sum, st))) return rc;
+      // (growth's wait brought the sum of this iteration's window)
+      const uint64_t sum = net->mail->window;
       if (hipMemsetAsync(s.acc64 + gsn::kA64Window, 0, 8, st) != hipSuccess) return GSN_E_HIP;
-      res->qe = static_cast<double>(static_cast<uint64_t>(sum)) * 0x1p-32 /
+      res->qe = static_cast<double>(sum) * 0x1p-32 /
                 static_cast<double>(wcount);
       have_qe = true;
       wcount = 0;
@@ -1123,9 +1154,7 @@ int gsn_run_schedule(gsn_net* net, const float* cloud, int64_t n_points,
     if (res->signals >= sc->max_signals) break;
   }
   if (!have_qe && wcount > 0) {
-    int64_t sum = 0;
-    if ((rc = read_acc64(net, gsn::kA64Window, &sum, st))) return rc;
-    res->qe = static_cast<double>(static_cast<uint64_t>(sum)) * 0x1p-32 /
+    res->qe = static_cast<double>(static_cast<uint64_t>(net->mail->window)) * 0x1p-32 /
               static_cast<double>(wcount);
   }
   if ((rc = read_acc64(net, gsn::kA64Accepted, &accepted1, st))) return rc;
@@ -1270,6 +1299,7 @@ int gsn_import(gsn_net* net, int32_t n, const float* xyz, const float* err, int3
     net->phase = kReady;
     net->bucket_n = -1;
     net->slots = 0;
+    net->appended = 0;
     net->staged = false;
     net->grew = false;
     net->small_run = 0;

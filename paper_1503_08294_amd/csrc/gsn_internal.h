@@ -614,6 +614,12 @@ hipError_t launch_init(const DevState& s, int cur, int32_t n0, int32_t n_max,
 // buffer that is not current: u and v in col[cur ^ 1], the ages in age[cur ^ 1].
 hipError_t launch_export_edges(const DevState& s, int cur, int32_t n, int32_t edges,
                                hipStream_t st);
+// Host words that growth and the schedule wait for, written by a device kernel.
+struct GrowMail {
+  int32_t orphans, inserted, kept, pad;
+  unsigned long long window;
+};
+hipError_t launch_grow_report(const DevState& s, GrowMail* mail, hipStream_t st);
 // order (of slots places; null and 0 for none): the unit order, renumbered, -1 for the removed
 hipError_t launch_remove(const DevState& s, int cur, int32_t n, int32_t n_max, int32_t* order,
                          int32_t slots, hipStream_t st);
@@ -645,7 +651,8 @@ hipError_t launch_find_grid(const DevState& s, const GridBufs& gb, const GridSpe
 hipError_t launch_draw(const float* cloud, int64_t n_points, uint64_t seed, int64_t c0,
                        int32_t m, float* sig, hipStream_t st);
 hipError_t launch_qe(const float* d1, int32_t m, unsigned long long* acc, hipStream_t st);
-// Up to `count` GNG insertions one after another; status[kStInserted] receives how many.
+// Up to `count` GNG insertions one after another; status[kStInserted] receives how many (none
+// while units wait to be removed, status[kStOrphans] > 0).
 hipError_t launch_insert(const DevState& s, int cur, int32_t n, int32_t count, float alpha,
                          int32_t n_max, int64_t half_cap, hipStream_t st);
 
