@@ -453,6 +453,10 @@ __global__ __launch_bounds__(1024) void gr_insert(int32_t n0, int32_t count, int
 // q's and f's of the prefix are pairwise distinct and the prefix applies in one parallel
 // pass.  Step 0 always qualifies, unless q_0's row is longer than 64 entries (it then takes
 // the one-wave insertion) or empty (insertion stops, as in the sequential order).
+// The rounds wait on barriers and on LDS, so T and the pool are made anew only when the pool
+// runs low: a round's changes leave it the units above the same T once its q's and f's are out
+// and the new keys still above T are in; and up to kRankSeg segments T comes from ranks instead
+// of a radix select (a call of a growing run of 1.5 M signals: 56.9 -> 40.6 us).
 constexpr int kSpecSeg = 64;      // segments above T at most (halved while the pool overflows)
 constexpr int kSpecPool = 512;    // pool units
 constexpr int kSpecRows = 4096;   // row entries of the pool units
@@ -513,6 +517,28 @@ __device__ unsigned long long kth_largest(const unsigned long long* keys, int32_
   return prefix;
 }
 
+// The same for few keys (nk <= kRankSeg): every key's rank, the threads sharing out the keys it
+// is compared with.  rank holds kRankSeg words.
+constexpr int kRankSeg = 512;
+__device__ unsigned long long kth_by_rank(const unsigned long long* keys, int32_t nk, int32_t k,
+                                          int32_t* rank, unsigned long long* out) {
+  const int t = threadIdx.x;
+  const int32_t parts = 1024 / nk, i = t % nk, p = t / nk;
+  if (t < nk) rank[t] = 0;
+  __syncthreads();
+  if (p < parts) {
+    const unsigned long long v = keys[i];
+    const int32_t j1 = (p + 1) * nk / parts;
+    int32_t r = 0;
+    for (int32_t j = p * nk / parts; j < j1; ++j) r += keys[j] > v;
+    if (r) atomicAdd(&rank[i], r);
+  }
+  __syncthreads();
+  if (t < nk && rank[t] == k - 1) *out = keys[t];
+  __syncthreads();
+  return *out;
+}
+
 __device__ __forceinline__ uint32_t spec_hash(int32_t u) {
   return (static_cast<uint32_t>(u) * 2654435761u) & (kSpecHash - 1);
 }
@@ -569,6 +595,8 @@ __global__ __launch_bounds__(1024) void gr_insert_spec(
     int32_t* __restrict__ status) {
   __shared__ unsigned long long sk[kMaxSeg];
   __shared__ int32_t hist[256];
+  static_assert(kSpecPool <= kRankSeg && 2 * kSpecPool <= 1024, "ranks; two threads a pool unit");
+  __shared__ int32_t rank[kRankSeg];
   __shared__ unsigned long long pkey[kSpecPool], skey[kSpecPool];
   __shared__ unsigned long long st_best[kSpecPool], st_mod[kSpecPool];
   __shared__ int32_t st_r0[kSpecPool], st_deg[kSpecPool], st_off[kSpecPool], st_f[kSpecPool];
@@ -585,54 +613,94 @@ __global__ __launch_bounds__(1024) void gr_insert_spec(
   int32_t nseg = (n0 + len - 1) / len;
   for (int32_t i = t; i < nseg; i += 1024) sk[i] = seg[i];
   __syncthreads();
-  int32_t n = n0, done = 0, kseg = kSpecSeg;
-  bool stop = false;
-  while (!stop && done < count && n < n_max) {
-    // ---- T and the pool (the units above T, at most kSpecPool of them)
-    const unsigned long long T = nseg > kseg ? kth_largest(sk, nseg, kseg + 1, hist, &s_bin, &s_k)
-                                             : 0ull;
+  for (int32_t i = t; i < kMaxSeg / 32; i += 1024) mark[i] = 0;
+  __syncthreads();
+  int32_t n = n0, done = 0, kseg = kSpecSeg, C = 0;
+  unsigned long long T = 0;
+  bool stop = false, pooled = false;
+  // the keys of the segments marked since the last call
+  auto rescan = [&]() {
     if (t == 0) s_cnt = 0;
     __syncthreads();
     for (int32_t i = t; i < nseg; i += 1024)
-      if (sk[i] > T) {
+      if (mark[i >> 5] >> (i & 31) & 1u) {
         const int32_t k = atomicAdd(&s_cnt, 1);
         if (k < 3 * kSpecPool) list[k] = i;
       }
     __syncthreads();
-    const int32_t nl = min(s_cnt, 3 * kSpecPool);
-    __syncthreads();
-    if (t == 0) s_cnt = 0;
-    __syncthreads();
-    for (int32_t e = t; e < nl * len; e += 1024) {
-      const int32_t u = list[e / len] * len + e % len;
-      if (u < n) {
-        const unsigned long long k = err_key(err[u], u);
-        if (k > T) {
-          const int32_t at = atomicAdd(&s_cnt, 1);
-          if (at < kSpecPool) pkey[at] = k;
-        }
+    const int32_t all = s_cnt, some = min(all, 3 * kSpecPool);
+    for (int32_t b = 0; b < some; b += 64) {
+      const int32_t my = b + (t >> 4);
+      const int32_t sg = my < some ? list[my] : -1;
+      const unsigned long long k = segment_key16(err, n, sg, len, t & 15);
+      if ((t & 15) == 0 && sg >= 0) {
+        sk[sg] = k;
+        atomicAnd(&mark[sg >> 5], ~(1u << (sg & 31)));
       }
     }
     __syncthreads();
-    const int32_t C = s_cnt;
-    __syncthreads();
+    return all > some;
+  };
+  while (!stop && done < count && n < n_max) {
     bool slow = false;
-    if (C > kSpecPool) {
-      if (kseg > 1) {
-        kseg >>= 1;
-        continue;
+    if (!pooled) {
+      // ---- T and the pool (the units above T, at most kSpecPool of them)
+      while (rescan()) {
       }
-      slow = true;  // one segment holds more pool units than fit: one sequential insertion
+      if (nseg <= kseg) T = 0;
+      else if (nseg <= kRankSeg) T = kth_by_rank(sk, nseg, kseg + 1, rank, pkey);
+      else T = kth_largest(sk, nseg, kseg + 1, hist, &s_bin, &s_k);
+      if (t == 0) s_cnt = 0;
+      __syncthreads();
+      for (int32_t i = t; i < nseg; i += 1024)
+        if (sk[i] > T) {
+          const int32_t k = atomicAdd(&s_cnt, 1);
+          if (k < 3 * kSpecPool) list[k] = i;
+        }
+      __syncthreads();
+      const int32_t nl = min(s_cnt, 3 * kSpecPool);
+      __syncthreads();
+      if (t == 0) s_cnt = 0;
+      __syncthreads();
+      for (int32_t e = t; e < nl * len; e += 1024) {
+        const int32_t u = list[e / len] * len + e % len;
+        if (u < n) {
+          const unsigned long long k = err_key(err[u], u);
+          if (k > T) {
+            const int32_t at = atomicAdd(&s_cnt, 1);
+            if (at < kSpecPool) pkey[at] = k;
+          }
+        }
+      }
+      __syncthreads();
+      C = s_cnt;
+      __syncthreads();
+      if (C > kSpecPool) {
+        if (kseg > 1) {
+          kseg >>= 1;
+          continue;
+        }
+        slow = true;  // one segment holds more pool units than fit: one sequential insertion
+      }
     }
     int32_t L = 0;
     if (!slow) {
       // ---- the pool in descending key order (ranks of distinct keys)
-      if (t < C) {
-        const unsigned long long k = pkey[t];
-        int32_t r = 0;
-        for (int32_t j = 0; j < C; ++j) r += pkey[j] > k;
-        skey[r] = k;
+      // (two threads per key, each counting in one half of the pool)
+      if (t < kSpecPool) rank[t] = 0;
+      __syncthreads();
+      {
+        const int32_t i = t & (kSpecPool - 1), half = t / kSpecPool, h = (C + 1) / 2;
+        if (i < C) {
+          const unsigned long long k = pkey[i];
+          int32_t r = 0;
+          const int32_t j1 = half ? C : h;
+          for (int32_t j = half ? h : 0; j < j1; ++j) r += pkey[j] > k;
+          if (r) atomicAdd(&rank[i], r);
+        }
       }
+      __syncthreads();
+      if (t < C) skey[rank[t]] = pkey[t];
       for (int32_t i = t; i < kSpecHash; i += 1024) {
         hk[i] = -1;
         hv[i] = INT32_MAX;
@@ -804,26 +872,35 @@ __global__ __launch_bounds__(1024) void gr_insert_spec(
         z[r] = (z[q] + z[f]) * 0.5f;
       }
     }
-    // ---- the segments of every unit touched
-    for (int32_t i = t; i < kMaxSeg / 32; i += 1024) mark[i] = 0;
+    // ---- the segments of every unit touched are due for a rescan before the next T; the pool
+    // goes on as the units above the same T: without the steps applied, with the new keys of
+    // their q's, f's and r's where these are still above it (an f's old key leaves it)
     if (t == 0) s_cnt = 0;
     __syncthreads();
     const int32_t n1 = n + L;
-    for (int32_t i = t; i < 3 * L; i += 1024) {
-      const int32_t s3 = i / 3, which = i % 3;
-      const int32_t u = which == 0 ? key_index(skey[s3]) : (which == 1 ? st_f[s3] : n + s3);
-      const int32_t sg = u / len;
-      if ((atomicOr(&mark[sg >> 5], 1u << (sg & 31)) & (1u << (sg & 31))) == 0)
-        list[atomicAdd(&s_cnt, 1)] = sg;
+    auto enter = [&](unsigned long long k) {
+      if (k > T) {
+        const int32_t at = atomicAdd(&s_cnt, 1);
+        if (at < kSpecPool) pkey[at] = k;
+      }
+    };
+    if (t < L) {
+      const int32_t q = key_index(skey[t]), f = st_f[t], r = n + t;
+      const int32_t us[3] = {q, f, r};
+      for (int k = 0; k < 3; ++k) {
+        const int32_t sg = us[k] / len;
+        atomicOr(&mark[sg >> 5], 1u << (sg & 31));
+      }
+      const float eq = key_err(skey[t]) * alpha;
+      enter(err_key(eq, q));
+      enter(err_key(key_err(st_best[t]) * alpha, f));
+      enter(err_key(eq, r));
+    } else if (!slow && t < C && touch_find(hk, hv, key_index(skey[t])) >= L) {
+      enter(skey[t]);
     }
     __syncthreads();
-    const int32_t nmark = s_cnt;
-    for (int32_t b = 0; b < nmark; b += 64) {
-      const int32_t my = b + (t >> 4);
-      const int32_t sg = my < nmark ? list[my] : -1;
-      const unsigned long long k = segment_key16(err, n1, sg, len, t & 15);
-      if ((t & 15) == 0 && sg >= 0) sk[sg] = k;
-    }
+    C = s_cnt;
+    pooled = !slow && C >= min(kSpecMin, count - done - L) && C <= kSpecPool;
     n = n1;
     done += L;
     nseg = (n + len - 1) / len;
@@ -831,6 +908,8 @@ __global__ __launch_bounds__(1024) void gr_insert_spec(
     __syncthreads();
     if (!slow || stop || done >= count || n >= n_max) continue;
     // ---- one insertion by the one-wave path: q = the largest segment key
+    while (rescan()) {
+    }
     unsigned long long best = 0;
     for (int32_t i = t; i < nseg; i += 1024) best = sk[i] > best ? sk[i] : best;
     best = wave_max(best);
