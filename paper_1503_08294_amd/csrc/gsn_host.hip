@@ -154,7 +154,8 @@ using gsn::DevState;
 
 enum Phase { kReady = 0, kFound = 1, kResolved = 2, kAdapted = 3 };
 constexpr int kRebucketEvery = 64;     // default calls between rebuilds of the unit order
-// Iterations of small batches on the same units after which they take the pruned search: its
+// Iterations of small batches on the same units, or finds alone on units at rest, after which
+// they take the pruned search: its
 // order and records cost about 60 us once, and then an iteration of a recorded loop takes less
 // (64 signals on 100,000 units 18.3 us against 24.6, 256 19.4 against 41.9, one 15.1 against
 // 15.7; 256 on 1,000 units 16.4 against 18.0).
@@ -201,6 +202,7 @@ struct gsn_net {
   int32_t finds_since_bucket;  // staged finds of more than kSmallM signals since it was made
   int64_t small_signals;       // signals of the smaller ones
   int32_t small_run;           // smaller iterations since the units were last replaced or grew
+  int32_t still;               // finds alone of small batches since the units last moved
   int grid_rounds;             // grid-wide rounds of the winner-lock update (0: automatic)
   int32_t* feedback;           // pinned host word: the last update's grid rounds used
   int32_t* feedback_dev;       // its device address, stored by the update's last kernel
@@ -412,6 +414,7 @@ int grow_step(gsn_net* net, int32_t count, int32_t* inserted_out, hipStream_t st
     net->staged = false;
     net->grew = true;
     net->small_run = 0;
+    net->still = 0;
     tried = can_insert();
     if (tried && ((rc = insert_units(net, count, st)) || (rc = read_mail(net, st)))) return rc;
   }
@@ -422,6 +425,7 @@ int grow_step(gsn_net* net, int32_t count, int32_t* inserted_out, hipStream_t st
     net->staged = false;
     net->grew = true;
     net->small_run = 0;
+    net->still = 0;
     // new units take the next indices: they join the spatial order at its end (the
     // periodic rebucketing restores locality)
     if (net->bucket_n == n_before && net->slots + inserted <= gsn::stage_slots(net->p.n_max)) {
@@ -483,6 +487,7 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   net->appended = 0;
   net->small_signals = 0;
   net->small_run = 0;
+  net->still = 0;
   net->grid_rounds = 0;
   net->graph_clock = 0;
   net->loop_records = 0;
@@ -572,26 +577,32 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
   hipStream_t st = as_stream(stream);
   gsn::FindConfig cfg =
       gsn::find_config(net->n, m, net->cus, net->tune_split, net->tune_variant);
+  // A small batch takes the search too where its records are at hand, or after enough finds of
+  // the same positions or, in an iteration, enough iterations on the same units.
+  const bool small = m <= gsn::kSmallM;
+  const bool may_search = cfg.variant == 6 && net->tune_variant == 0 && !net->foreign;
+  if (may_search) {
+    int32_t& run = claim ? net->small_run : net->still;
+    run = std::min(run + 1, kSmallRun);
+    if ((net->staged && net->bucket_n == net->n) || run >= kSmallRun) cfg.variant = 7;
+  }
   // Recorded by the caller (not by gsn_iterate_loop, which tracks what its graph leaves): the
   // launches run later and perhaps often, so they may not rely on records or an order that
   // are in place now, and leave the handle's account of them alone.
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (!net->capturing && hipStreamIsCapturing(st, &cs) != hipSuccess) {
-    (void)hipGetLastError();
-    cs = hipStreamCaptureStatusNone;
+  bool recorded = false;
+  if (cfg.variant != 6 && cfg.variant >= 2 && !net->capturing) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
+    else recorded = cs != hipStreamCaptureStatusNone;
   }
-  const bool recorded = cs != hipStreamCaptureStatusNone;
-  if (recorded) net->staged = false;
-  // A small batch takes the search too where its records are at hand, or, in an iteration,
-  // after enough iterations on the same units.
-  const bool small = m <= gsn::kSmallM;
-  if (cfg.variant == 6 && net->tune_variant == 0 && !recorded) {
-    if (claim) net->small_run = std::min(net->small_run + 1, kSmallRun);
-    if (net->foreign) net->small_run = 0;
-    if ((net->staged && net->bucket_n == net->n) || (claim && net->small_run >= kSmallRun))
-      cfg.variant = 7;
+  if (recorded && may_search) {
+    cfg.variant = 6;   // the scan that needs neither
+    recorded = false;
   }
-  if (recorded && cfg.variant >= 2 && cfg.variant != 6) net->foreign = true;
+  if (recorded) {
+    net->staged = false;
+    net->foreign = true;
+  }
   net->searched = cfg.variant == 7 && !net->foreign;
   TimedRegion all(net, GSN_T_FIND, st);
   hipError_t e;
@@ -685,6 +696,7 @@ int update_impl(gsn_net* net, const float* sig, int32_t m, const int32_t* winner
   const bool ahead = net->searched && net->staged && !net->grew && m > 0 && gsn::update_gathers(net->n) &&
                      (net->capturing || !order_due(net, m, 1));
   net->staged = false;
+  net->still = 0;
   net->grew = false;
   gsn::GatherArgs ga{};
   if (ahead)
@@ -863,6 +875,7 @@ int gsn_adapt(gsn_net* net, const float* sig, int32_t m, const int32_t* winner,
   if (m > 0 && (!sig || !winner || !second || !d1 || !accepted)) return GSN_E_INVAL;
   net->phase = kAdapted;
   net->staged = false;
+  net->still = 0;
   hipStream_t st = as_stream(stream);
   TimedRegion t(net, GSN_T_ADAPT, st);
   hipError_t e;
@@ -1303,6 +1316,7 @@ int gsn_import(gsn_net* net, int32_t n, const float* xyz, const float* err, int3
     net->staged = false;
     net->grew = false;
     net->small_run = 0;
+    net->still = 0;
   } catch (const std::bad_alloc&) {
     return GSN_E_CAPACITY;
   }

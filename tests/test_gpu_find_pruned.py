@@ -98,8 +98,8 @@ def test_records_follow_every_change_of_the_units(lock_mode):
         return rng.standard_normal((3, k)).astype(np.float32)
 
     for t in range(1, 31):
-        what = ("fused", "steps", "grow", "small", "index", "twice", "import", "loop")[
-            int(rng.integers(0, 8))]
+        what = ("fused", "steps", "grow", "small", "index", "twice", "import", "loop", "still")[
+            int(rng.integers(0, 9))]
         sig = batch(60 if what == "small" else m)
         if what in ("fused", "small"):
             assert_iter_equal(*pair.iterate(sig), f"{t} {what}")
@@ -119,6 +119,9 @@ def test_records_follow_every_change_of_the_units(lock_mode):
         elif what == "twice":
             for _ in range(2):
                 assert_find_equal(*pair.find(batch()), f"{t} {what}")
+        elif what == "still":
+            for _ in range(10):
+                assert_find_equal(*pair.find(batch(37)), f"{t} {what}")
         elif what == "import":
             s = pair.orc.export()
             s["xyz"] = (s["xyz"] * np.float32(1.1)).astype(np.float32)
