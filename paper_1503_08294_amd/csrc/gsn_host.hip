@@ -96,7 +96,7 @@ Layout layout_for(const gsn_params& p) {
   add(wl ? 32 * nm : 0);       // 35 survivor records (key, second), two parities
   add(wl ? 2 * nm : 0);        // 36 survivor flags, two parities
   add(wl ? 8 * nm : 0);        // 37 heads of the second lists, two parities
-  add(wl ? 4 * mm : 0);        // 38 links of the second lists
+  add(wl ? 8 * mm : 0);        // 38 links of the second lists
   add(wl ? 8 : 0);             // 39 table bounds
   L.total = (o + 255) & ~static_cast<size_t>(255);
   return L;
@@ -144,7 +144,7 @@ void carve(const gsn_params& p, void* base, DevState* s) {
   s->wkey = wl ? reinterpret_cast<unsigned long long*>(b + L.off[35]) : nullptr;
   s->wflag = wl ? reinterpret_cast<uint8_t*>(b + L.off[36]) : nullptr;
   s->rhead = wl ? reinterpret_cast<int32_t*>(b + L.off[37]) : nullptr;
-  s->rnext = wl ? reinterpret_cast<int32_t*>(b + L.off[38]) : nullptr;
+  s->rlink = wl ? reinterpret_cast<int2*>(b + L.off[38]) : nullptr;
   s->whi = wl ? reinterpret_cast<int32_t*>(b + L.off[39]) : nullptr;
 }
 

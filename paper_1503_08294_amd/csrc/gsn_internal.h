@@ -338,7 +338,8 @@ struct DevState {
                                    //               first, so that the records of the many
                                    //               units without one are not fetched
   int32_t* rhead;                  // [2 n_max]     a survivor whose second is the unit, -1 none
-  int32_t* rnext;                  // [m_max]       the next survivor with the same second
+  int2* rlink;                     // [m_max]       the next survivor with the same second, and
+                                   //               this one's winner
   int32_t* whi;                    // [2]           tables of parity q hold entries below whi[q]
   // growing-network schedule
   float* ssig;                     // [3 m_max]     signals of the iteration, SoA
@@ -524,7 +525,7 @@ struct WinnerTables {
   unsigned long long* wkey;
   uint8_t* wflag;
   int32_t* rhead;
-  int32_t* rnext;
+  int2* rlink;
   int32_t* whi;
   int par;
 };

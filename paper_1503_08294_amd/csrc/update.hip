@@ -121,7 +121,7 @@ __global__ void rs_check(int32_t m, int32_t n, const int32_t* __restrict__ winne
         reinterpret_cast<ulonglong2*>(tab.wkey)[b] =
             make_ulonglong2(key, static_cast<uint32_t>(s));
         tab.wflag[b] = 1;
-        tab.rnext[j] = atomicExch(&tab.rhead[s], j);
+        tab.rlink[j] = make_int2(atomicExch(&tab.rhead[s], j), b);
       }
     }
     accepted[j] = ok ? 1 : 0;

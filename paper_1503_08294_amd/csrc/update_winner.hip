@@ -594,7 +594,7 @@ __global__ __launch_bounds__(kTailBlock) void wl_tail(RoundArgs a, int32_t grid_
 //     after E_v;
 //   * its error grows by d1 in E_x.
 // The steps that can involve x are those of x, of its neighbours before the update, of the
-// survivors whose second is x (a list per unit, rhead / rnext), and that of the second of
+// survivors whose second is x (a list per unit, rhead / rlink), and that of the second of
 // E_x.  The resolve's check fills the tables (the key and second of each winner's
 // survivor, and the list of the survivors by second); then one thread per unit finds the
 // steps: two launches and no rounds.  The tables have two
@@ -610,7 +610,7 @@ struct LocalArgs {
   unsigned long long* wkey;  // tables of this update's parity (records of key and second)
   uint8_t* wflag;            // 1 iff the unit has a record
   int32_t* rhead;
-  int32_t* rnext;
+  int2* rlink;
   unsigned long long* wkey_o;  // tables of the other parity (cleared by wu_write)
   uint8_t* wflag_o;
   int32_t* rhead_o;
@@ -698,12 +698,29 @@ __device__ __forceinline__ EdgeState edge_state(bool alive0, int32_t age0, int32
 // f(w, alive0, age0, sw) for every unit w that can share an edge with x in this update, each
 // once: the neighbours before it (in ascending order), then the winners of the survivors
 // whose second is x, then the second of the step of x.
+// The loads form few dependent rounds: the list's head, the flag of x's second and the row's
+// bounds first; then the first list node, that second's record and the row's first eight
+// entries, which stay in registers, so that whether a unit is in a short row needs no further
+// load; a list node holds its survivor's winner, and the next node is on its way while one is
+// used.
 template <typename F>
 __device__ __forceinline__ void for_each_incident(const LocalArgs& a, int32_t x, const Surv& sx,
                                                   F&& f) {
+  const int32_t head = a.rhead[x];
   const int32_t r0 = a.rp[x], l = a.rp[x + 1] - r0;
+  const bool own = has_step(sx) && sx.sec >= 0 && sx.sec < a.n;
+  const int32_t t = own ? sx.sec : x;
+  const bool tf = own && a.wflag[t] != 0;
+  auto node_ok = [&](int32_t j) { return j >= 0 && j < a.m; };
+  int2 node = make_int2(-1, -1);
+  if (node_ok(head)) node = a.rlink[head];
+  Surv st{~0ull, -1};
+  if (tf) st = surv_of(a, t);
   // the row in batches of eight entries, each batch's entries and then their survivor
   // records loaded together
+  int32_t w0[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) w0[i] = -1;
   for (int32_t k0 = 0; k0 < l; k0 += 8) {
     int32_t w[8], g[8];
 #pragma unroll
@@ -713,6 +730,7 @@ __device__ __forceinline__ void for_each_incident(const LocalArgs& a, int32_t x,
       if (k0 + i < l) {
         w[i] = a.col[r0 + k0 + i];
         g[i] = a.age[r0 + k0 + i];
+        if (k0 == 0) w0[i] = w[i];
       }
     }
     bool fl[8];
@@ -725,19 +743,24 @@ __device__ __forceinline__ void for_each_incident(const LocalArgs& a, int32_t x,
     for (int i = 0; i < 8; ++i)
       if (k0 + i < l) f(w[i], true, g[i], sw[i]);
   }
+  auto in_row = [&](int32_t v) {
+    if (l > 8) return slice_find(a.col, r0, r0 + l, v) >= 0;
+    bool in = false;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) in |= w0[i] == v;
+    return in;
+  };
   // (a list holds distinct signals of this update, so it ends within m links; the bounds
   // only keep a corrupted table from reading out of range)
   int32_t steps = 0;
-  for (int32_t j = a.rhead[x]; j >= 0 && j < a.m && steps < a.m; j = a.rnext[j], ++steps) {
-    const int32_t b = a.winner[j];
-    if (b >= 0 && b < a.n && row_find(a.col, r0, l, b) < 0) f(b, false, 0, surv_of(a, b));
+  for (int32_t j = head; node_ok(j) && steps < a.m; ++steps) {
+    const int32_t b = node.y;
+    j = node.x;
+    if (node_ok(j)) node = a.rlink[j];
+    if (b >= 0 && b < a.n && !in_row(b)) f(b, false, 0, surv_of(a, b));
   }
-  if (has_step(sx) && sx.sec >= 0 && sx.sec < a.n) {
-    const int32_t t = sx.sec;
-    const Surv st = surv_flagged(a, t);
-    // (a second whose own step has x as its second is in the list above)
-    if (row_find(a.col, r0, l, t) < 0 && !(has_step(st) && st.sec == x)) f(t, false, 0, st);
-  }
+  // (a second whose own step has x as its second is in the list above)
+  if (own && !in_row(t) && !(has_step(st) && st.sec == x)) f(t, false, 0, st);
 }
 
 constexpr int kMoves = 8;  // moves of a unit gathered per pass
@@ -781,15 +804,26 @@ __global__ __launch_bounds__(kBlock) void wu_apply(LocalArgs a) {
         offer(sw.key);
     };
     auto apply_moves = [&]() {
+      // the signals of all of them on their way before the first is applied
+      float mx[kMoves], my[kMoves], mz[kMoves];
+#pragma unroll
+      for (int i = 0; i < kMoves; ++i) {
+        mx[i] = my[i] = mz[i] = 0.0f;
+        if (keys[i] != ~0ull) {
+          const int32_t j = static_cast<int32_t>(static_cast<uint32_t>(keys[i]));
+          mx[i] = a.sig[j];
+          my[i] = a.sig[a.m + j];
+          mz[i] = a.sig[2 * a.m + j];
+        }
+      }
 #pragma unroll
       for (int i = 0; i < kMoves; ++i) {
         if (keys[i] == ~0ull) continue;
-        const int32_t j = static_cast<int32_t>(static_cast<uint32_t>(keys[i]));
         const float eps = keys[i] == sx.key ? a.eps_b : a.eps_n;
         float t;
-        t = a.sig[j] - px; t = eps * t; px = px + t;
-        t = a.sig[a.m + j] - py; t = eps * t; py = py + t;
-        t = a.sig[2 * a.m + j] - pz; t = eps * t; pz = pz + t;
+        t = mx[i] - px; t = eps * t; px = px + t;
+        t = my[i] - py; t = eps * t; py = py + t;
+        t = mz[i] - pz; t = eps * t; pz = pz + t;
         moved = true;
       }
     };
@@ -955,7 +989,7 @@ namespace gsn {
 
 WinnerTables winner_tables(const DevState& s, int par, int32_t n_max) {
   const size_t nm = static_cast<size_t>(n_max);
-  return WinnerTables{s.wkey + 2 * par * nm, s.wflag + par * nm, s.rhead + par * nm, s.rnext,
+  return WinnerTables{s.wkey + 2 * par * nm, s.wflag + par * nm, s.rhead + par * nm, s.rlink,
                       s.whi, par};
 }
 
@@ -968,7 +1002,7 @@ hipError_t launch_winner_local(const DevState& s, int cur, int par, int32_t n,
   const int nb = blocks(n);
   const int fold = nb <= kFoldBlocks;
   LocalArgs a{w.sig, w.m, n, w.winner, w.d1,
-              s.wkey + 2 * par * nm, s.wflag + par * nm, s.rhead + par * nm, s.rnext,
+              s.wkey + 2 * par * nm, s.wflag + par * nm, s.rhead + par * nm, s.rlink,
               s.wkey + 2 * po * nm, s.wflag + po * nm, s.rhead + po * nm, s.whi, par,
               s.rp[cur], s.col[cur], s.age[cur], s.rp[nxt], s.col[nxt], s.age[nxt],
               s.x, s.y, s.z, s.err, s.orphan, s.status, s.cnt, s.bsum,
