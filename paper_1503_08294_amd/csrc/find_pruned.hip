@@ -120,6 +120,7 @@ constexpr int kFewUnits = 3;     // a cell with fewer leaves the first bound to 
 // kMostLeaves will do.
 constexpr int kFewLeaves = 40;
 constexpr int kMostLeaves = 64;
+constexpr int kNearFrom = 8;     // passing leaves before the nearest is looked for
 constexpr int kMostTops = 32;
 constexpr int kTries = 4;
 
@@ -278,7 +279,8 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
       for (int u = 0; u < kUnroll; ++u) {
         const bool pass = k + u * kRows < mt && f[u] < a.nleaf && f[u] != skip &&
                           !(lb[u] > bound);
-        if (pass && f[u] != tried) near = min(near, pack_key(lb[u], f[u]));
+        // (of the first few there is no need: most signals have no more)
+        if (nl > kNearFrom && pass && f[u] != tried) near = min(near, pack_key(lb[u], f[u]));
         const Bits b = bits(pass);
         const int32_t at = nl + below(b);
         if (pass && at < kMostLeaves) leaves[g][at] = f[u];
@@ -330,7 +332,10 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
       }
     }
   }
-  merge_group<L>(k1, k2);
+  // the least key of the group, then the least of the others
+  const unsigned long long best1 = min_group<L>(k1);
+  k2 = min_group<L>(k1 == best1 ? k2 : k1);
+  k1 = best1;
 
   const int32_t bw = static_cast<int32_t>(static_cast<uint32_t>(k1));
   const int32_t sw = static_cast<int32_t>(static_cast<uint32_t>(k2));
