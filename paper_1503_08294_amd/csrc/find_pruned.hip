@@ -22,9 +22,9 @@
 // compacted in LDS, and evaluate the units of the leaves that pass (about six of 32 units on a
 // surface).  The kernel is bound by the vector unit for many signals (about 210 instructions a
 // signal) and by the chain of seven dependent loads for few.  At 200,000 units and 16,384
-// signals an iteration's find takes 8 us of gather and 17 us of search with its claims, where
-// staging, the exhaustive screen on the matrix cores and its merge took 125; at 100,000 and
-// 65,536, 6 + 41 us where they took 231.  What it took: boxes in three levels with leaves of 32
+// signals an iteration's search takes 16.5 us with its claims (and 3.7 more in the rewrite that
+// gathers for it), where staging, the exhaustive screen on the matrix cores and its merge took
+// 125; at 100,000 and 65,536, 35.5 us where they took 231.  What it took: boxes in three levels with leaves of 32
 // units (88 us with 64 and two levels), cells in cubes, 64 a side (32 a side fitted to the box:
 // a quarter more leaves), and the tries below, without which the few signals with a poor first
 // bound (one unit in their cell, the next in Morton order far off) held up four launches in
@@ -116,11 +116,12 @@ struct PrunedArgs {
 
 constexpr int kFewUnits = 3;     // a cell with fewer leaves the first bound to a larger one
 // A signal with more passing leaves than this has a poor bound: the nearest of those leaves
-// improves it and the boxes are tested again, up to kTries times in all; on the last try up to
+// improve it and the boxes are tested again, up to kTries times in all; on the last try up to
 // kMostLeaves will do.
 constexpr int kFewLeaves = 40;
 constexpr int kMostLeaves = 64;
-constexpr int kNearFrom = 8;     // passing leaves before the nearest is looked for
+constexpr int kNearFrom = 8;     // passing leaves before the nearest is looked for (first try)
+constexpr int kNearLeaves = 8;   // nearest leaves evaluated before another try
 constexpr int kMostTops = 32;
 constexpr int kTries = 4;
 
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
         const bool pass = k + u * kRows < mt && f[u] < a.nleaf && f[u] != skip &&
                           !(lb[u] > bound);
         // (of the first few there is no need: most signals have no more)
-        if (nl > kNearFrom && pass && f[u] != tried) near = min(near, pack_key(lb[u], f[u]));
+        if ((nl > kNearFrom || attempt > 1) && pass && f[u] != tried) near = min(near, pack_key(lb[u], f[u]));
         const Bits b = bits(pass);
         const int32_t at = nl + below(b);
         if (pass && at < kMostLeaves) leaves[g][at] = f[u];
@@ -291,13 +292,18 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
     many = nt > kMostTops || nl > kMostLeaves;
     if (attempt == kTries || (!many && nl <= kFewLeaves)) break;
 
-    // (with each try the lists start again from nothing: a unit enters them once)
-    near = min_group<L>(near);
-    if (near == kNone) break;
-    tried = static_cast<int32_t>(static_cast<uint32_t>(near));
-    k1 = k2 = kNone;
-    eval(load_leaf(tried, tried), false);
-    tighten();
+    // Nearest first, each lane's nearest leaf in turn, while one is nearer than the bound: boxes
+    // that span a jump of the order hold many signals and few units near them.  (With each try
+    // the lists start again from nothing: a unit enters them once.)
+    for (int i = 0; i < kNearLeaves; ++i) {
+      const unsigned long long best = min_group<L>(near);
+      if (best == kNone || __uint_as_float(static_cast<uint32_t>(best >> 32)) > bound) break;
+      if (near == best) near = kNone;
+      tried = static_cast<int32_t>(static_cast<uint32_t>(best));
+      k1 = k2 = kNone;
+      eval(load_leaf(tried, tried), false);
+      tighten();
+    }
     k1 = k2 = kNone;
     skip = -1;
   }
