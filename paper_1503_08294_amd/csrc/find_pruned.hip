@@ -1,10 +1,10 @@
 // Find Winners over the units in spatial order, with whole blocks of units left out where a
-// bound shows that they hold neither of the two nearest (variant 7, the default for larger
-// batches).
+// bound shows that they hold neither of the two nearest (variant 7: the default above 256
+// signals, and for smaller batches in a running network).
 //
 // Order and blocks.  The units are gathered into the staging's spatial order (staging.hip)
-// as packed (x, y, z, index) records; every leaf of kLeaf = 64 consecutive records and every
-// block of kTop = 1,024 has its bounding box (pr_gather, from the positions of this call, so
+// as packed (x, y, z, index) records; every leaf of 32 consecutive records, every top of 512 and
+// every sixteen tops have their bounding box (pruned_gather.h, from the present positions, so
 // the boxes are exact however old the order is; the order affects speed only).
 //
 // The bound needs no rounding margin.  With g_a = max(lo_a - s_a, s_a - hi_a, 0), each
@@ -24,11 +24,12 @@
 // signal) and by the chain of seven dependent loads for few.  At 200,000 units and 16,384
 // signals an iteration's search takes 16.5 us with its claims (and 3.7 more in the rewrite that
 // gathers for it), where staging, the exhaustive screen on the matrix cores and its merge took
-// 125; at 100,000 and 65,536, 35.5 us where they took 231.  What it took: boxes in three levels with leaves of 32
-// units (88 us with 64 and two levels), cells in cubes, 64 a side (32 a side fitted to the box:
-// a quarter more leaves), and the tries below, without which the few signals with a poor first
-// bound (one unit in their cell, the next in Morton order far off) held up four launches in
-// ten by 12 to 40 us.  16 lanes a signal measured 26.3 and 43.6 us, 8 and 4 lanes more.
+// 125; at 100,000 and 65,536, 35.5 us where they took 231.  What it took: boxes in three levels
+// with leaves of 32 units (88 us with 64 and two levels), cells in cubes, 64 a side (32 a side
+// fitted to the box: a quarter more leaves), and the tries below, without which the few signals
+// with a poor first bound (one unit in their cell, the next in Morton order far off) held up
+// four launches in ten by 12 to 40 us.  16 lanes a signal measured 26.3 and 43.6 us (when 32
+// measured 20.6 and 42.1), 8 and 4 lanes more.
 #include <type_traits>
 
 #include "pruned_gather.h"

@@ -365,7 +365,7 @@ void carve(const gsn_params& p, void* base, DevState* s);
 struct FindConfig {
   int variant;   // 1 = direct scan, 2 = screened scan (VALU), 3 = screened scan (MFMA),
                  // 4 = screened scan (split binary16 MFMA), 5 = variant 4 with dynamic grabs,
-                 // 6 = small-batch unit-parallel scan
+                 // 6 = small-batch unit-parallel scan, 7 = pruned search (automatic only)
   int split;     // unit chunks (variant 5: partial rows, 8 per replica)
 };
 FindConfig find_config(int32_t n, int32_t m, int cus, int want_split, int want_variant);
