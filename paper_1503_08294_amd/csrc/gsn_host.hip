@@ -192,8 +192,9 @@ struct gsn_net {
   bool staged;
   bool grew;
   bool searched;     // the last find took the pruned search
-  bool foreign;      // a caller recorded a staged find: its graph may run at any time and
-                     // rewrite the records, so each find makes its own
+  bool foreign;      // a caller recorded a staged find or an update: its graph may run at any
+                     // time and rewrite the records or move the units, so each find makes its
+                     // own records
   bool timing;
   uint32_t timing_mask;  // timers that record while timing is on (bit GSN_T_*)
   int32_t bucket_n;            // units in the spatial order (-1: none, or not these units)
@@ -560,6 +561,17 @@ bool order_due(const gsn_net* net, int32_t m, int64_t count) {
   return net->small_signals + m * count > std::max(net->n, 64 * gsn::kSmallM);
 }
 
+// Whether the caller, not gsn_iterate_loop, records the launches on st into a graph.
+bool caller_records(const gsn_net* net, hipStream_t st) {
+  if (net->capturing) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs != hipStreamCaptureStatusNone;
+}
+
 // gsn_find_winners; with claim not null the merge of the staged scans also makes the
 // lock-set claims of every signal, and *claimed says whether it did (the direct scan's
 // merge does not).
@@ -589,12 +601,7 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
   // Recorded by the caller (not by gsn_iterate_loop, which tracks what its graph leaves): the
   // launches run later and perhaps often, so they may not rely on records or an order that
   // are in place now, and leave the handle's account of them alone.
-  bool recorded = false;
-  if (cfg.variant != 6 && cfg.variant >= 2 && !net->capturing) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
-    else recorded = cs != hipStreamCaptureStatusNone;
-  }
+  bool recorded = cfg.variant != 6 && cfg.variant >= 2 && caller_records(net, st);
   if (recorded && may_search) {
     cfg.variant = 6;   // the scan that needs neither
     recorded = false;
@@ -691,6 +698,10 @@ int update_impl(gsn_net* net, const float* sig, int32_t m, const int32_t* winner
                 bool claimed, const int32_t* order) {
   hipStream_t st = as_stream(stream);
   const int64_t half_cap = 2 * static_cast<int64_t>(net->p.e_max);
+  if (caller_records(net, st)) {   // its graph may move the units at any time
+    net->staged = false;
+    net->foreign = true;
+  }
   // The update moves units.  Its last launch gathers them for the next search if this find took
   // the search and the next one is due to use the same units in the same order.
   const bool ahead = net->searched && net->staged && !net->grew && m > 0 && gsn::update_gathers(net->n) &&
@@ -873,10 +884,11 @@ int gsn_adapt(gsn_net* net, const float* sig, int32_t m, const int32_t* winner,
   if (!net || m < 0 || m > net->p.m_max) return GSN_E_INVAL;
   if (net->phase != kResolved) return GSN_E_STATE;
   if (m > 0 && (!sig || !winner || !second || !d1 || !accepted)) return GSN_E_INVAL;
+  hipStream_t st = as_stream(stream);
   net->phase = kAdapted;
+  if (caller_records(net, st)) net->foreign = true;   // its graph may move the units at any time
   net->staged = false;
   net->still = 0;
-  hipStream_t st = as_stream(stream);
   TimedRegion t(net, GSN_T_ADAPT, st);
   hipError_t e;
   if (net->p.lock_mode == 1 && m > 0 && net->n > 0) {
@@ -1085,7 +1097,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   net->wpar = hit->wpar_after;
   net->stage_parity = hit->stage_parity_after;
   net->sup_parity = hit->sup_parity_after;
-  net->staged = hit->staged_after;
+  net->staged = hit->staged_after && !net->foreign;
   net->grew = false;
   net->slots = hit->slots_after;
   net->appended = hit->appended_after;

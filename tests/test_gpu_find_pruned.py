@@ -170,3 +170,43 @@ def test_a_find_recorded_by_the_caller(m):
         step()
         step()
     pair.compare_state("end")
+
+
+@pytest.mark.parametrize("lock_mode", [0, 1, 2])
+@pytest.mark.parametrize("m", [64, 600])
+def test_iterations_recorded_by_the_caller(m, lock_mode):
+    """Two iterations in the caller's own graph move the units at each replay, without a call
+    that the handle sees: finds and recorded loops in between keep no records of them."""
+    import torch
+    rng = np.random.default_rng(m)
+    n = 4_000
+    units = rng.standard_normal((3, n)).astype(np.float32)
+    pair = Pair(units, m_max=600, eps_b=0.5, eps_n=0.1, max_age=3, lock_mode=lock_mode)
+
+    def batch():
+        return rng.standard_normal((3, m)).astype(np.float32)
+
+    for _ in range(12):   # enough for small batches to take the search
+        assert_iter_equal(*pair.iterate(batch()))
+    sig = [pair.to_dev(batch()) for _ in range(2)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        for s in sig:
+            pair.net.iterate(s)
+    for t in range(3):
+        new = [batch() for _ in sig]
+        for s, b in zip(sig, new):
+            s.copy_(pair.to_dev(b))
+        graph.replay()
+        torch.cuda.synchronize()
+        for b in new:
+            pair.orc.iterate(b, 0, 0, False)
+        assert_find_equal(*pair.find(batch()), f"{t} eager find")
+        for k in range(2):
+            assert_iter_equal(*pair.iterate(batch()), f"{t} {k}")
+        loop = [batch() for _ in sig]
+        pair.net.iterate_loop(pair.to_dev(np.stack(loop)))
+        for b in loop:
+            pair.orc.iterate(b, 0, 0, False)
+    pair.compare_state("end")
