@@ -550,11 +550,13 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
 
 namespace {
 
-// Whether a staged find of m signals, or one of `count` of them in a row, is due to rebuild the
-// unit order: when there is none of these units, every tune_rebucket finds, and, for small
-// batches, which move few units, about once for as many signals as units.
-bool order_due(const gsn_net* net, int32_t m, int64_t count) {
+// Whether a staged find of m signals with this variant, or one of `count` of them in a row, is
+// due to rebuild the unit order: when there is none of these units, when it has empty places and
+// a scan is to use it (which reads the first n places, unlike the search), every tune_rebucket
+// finds, and, for small batches, which move few units, about once for as many signals as units.
+bool order_due(const gsn_net* net, int variant, int32_t m, int64_t count) {
   if (net->bucket_n != net->n) return true;
+  if (variant >= 2 && variant <= 5 && net->slots != net->n) return true;
   // units appended far from their place are in the way of every signal
   if (static_cast<int64_t>(net->appended) * kAppendedPart > net->n) return true;
   if (m > gsn::kSmallM) return net->finds_since_bucket + count > net->tune_rebucket;
@@ -625,9 +627,8 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
     }
   } else if (cfg.variant >= 2) {
     const gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
-    // the unit order is rebuilt when the network changed and every kRebucketEvery calls (the
-    // scans, unlike the search, take no order with empty places)
-    bool rebucket = order_due(net, m, 1) || (cfg.variant != 7 && net->slots != net->n);
+    // the unit order is rebuilt when the network changed and every kRebucketEvery calls
+    bool rebucket = order_due(net, cfg.variant, m, 1);
     if (net->loop_rebuild >= 0) {  // the first staged find of a recorded loop
       rebucket = net->loop_rebuild == 1;
       net->loop_rebuild = -1;
@@ -705,7 +706,7 @@ int update_impl(gsn_net* net, const float* sig, int32_t m, const int32_t* winner
   // The update moves units.  Its last launch gathers them for the next search if this find took
   // the search and the next one is due to use the same units in the same order.
   const bool ahead = net->searched && net->staged && !net->grew && m > 0 && gsn::update_gathers(net->n) &&
-                     (net->capturing || !order_due(net, m, 1));
+                     (net->capturing || !order_due(net, 7, m, 1));
   net->staged = false;
   net->still = 0;
   net->grew = false;
@@ -974,7 +975,10 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   hipStream_t st = as_stream(stream);
   // the unit order is rebuilt at the first iteration if the usual rule would rebuild it
   // anywhere inside the loop (after that the usual rule applies, from a fresh count)
-  const bool rebuild_first = order_due(net, m, count);
+  const int variant =
+      m > 0 ? gsn::find_config(net->n, m, net->cus, net->tune_split, net->tune_variant).variant
+            : 0;
+  const bool rebuild_first = order_due(net, variant, m, count);
   // (small batches decide at the first iteration whether they take the search)
   if (m > 0 && m <= gsn::kSmallM)
     net->small_run = std::min<int32_t>(net->small_run + count, kSmallRun);

@@ -210,3 +210,46 @@ def test_iterations_recorded_by_the_caller(m, lock_mode):
         for b in loop:
             pair.orc.iterate(b, 0, 0, False)
     pair.compare_state("end")
+
+
+def prune(pair, rng, m, least=5):
+    """Iterations with removal until `least` units are gone: the order keeps their places."""
+    n = pair.net.sizes()[0]
+    for t in range(20):
+        assert_iter_equal(*pair.iterate(rng.standard_normal((3, m)).astype(np.float32), 0, 0, True),
+                          f"prune {t}")
+        if pair.net.sizes()[0] <= n - least:
+            return
+    raise AssertionError("no units removed")
+
+
+@pytest.mark.parametrize("insert", [False, True])
+@pytest.mark.parametrize("variant", [2, 3, 4, 5, "split"])
+def test_scans_in_a_recorded_loop_after_a_removal(variant, insert):
+    """A removal leaves empty places in the unit order, which only the search can read: a
+    recorded loop of a scan starts from a new order, also with units appended behind them."""
+    from paper_1503_08294_amd import gsn
+    rng = np.random.default_rng(70)
+    n, m = 3_000, 400
+    pair = Pair(rng.standard_normal((3, n)).astype(np.float32), n_max=n + 64, e_max=8 * n, m_max=m,
+                eps_b=0.2, eps_n=0.05, max_age=1)
+    assert_iter_equal(*pair.iterate(rng.standard_normal((3, m)).astype(np.float32)))
+    for call in range(2):
+        pair.net.tune(gsn.GSN_TUNE_VARIANT, 0)
+        pair.net.tune(gsn.GSN_TUNE_SPLIT, 0)
+        prune(pair, rng, m)
+        if insert:
+            pair.net.grow(1, 1)
+            pair.orc.grow(1, 1)
+        if variant == "split":
+            pair.net.tune(gsn.GSN_TUNE_SPLIT, 3)
+        else:
+            pair.net.tune(gsn.GSN_TUNE_VARIANT, variant)
+        for again in range(2):
+            sigs = rng.standard_normal((2, 3, m)).astype(np.float32)
+            g = [x.cpu().numpy() for x in pair.net.iterate_loop(pair.to_dev(sigs))]
+            for s in sigs:
+                o = pair.orc.iterate(s, 0, 0, False)
+            assert_iter_equal(g, o, f"loop {call} {again}")
+            pair.compare_state(f"loop {call} {again}")
+    assert pair.net.check() == 0
