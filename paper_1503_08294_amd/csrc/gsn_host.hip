@@ -194,7 +194,7 @@ struct gsn_net {
   bool searched;     // the last find took the pruned search
   bool foreign;      // a caller recorded a staged find or an update: its graph may run at any
                      // time and rewrite the records or move the units, so each find makes its
-                     // own records
+                     // own records (the unit order stays: a recorded find has its own)
   bool timing;
   uint32_t timing_mask;  // timers that record while timing is on (bit GSN_T_*)
   int32_t bucket_n;            // units in the spatial order (-1: none, or not these units)
@@ -602,7 +602,9 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
   }
   // Recorded by the caller (not by gsn_iterate_loop, which tracks what its graph leaves): the
   // launches run later and perhaps often, so they may not rely on records or an order that
-  // are in place now, and leave the handle's account of them alone.
+  // are in place now, and leave the handle's account of them alone: they make an order of their
+  // own, in places of their own (the handle's has other units and empty places by then), at
+  // each replay.
   bool recorded = cfg.variant != 6 && cfg.variant >= 2 && caller_records(net, st);
   if (recorded && may_search) {
     cfg.variant = 6;   // the scan that needs neither
@@ -626,21 +628,21 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
       if (claimed) *claimed = claim != nullptr;
     }
   } else if (cfg.variant >= 2) {
-    const gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
+    gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
+    if (recorded) sb.pidx = sb.rpidx;
     // the unit order is rebuilt when the network changed and every kRebucketEvery calls
-    bool rebucket = order_due(net, cfg.variant, m, 1);
+    bool rebucket = recorded || order_due(net, cfg.variant, m, 1);
     if (net->loop_rebuild >= 0) {  // the first staged find of a recorded loop
       rebucket = net->loop_rebuild == 1;
       net->loop_rebuild = -1;
     }
+    const int32_t slots = rebucket ? net->n : net->slots;
     if (cfg.variant == 7) {
       e = rebucket ? gsn::launch_stage_order(net->s, sb, net->n, st) : hipSuccess;
-      if (rebucket) net->slots = net->n;
       if (e == hipSuccess && (rebucket || !net->staged)) {
         net->sup_parity ^= 1;
         e = gsn::launch_pruned_gather(
-            gsn::pruned_gather_args(net->s, sb, net->n, net->slots, net->p.n_max,
-                                    net->sup_parity),
+            gsn::pruned_gather_args(net->s, sb, net->n, slots, net->p.n_max, net->sup_parity),
             st);
         net->staged = !net->foreign;
       }
@@ -649,19 +651,22 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
                             cfg.variant, st);
       net->stage_parity ^= 1;
       if (rebucket) net->staged = false;   // a new order, gathered for the scans alone
-      if (rebucket) net->slots = net->n;
     }
-    if (rebucket) {
-      net->bucket_n = recorded ? -1 : net->n;
-      net->finds_since_bucket = 0;
-      net->small_signals = 0;
-      net->appended = 0;
+    if (!recorded) {
+      if (rebucket) {
+        net->bucket_n = net->n;
+        net->slots = slots;
+        net->finds_since_bucket = 0;
+        net->small_signals = 0;
+        net->appended = 0;
+      }
+      if (small) net->small_signals += m;
+      else ++net->finds_since_bucket;
     }
-    if (small) net->small_signals += m;
-    else ++net->finds_since_bucket;
     if (e == hipSuccess && cfg.variant == 7) {
       TimedRegion scan(net, GSN_T_FIND_SCAN, st);
-      e = gsn::launch_pruned_search(sb, net->n, net->slots, net->p.n_max, net->sup_parity, sig, m, winner, second, d1, d2, claim, st);
+      e = gsn::launch_pruned_search(sb, net->n, slots, net->p.n_max, net->sup_parity, sig, m,
+                                    winner, second, d1, d2, claim, st);
       scan.end();
       if (claimed) *claimed = claim != nullptr;
     } else if (e == hipSuccess) {

@@ -411,6 +411,8 @@ struct StageBufs {
   float4* pu;       // [ceil64(n_max)] units in bucket order: (x, y, z, |w|^2); slots from n
                     // to the end of the last batch hold stale values
   int32_t* pidx;    // [ceil64(n_max)] original index of every sorted slot (same padding)
+  int32_t* rpidx;   // [ceil64(n_max)] the order of finds that a caller recorded, made anew by
+                    // each of them
   int32_t* ukey;    // [n_max] bucket of every unit at the last bucketing
   int32_t* skey;    // [m_max] bucket of every signal
   int32_t* sperm;   // [m_max] original index of the signal at every sorted position

@@ -521,6 +521,7 @@ size_t stage_bytes(int32_t n_max, int32_t m_max) {
   const size_t nb64 = (nm + 63) / 64 * 64;  // pu and pidx cover whole batches of 64 units
   add(16 * nb64);  // pu
   add(4 * nb64);   // pidx
+  add(4 * nb64);   // rpidx
   add(4 * nm);   // ukey
   add(4 * mm);   // skey
   add(4 * mm);   // stk
@@ -558,6 +559,7 @@ StageBufs carve_stage(void* base, int32_t n_max, int32_t m_max) {
   const size_t nb64 = (nm + 63) / 64 * 64;
   s.pu = reinterpret_cast<float4*>(take(16 * nb64));
   s.pidx = reinterpret_cast<int32_t*>(take(4 * nb64));
+  s.rpidx = reinterpret_cast<int32_t*>(take(4 * nb64));
   s.ukey = reinterpret_cast<int32_t*>(take(4 * nm));
   s.skey = reinterpret_cast<int32_t*>(take(4 * mm));
   s.stk = reinterpret_cast<int32_t*>(take(4 * mm));

@@ -253,3 +253,66 @@ def test_scans_in_a_recorded_loop_after_a_removal(variant, insert):
             assert_iter_equal(g, o, f"loop {call} {again}")
             pair.compare_state(f"loop {call} {again}")
     assert pair.net.check() == 0
+
+
+def record_find(pair, sig):
+    import torch
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        got = pair.net.find_winners(sig)
+
+    def replay(new):
+        sig.copy_(pair.to_dev(new))
+        graph.replay()
+        torch.cuda.synchronize()
+        return [x.cpu().numpy() for x in got]
+    return replay
+
+
+@pytest.mark.parametrize("variant", [0])
+@pytest.mark.parametrize("places", ["none", "before", "between"])
+def test_recorded_finds_and_changes_of_the_order(variant, places):
+    """A recorded find keeps to its own unit order: between its replays units are removed, others
+    appended up to the same number, and eager finds make new orders of more or fewer places,
+    recorded with empty places in the handle's order (before), without (none), and with the
+    empty places made and filled between replays."""
+    from paper_1503_08294_amd import gsn
+    rng = np.random.default_rng(80)
+    n, m = 3_000, 400
+    pair = Pair(rng.standard_normal((3, n)).astype(np.float32), n_max=n + 64, e_max=8 * n, m_max=m,
+                eps_b=0.2, eps_n=0.05, max_age=1)
+    pair.net.tune(gsn.GSN_TUNE_REBUCKET, 4096)
+    pair.net.tune(gsn.GSN_TUNE_VARIANT, variant)
+
+    def batch():
+        return rng.standard_normal((3, m)).astype(np.float32)
+
+    def refill(count):
+        while pair.net.sizes()[0] < count:
+            pair.net.grow(1, 1)
+            pair.orc.grow(1, 1)
+
+    assert_iter_equal(*pair.iterate(batch()))
+    if places == "before":
+        prune(pair, rng, m)
+    count = pair.net.sizes()[0]
+    replay = record_find(pair, pair.to_dev(batch()))
+    for t in range(4):
+        if places == "between":
+            # removed and appended to the recorded number (the network must hold no more)
+            prune(pair, rng, m)
+            refill(count)
+        assert pair.net.sizes()[0] == count
+        new = batch()
+        assert_find_equal(replay(new), pair.orc.find_winners(new), f"{t} replay")
+        # eager finds: one with the order in place, then one that makes a new order
+        assert_find_equal(*pair.find(batch()), f"{t} eager")
+        pair.net.tune(gsn.GSN_TUNE_REBUCKET, 1)
+        assert_find_equal(*pair.find(batch()), f"{t} eager, new order")
+        pair.net.tune(gsn.GSN_TUNE_REBUCKET, 4096)
+        new = batch()
+        assert_find_equal(replay(new), pair.orc.find_winners(new), f"{t} replay, new order")
+        assert_find_equal(*pair.find(batch()), f"{t} eager after it")
+        pair.compare_state(f"{t}")
+    assert pair.net.check() == 0
