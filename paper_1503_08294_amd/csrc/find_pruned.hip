@@ -376,7 +376,7 @@ GatherArgs pruned_gather_args(const DevState& s, const StageBufs& b, int32_t n, 
                               int32_t n_max, int par) {
   const int32_t words = sup_words(n_max);
   return GatherArgs{s.x, s.y, s.z, b.pidx, b.pq, b.leaf, b.top, b.sup + par * words,
-                    b.sup + (par ^ 1) * words, n, slots, (slots + kTop - 1) / kTop, words};
+                    b.sup + stage_next(par) * words, n, slots, (slots + kTop - 1) / kTop, words};
 }
 
 hipError_t launch_pruned_gather(const GatherArgs& g, hipStream_t st) {

@@ -637,19 +637,21 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
       net->loop_rebuild = -1;
     }
     const int32_t slots = rebucket ? net->n : net->slots;
+    const bool gather = cfg.variant == 7 && (rebucket || !net->staged);
+    if (gather && !rebucket) net->sup_parity ^= 1;   // (a new order leaves every set empty)
+    const int boxes = recorded ? gsn::kRecordedSet : net->sup_parity;
     if (cfg.variant == 7) {
-      e = rebucket ? gsn::launch_stage_order(net->s, sb, net->n, st) : hipSuccess;
-      if (e == hipSuccess && (rebucket || !net->staged)) {
-        net->sup_parity ^= 1;
+      e = rebucket ? gsn::launch_stage_order(net->s, sb, net->n, net->p.n_max, st)
+                   : hipSuccess;
+      if (e == hipSuccess && gather) {
         e = gsn::launch_pruned_gather(
-            gsn::pruned_gather_args(net->s, sb, net->n, slots, net->p.n_max, net->sup_parity),
-            st);
+            gsn::pruned_gather_args(net->s, sb, net->n, slots, net->p.n_max, boxes), st);
         net->staged = !net->foreign;
       }
     } else {
-      e = gsn::launch_stage(net->s, sb, net->n, sig, m, rebucket, net->stage_parity,
-                            cfg.variant, st);
-      net->stage_parity ^= 1;
+      e = gsn::launch_stage(net->s, sb, net->n, net->p.n_max, sig, m, rebucket,
+                            recorded ? gsn::kRecordedSet : net->stage_parity, cfg.variant, st);
+      if (!recorded) net->stage_parity ^= 1;
       if (rebucket) net->staged = false;   // a new order, gathered for the scans alone
     }
     if (!recorded) {
@@ -665,8 +667,8 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
     }
     if (e == hipSuccess && cfg.variant == 7) {
       TimedRegion scan(net, GSN_T_FIND_SCAN, st);
-      e = gsn::launch_pruned_search(sb, net->n, slots, net->p.n_max, net->sup_parity, sig, m,
-                                    winner, second, d1, d2, claim, st);
+      e = gsn::launch_pruned_search(sb, net->n, slots, net->p.n_max, boxes, sig, m, winner,
+                                    second, d1, d2, claim, st);
       scan.end();
       if (claimed) *claimed = claim != nullptr;
     } else if (e == hipSuccess) {
@@ -1328,8 +1330,8 @@ int gsn_import(gsn_net* net, int32_t n, const float* xyz, const float* err, int3
     net->n = n;
     net->dpar = 0;
     net->wpar = 0;
-    net->stage_parity = 0;   // both histogram sets were cleared above
-    net->sup_parity = 0;     // and both sets of outer boxes
+    net->stage_parity = 0;   // every histogram set was cleared above
+    net->sup_parity = 0;     // and every set of outer boxes
     net->phase = kReady;
     net->bucket_n = -1;
     net->slots = 0;

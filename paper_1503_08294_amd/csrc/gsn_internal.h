@@ -407,6 +407,12 @@ __device__ __forceinline__ float unord(int32_t b) {
   return __int_as_float(b >= 0 ? b : b ^ 0x7fffffff);
 }
 
+// Signal histograms and outer boxes: two sets that successive calls take in turn, each clearing
+// the other, and one for the finds that a caller recorded, cleared by the order these make.
+constexpr int kStageSets = 3;
+constexpr int kRecordedSet = 2;
+__host__ __device__ constexpr int stage_next(int par) { return par == 0 ? 1 : 0; }
+
 struct StageBufs {
   float4* pu;       // [ceil64(n_max)] units in bucket order: (x, y, z, |w|^2); slots from n
                     // to the end of the last batch hold stale values
@@ -421,7 +427,7 @@ struct StageBufs {
   int32_t* stk;     // [m_max] rank of every signal inside its histogram bin (the ticket its
                     // count increment returned)
   int32_t *hist_u, *off_u, *cur_u;  // [kBuckets + 1] each
-  int32_t* hist_s;  // [2][kBuckets / 64] signal histograms
+  int32_t* hist_s;  // [kStageSets][kBuckets / 64] signal histograms
   int32_t* hsum;    // [kBuckets / 1024] sums of the unit histogram's parts
   int32_t* acc;     // [16] bounding-box accumulators
   float* bb;        // [8] grid of the last unit bucketing: lo.xyz, cells per length.xyz
@@ -434,8 +440,7 @@ struct StageBufs {
                     // index bits)
   float4* leaf;     // [ceil(n_max / kPrunedLeaf)][2] bounding box (lo, hi) of every leaf
   float4* top;      // [ceil(n_max / kPrunedTop)][2] and of every block of leaves
-  int32_t* sup;     // [2][sup_words(n_max)] and of every sixteen such blocks: two sets, taken
-                    // by successive gathers in turn, each clearing the other's
+  int32_t* sup;     // [kStageSets][sup_words(n_max)] and of every sixteen such blocks
   int32_t* wctr;    // [wctr_count(m_max)] grab counters of the dynamic scan, zeroed by the
                     // seed kernel of every call: 8 lists per 64-signal block
 };
@@ -468,9 +473,10 @@ inline int32_t stage_slots(int32_t n_max) { return (n_max + 63) / 64 * 64; }
 // units n0 .. n1 - 1 appended to the spatial order from its place at (older indices unchanged)
 hipError_t launch_stage_append(const StageBufs& b, int32_t n0, int32_t n1, int32_t at,
                                hipStream_t st);
-// parity alternates between calls (two sets of signal histogram and cursors)
-hipError_t launch_stage(const DevState& s, const StageBufs& b, int32_t n, const float* sig,
-                        int32_t m, bool rebucket, int parity, int variant, hipStream_t st);
+// parity: which set of signal histograms; successive calls alternate
+hipError_t launch_stage(const DevState& s, const StageBufs& b, int32_t n, int32_t n_max,
+                        const float* sig, int32_t m, bool rebucket, int parity, int variant,
+                        hipStream_t st);
 // The lock-set claims of the fused iteration, made by the merge once a signal's winner and
 // second are known (claim = nullptr: the merge only merges).
 struct ClaimArgs {
@@ -505,7 +511,8 @@ hipError_t launch_scan_mfma(const DevState& s, const StageBufs& b, int32_t n, co
 // The pruned search (find_pruned.hip, variant 7): the records and boxes of the present
 // positions in the unit order (of `slots` places, some of them empty after a removal), then the
 // two nearest of every signal with the claims of claim (null: none).  par: which set of outer
-// boxes; successive gathers alternate.
+// boxes; successive gathers alternate, but for the gather after a new order, which leaves every
+// set empty.
 struct GatherArgs {
   const float *x, *y, *z;
   const int32_t* pidx;
@@ -515,7 +522,8 @@ struct GatherArgs {
 };
 GatherArgs pruned_gather_args(const DevState& s, const StageBufs& b, int32_t n, int32_t slots,
                               int32_t n_max, int par);
-hipError_t launch_stage_order(const DevState& s, const StageBufs& b, int32_t n, hipStream_t st);
+hipError_t launch_stage_order(const DevState& s, const StageBufs& b, int32_t n, int32_t n_max,
+                              hipStream_t st);
 hipError_t launch_pruned_gather(const GatherArgs& g, hipStream_t st);
 hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t slots, int32_t n_max, int par,
                                 const float* sig, int32_t m,

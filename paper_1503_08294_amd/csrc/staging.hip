@@ -60,6 +60,11 @@ __device__ __forceinline__ void split16(float v, _Float16& hi, _Float16& lo) {
   lo = static_cast<_Float16>(v - static_cast<float>(hi));
 }
 
+// word k of the outer boxes, empty
+__device__ __forceinline__ int32_t sup_identity(int32_t k) {
+  return k % kSupWords < 3 ? ord(__builtin_huge_valf()) : ord(-__builtin_huge_valf());
+}
+
 // block-wide reduction of up to 4 values with op, result valid in thread 0
 template <typename Op>
 __device__ void block_reduce4(float v[4], Op op) {
@@ -90,9 +95,8 @@ __global__ __launch_bounds__(kBlock) void st_init(StageBufs b, int32_t supw) {
     b.off_u[i] = 0;
     b.cur_u[i] = 0;
   }
-  if (i < 2 * kSignalBuckets) b.hist_s[i] = 0;
-  for (int32_t k = i; k < 2 * supw; k += gridDim.x * kBlock)
-    b.sup[k] = k % kSupWords < 3 ? ord(__builtin_huge_valf()) : ord(-__builtin_huge_valf());
+  if (i < kStageSets * kSignalBuckets) b.hist_s[i] = 0;
+  for (int32_t k = i; k < kStageSets * supw; k += gridDim.x * kBlock) b.sup[k] = sup_identity(k);
   if (i < 16) b.acc[i] = i < 6 ? acc_identity(i) : 0;
   if (i < 8) b.bb[i] = 0.0f;
 }
@@ -158,10 +162,13 @@ __global__ __launch_bounds__(kBlock) void st_hist_units(const float* __restrict_
 // Exclusive scan of the unit histogram into off[] (off[kBuckets] = total) and cur[], clearing
 // it, in two launches of kBuckets / kScanPart workgroups: each sums its part, then each scans
 // its part from the sum of the parts before it.  The second also resets the bounding-box
-// accumulators.
+// accumulators, and clears every set of signal histograms and outer boxes: successive calls
+// alternate between two of each and clear the other, but a find that a caller recorded uses its
+// own set at each replay and relies on the order it makes first.
 constexpr int kScanPart = 4 * kBlock;
 constexpr int kScanParts = kBuckets / kScanPart;
 static_assert(kScanParts == kBlock, "a thread per part");
+static_assert(kStageSets * kSignalBuckets <= kScanParts * kBlock, "a thread per bin to clear");
 
 __global__ __launch_bounds__(kBlock) void st_scan_sum(const int32_t* __restrict__ hist,
                                                       int32_t* __restrict__ hsum) {
@@ -175,9 +182,15 @@ __global__ __launch_bounds__(kBlock) void st_scan_write(int32_t* __restrict__ hi
                                                         const int32_t* __restrict__ hsum,
                                                         int32_t* __restrict__ off,
                                                         int32_t* __restrict__ cur,
-                                                        int32_t* __restrict__ acc) {
+                                                        int32_t* __restrict__ acc,
+                                                        int32_t* __restrict__ hist_s,
+                                                        int32_t* __restrict__ sup,
+                                                        int32_t supw) {
   __shared__ int32_t wa[kBlock / 64], wb[kBlock / 64];
   const int32_t b = blockIdx.x, t = threadIdx.x;
+  const int32_t i = b * kBlock + t;
+  if (i < kStageSets * kSignalBuckets) hist_s[i] = 0;
+  for (int32_t k = i; k < kStageSets * supw; k += kScanParts * kBlock) sup[k] = sup_identity(k);
   const int4 v = reinterpret_cast<const int4*>(hist)[b * kBlock + t];
   const int32_t before = block_sum(t < b ? hsum[t] : 0, wa);
   const int32_t sum = v.x + v.y + v.z + v.w;
@@ -529,7 +542,7 @@ size_t stage_bytes(int32_t n_max, int32_t m_max) {
   add(4 * mm);   // seed
   add(12 * mm);  // ssig
   for (int i = 0; i < 3; ++i) add(hb);  // hist/off/cur for units
-  add(8 * kSignalBuckets);              // hist for signals
+  add(4 * kStageSets * kSignalBuckets);  // hist for signals
   add(4 * kScanParts);                  // hsum
   add(4 * 16);   // acc
   add(4 * 8);    // bb
@@ -541,7 +554,7 @@ size_t stage_bytes(int32_t n_max, int32_t m_max) {
   add(16 * nb64);                    // pq
   add(32 * (nb64 / kPrunedLeaf));    // leaf
   add(32 * (nm / kPrunedTop + 1));   // top
-  add(8 * static_cast<size_t>(sup_words(n_max)));  // sup
+  add(4 * kStageSets * static_cast<size_t>(sup_words(n_max)));  // sup
   return b;
 }
 
@@ -569,7 +582,7 @@ StageBufs carve_stage(void* base, int32_t n_max, int32_t m_max) {
   s.hist_u = reinterpret_cast<int32_t*>(take(hb));
   s.off_u = reinterpret_cast<int32_t*>(take(hb));
   s.cur_u = reinterpret_cast<int32_t*>(take(hb));
-  s.hist_s = reinterpret_cast<int32_t*>(take(8 * kSignalBuckets));
+  s.hist_s = reinterpret_cast<int32_t*>(take(4 * kStageSets * kSignalBuckets));
   s.hsum = reinterpret_cast<int32_t*>(take(4 * kScanParts));
   s.acc = reinterpret_cast<int32_t*>(take(4 * 16));
   s.bb = reinterpret_cast<float*>(take(4 * 8));
@@ -581,7 +594,7 @@ StageBufs carve_stage(void* base, int32_t n_max, int32_t m_max) {
   s.pq = reinterpret_cast<float4*>(take(16 * nb64));
   s.leaf = reinterpret_cast<float4*>(take(32 * (nb64 / kPrunedLeaf)));
   s.top = reinterpret_cast<float4*>(take(32 * (nm / kPrunedTop + 1)));
-  s.sup = reinterpret_cast<int32_t*>(take(8 * static_cast<size_t>(sup_words(n_max))));
+  s.sup = reinterpret_cast<int32_t*>(take(4 * kStageSets * static_cast<size_t>(sup_words(n_max))));
   return s;
 }
 
@@ -597,28 +610,31 @@ hipError_t launch_stage_init(const StageBufs& b, int32_t n_max, hipStream_t st) 
   return hipGetLastError();
 }
 
-hipError_t launch_stage_order(const DevState& s, const StageBufs& b, int32_t n, hipStream_t st) {
+hipError_t launch_stage_order(const DevState& s, const StageBufs& b, int32_t n, int32_t n_max,
+                              hipStream_t st) {
   const int nb = blocks(n);
   st_bbox<<<std::min(nb, 64), kBlock, 0, st>>>(s.x, s.y, s.z, n, b.acc);
   st_hist_units<<<nb, kBlock, 0, st>>>(s.x, s.y, s.z, n, b.acc, b.bb, b.ukey, b.hist_u);
   st_scan_sum<<<kScanParts, kBlock, 0, st>>>(b.hist_u, b.hsum);
-  st_scan_write<<<kScanParts, kBlock, 0, st>>>(b.hist_u, b.hsum, b.off_u, b.cur_u, b.acc);
+  st_scan_write<<<kScanParts, kBlock, 0, st>>>(b.hist_u, b.hsum, b.off_u, b.cur_u, b.acc,
+                                               b.hist_s, b.sup, sup_words(n_max));
   st_scatter_units<<<nb, kBlock, 0, st>>>(n, b.ukey, b.cur_u, b.pidx);
   return hipGetLastError();
 }
 
-hipError_t launch_stage(const DevState& s, const StageBufs& b, int32_t n, const float* sig,
-                        int32_t m, bool rebucket, int parity, int variant, hipStream_t st) {
+hipError_t launch_stage(const DevState& s, const StageBufs& b, int32_t n, int32_t n_max,
+                        const float* sig, int32_t m, bool rebucket, int parity, int variant,
+                        hipStream_t st) {
   const int layouts = variant == 3 ? kLayoutF32 : variant >= 4 ? kLayoutF16 : 0;
   if (rebucket) {
-    const hipError_t e = launch_stage_order(s, b, n, st);
+    const hipError_t e = launch_stage_order(s, b, n, n_max, st);
     if (e != hipSuccess) return e;
   }
   const int nb_g = blocks((static_cast<int64_t>(n) + 63) & ~static_cast<int64_t>(63));
   // the signal histogram alternates between two sets by call parity; each call's gather
   // zeroes the other set for the next call
   int32_t* hist = b.hist_s + parity * kSignalBuckets;
-  int32_t* hist_next = b.hist_s + (parity ^ 1) * kSignalBuckets;
+  int32_t* hist_next = b.hist_s + stage_next(parity) * kSignalBuckets;
   st_gather<<<nb_g + blocks(m), kBlock, 0, st>>>(s.x, s.y, s.z, n, b.pidx, b.pu, b.pm, b.pmh, sig,
                                                  m, nb_g, b.bb, b.skey, b.stk, hist, hist_next,
                                                  b.bmag, layouts);

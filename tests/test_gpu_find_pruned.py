@@ -270,13 +270,13 @@ def record_find(pair, sig):
     return replay
 
 
-@pytest.mark.parametrize("variant", [0])
+@pytest.mark.parametrize("variant", [0, 2, 3, 4, 5])
 @pytest.mark.parametrize("places", ["none", "before", "between"])
 def test_recorded_finds_and_changes_of_the_order(variant, places):
-    """A recorded find keeps to its own unit order: between its replays units are removed, others
-    appended up to the same number, and eager finds make new orders of more or fewer places,
-    recorded with empty places in the handle's order (before), without (none), and with the
-    empty places made and filled between replays."""
+    """A recorded find keeps to its own unit order and its own counts: between its replays units
+    are removed, others appended up to the same number, and eager finds make new orders of more
+    or fewer places, recorded with empty places in the handle's order (before), without (none),
+    and with the empty places made and filled between replays; some replays follow each other."""
     from paper_1503_08294_amd import gsn
     rng = np.random.default_rng(80)
     n, m = 3_000, 400
@@ -304,8 +304,9 @@ def test_recorded_finds_and_changes_of_the_order(variant, places):
             prune(pair, rng, m)
             refill(count)
         assert pair.net.sizes()[0] == count
-        new = batch()
-        assert_find_equal(replay(new), pair.orc.find_winners(new), f"{t} replay")
+        for again in range(1 + t):
+            new = batch()
+            assert_find_equal(replay(new), pair.orc.find_winners(new), f"{t} replay {again}")
         # eager finds: one with the order in place, then one that makes a new order
         assert_find_equal(*pair.find(batch()), f"{t} eager")
         pair.net.tune(gsn.GSN_TUNE_REBUCKET, 1)
