@@ -104,7 +104,7 @@ struct PrunedArgs {
   const float4* leaf;
   const float4* top;
   const int32_t* sup;
-  int32_t n, nleaf, ntop;
+  int32_t nleaf, ntop;
   const int32_t* off_u;
   const float* bb;
   const float* sig;
@@ -113,6 +113,7 @@ struct PrunedArgs {
   float *d1, *d2;
   ClaimArgs claim;
   int do_claim;
+  int32_t* mail;
 };
 
 constexpr int kFewUnits = 3;     // a cell with fewer leaves the first bound to a larger one
@@ -175,19 +176,16 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
     return u;
   };
   auto eval = [&](const Units& u, bool both) {
-    bool entered = false;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const float dx = sx - u.w[i].x, dy = sy - u.w[i].y, dz = sz - u.w[i].z;
       const float d = (dx * dx + dy * dy) + dz * dz;
       if (!(d > bound) && (kSide == 1 || both || q < kLeaf)) {
         const unsigned long long k = pack_key(d, __float_as_int(u.w[i].w));
-        entered |= k < k2;
         k2 = min(k2, max(k1, k));
         k1 = min(k1, k);
       }
     }
-    return entered;
   };
   // The second smallest distance of the group's units so far as the bound (the words of an
   // empty place read as NaN, which the minima leave out).
@@ -206,158 +204,178 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
                      make_float4(unord(u.w), unord(v.x), unord(v.y), 0.0f));
   };
 
-  // A signal that is not a number is at such a distance from every unit: the two of lowest index
-  // are its nearest, as in the scans, and there is nothing to search.
-  const bool number = sx == sx && sy == sy && sz == sz;
-  if (!number) {
-    const float d = (sx * sx + sy * sy) + sz * sz;
-    k1 = pack_key(d, 0);
-    k2 = pack_key(d, 1);
-  } else {
-    // (the first supers' boxes are read beside the chain that gives the first bound)
-    const float first_sup = sup_box(min(q, nsup - 1));
-    // The leaf at the middle of the signal's cell gives the first bound; with few units in the
-    // cell, of the eight or 64 cells it is one of (consecutive in Morton order).
-    const int32_t key = stage_bucket(sx, sy, sz, a.bb);
-    int32_t r0 = a.off_u[key], r1 = a.off_u[key + 1];
-    {
-      const int32_t p0 = a.off_u[key & ~7], p1 = a.off_u[(key | 7) + 1];
-      const int32_t g0 = a.off_u[key & ~63], g1 = a.off_u[(key | 63) + 1];
-      if (r1 - r0 < kFewUnits) {
-        const bool parent = p1 - p0 >= kFewUnits;
-        r0 = parent ? p0 : g0;
-        r1 = parent ? p1 : g1;
-      }
+  // (the first supers' boxes are read beside the chain that gives the first bound)
+  const float first_sup = sup_box(min(q, nsup - 1));
+  // The leaf at the middle of the signal's cell gives the first bound; with few units in the
+  // cell, of the eight or 64 cells it is one of (consecutive in Morton order).
+  const int32_t key = stage_bucket(sx, sy, sz, a.bb);
+  int32_t r0 = a.off_u[key], r1 = a.off_u[key + 1];
+  {
+    const int32_t p0 = a.off_u[key & ~7], p1 = a.off_u[(key | 7) + 1];
+    const int32_t g0 = a.off_u[key & ~63], g1 = a.off_u[(key | 63) + 1];
+    if (r1 - r0 < kFewUnits) {
+      const bool parent = p1 - p0 >= kFewUnits;
+      r0 = parent ? p0 : g0;
+      r1 = parent ? p1 : g1;
     }
-    const int32_t home = min(max((r0 + r1) / 2 / kLeaf, 0), a.nleaf - 1);
-    eval(load_leaf(home, home), false);
-    tighten();
-
-    int32_t nl = 0, skip = home, tried = -1;
-    bool many;
-    for (int attempt = 1;; ++attempt) {
-      // the tops that pass, through the boxes of kFan of them
-      int32_t nt = 0;
-      for (int32_t s0 = 0; s0 < nsup && nt <= kMostTops; s0 += L) {
-        const int32_t s = s0 + q;
-        const float ls = s0 == 0 ? first_sup : sup_box(min(s, nsup - 1));
-        Bits sm = bits(s < nsup && !(ls > bound));
-        while (sm != 0 && nt <= kMostTops) {
-          // kUnroll supers per row at a time
-          int32_t t[kUnroll];
-          bool have[kUnroll];
-  #pragma unroll
-          for (int u = 0; u < kUnroll; ++u) {
-            t[u] = 0;
-            have[u] = false;
-  #pragma unroll
-            for (int r = 0; r < kRows; ++r) {
-              if (r == row) {
-                have[u] = sm != 0;
-                t[u] = (s0 + (sm != 0 ? first(sm) : 0)) * kFan + c;
-              }
-              sm &= sm - 1;
-            }
-            have[u] = have[u] && t[u] < a.ntop;
-          }
-          float lb[kUnroll];
-  #pragma unroll
-          for (int u = 0; u < kUnroll; ++u) lb[u] = box(a.top, min(t[u], a.ntop - 1));
-  #pragma unroll
-          for (int u = 0; u < kUnroll; ++u) {
-            const bool pass = have[u] && !(lb[u] > bound);
-            const Bits b = bits(pass);
-            if (pass) tops[g][nt + below(b)] = t[u];
-            nt += count(b);
-          }
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-      const int32_t mt = min(nt, kMostTops);
-
-      // their leaves that pass, and the nearest of them
-      nl = 0;
-      unsigned long long near = kNone;
-      for (int32_t k = row; k < mt + row; k += kUnroll * kRows) {
-        int32_t f[kUnroll];
-        float lb[kUnroll];
-  #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) f[u] = tops[g][min(k + u * kRows, mt - 1)] * kFan + c;
-  #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) lb[u] = box(a.leaf, min(f[u], a.nleaf - 1));
-  #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const bool pass = k + u * kRows < mt && f[u] < a.nleaf && f[u] != skip &&
-                            !(lb[u] > bound);
-          // (of the first few there is no need: most signals have no more)
-          if ((nl > kNearFrom || attempt > 1) && pass && f[u] != tried) near = min(near, pack_key(lb[u], f[u]));
-          const Bits b = bits(pass);
-          const int32_t at = nl + below(b);
-          if (pass && at < kMostLeaves) leaves[g][at] = f[u];
-          nl += count(b);
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-      many = nt > kMostTops || nl > kMostLeaves;
-      if (attempt == kTries || (!many && nl <= kFewLeaves)) break;
-
-      // Nearest first, each lane's nearest leaf in turn, while one is nearer than the bound: boxes
-      // that span a jump of the order hold many signals and few units near them.  (With each try
-      // the lists start again from nothing: a unit enters them once.)
-      for (int i = 0; i < kNearLeaves; ++i) {
-        const unsigned long long best = min_group<L>(near);
-        if (best == kNone || __uint_as_float(static_cast<uint32_t>(best >> 32)) > bound) break;
-        if (near == best) near = kNone;
-        tried = static_cast<int32_t>(static_cast<uint32_t>(best));
-        k1 = k2 = kNone;
-        eval(load_leaf(tried, tried), false);
-        tighten();
-      }
-      k1 = k2 = kNone;
-      skip = -1;
-    }
-    if (!many) {
-      if (nl > 0) {
-        Units u = load_leaf(leaves[g][0], leaves[g][min(1, nl - 1)]);
-        int32_t e = kSide;
-        for (; e < nl; e += kSide) {
-          const Units v = load_leaf(leaves[g][e], leaves[g][min(e + 1, nl - 1)]);
-          eval(u, true);
-          u = v;
-        }
-        eval(u, e <= nl);
-      }
-    } else {
-      for (int32_t s = 0; s < nsup; ++s) {
-        if (sup_box(s) > bound) continue;
-        const int32_t t = s * kFan + c;
-        Bits tm =
-            bits(row == 0 && t < a.ntop && !(box(a.top, min(t, a.ntop - 1)) > bound));
-        while (tm != 0) {
-          const int32_t f0 = (s * kFan + first(tm)) * kFan;
-          tm &= tm - 1;
-          const int32_t lf = f0 + c;
-          Bits lm =
-              bits(row == 0 && lf < a.nleaf && !(box(a.leaf, min(lf, a.nleaf - 1)) > bound));
-          while (lm != 0) {
-            const int32_t l = f0 + first(lm);
-            lm &= lm - 1;
-            if (bits(eval(load_leaf(l, l), false)) != 0) tighten();
-          }
-        }
-      }
-    }
-    // the least key of the group, then the least of the others
-    const unsigned long long best1 = min_group<L>(k1);
-    k2 = min_group<L>(k1 == best1 ? k2 : k1);
-    k1 = best1;
   }
-  // The scan of a small batch leaves out units at a distance that is no number; so does the
-  // search of one (their keys are above all others).
-  if (a.m <= kSmallM) {
-    constexpr unsigned long long kInfinite = 0x7f800000ffffffffull;
-    if (k1 > kInfinite) k1 = kNone;
-    if (k2 > kInfinite) k2 = kNone;
+  const int32_t home = min(max((r0 + r1) / 2 / kLeaf, 0), a.nleaf - 1);
+  eval(load_leaf(home, home), false);
+  tighten();
+
+  int32_t nl = 0, skip = home, tried = -1;
+  bool many;
+  for (int attempt = 1;; ++attempt) {
+    // the tops that pass, through the boxes of kFan of them
+    int32_t nt = 0;
+    for (int32_t s0 = 0; s0 < nsup && nt <= kMostTops; s0 += L) {
+      const int32_t s = s0 + q;
+      const float ls = s0 == 0 ? first_sup : sup_box(min(s, nsup - 1));
+      Bits sm = bits(s < nsup && !(ls > bound));
+      while (sm != 0 && nt <= kMostTops) {
+        // kUnroll supers per row at a time
+        int32_t t[kUnroll];
+        bool have[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          t[u] = 0;
+          have[u] = false;
+#pragma unroll
+          for (int r = 0; r < kRows; ++r) {
+            if (r == row) {
+              have[u] = sm != 0;
+              t[u] = (s0 + (sm != 0 ? first(sm) : 0)) * kFan + c;
+            }
+            sm &= sm - 1;
+          }
+          have[u] = have[u] && t[u] < a.ntop;
+        }
+        float lb[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) lb[u] = box(a.top, min(t[u], a.ntop - 1));
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+          const bool pass = have[u] && !(lb[u] > bound);
+          const Bits b = bits(pass);
+          if (pass) tops[g][nt + below(b)] = t[u];
+          nt += count(b);
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    const int32_t mt = min(nt, kMostTops);
+
+    // their leaves that pass, and the nearest of them
+    nl = 0;
+    unsigned long long near = kNone;
+    for (int32_t k = row; k < mt + row; k += kUnroll * kRows) {
+      int32_t f[kUnroll];
+      float lb[kUnroll];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) f[u] = tops[g][min(k + u * kRows, mt - 1)] * kFan + c;
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) lb[u] = box(a.leaf, min(f[u], a.nleaf - 1));
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const bool pass = k + u * kRows < mt && f[u] < a.nleaf && f[u] != skip &&
+                          !(lb[u] > bound);
+        // (of the first few there is no need: most signals have no more)
+        if ((nl > kNearFrom || attempt > 1) && pass && f[u] != tried) near = min(near, pack_key(lb[u], f[u]));
+        const Bits b = bits(pass);
+        const int32_t at = nl + below(b);
+        if (pass && at < kMostLeaves) leaves[g][at] = f[u];
+        nl += count(b);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    many = nt > kMostTops || nl > kMostLeaves;
+    if (attempt == kTries || (!many && nl <= kFewLeaves)) break;
+
+    // Nearest first, each lane's nearest leaf in turn, while one is nearer than the bound: boxes
+    // that span a jump of the order hold many signals and few units near them.  (With each try
+    // the lists start again from nothing: a unit enters them once.)
+    for (int i = 0; i < kNearLeaves; ++i) {
+      const unsigned long long best = min_group<L>(near);
+      if (best == kNone || __uint_as_float(static_cast<uint32_t>(best >> 32)) > bound) break;
+      if (near == best) near = kNone;
+      tried = static_cast<int32_t>(static_cast<uint32_t>(best));
+      k1 = k2 = kNone;
+      eval(load_leaf(tried, tried), false);
+      tighten();
+    }
+    k1 = k2 = kNone;
+    skip = -1;
+  }
+  if (!many && nl > 0) {
+    Units u = load_leaf(leaves[g][0], leaves[g][min(1, nl - 1)]);
+    int32_t e = kSide;
+    for (; e < nl; e += kSide) {
+      const Units v = load_leaf(leaves[g][e], leaves[g][min(e + 1, nl - 1)]);
+      eval(u, true);
+      u = v;
+    }
+    eval(u, e <= nl);
+  }
+  // A hard signal (near the centre of a closed surface, or so far away that distances round alike,
+  // no box can be left out): a top per lane, then the leaves of a row's tops, then the units of
+  // those that pass, eight leaves on their way at a time.  Bound by that chain of loads when few
+  // signals are hard, by the vector unit and the cache when all are: on 200,000 units of a
+  // sphere, 16,384 signals at its centre take 1.8 ms a find (one leaf after another took 2.1, and
+  // the scan of every pair, whose screen passes them all too, takes 2.8), one among others on the
+  // surface 0.73 (1.4 and 1.2).
+  if (many) {
+    for (int32_t t0 = 0; t0 < a.ntop; t0 += L) {
+      const int32_t t = t0 + q;
+      Bits tm = bits(t < a.ntop && !(box(a.top, min(t, a.ntop - 1)) > bound));
+      while (tm != 0) {
+        int32_t f = a.nleaf;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+          if (r == row && tm != 0) f = (t0 + first(tm)) * kFan + c;
+          tm &= tm - 1;
+        }
+        const bool pass = f < a.nleaf && !(box(a.leaf, min(f, a.nleaf - 1)) > bound);
+        const Bits lm = bits(pass);
+        const int32_t n = count(lm);
+        if (pass) leaves[g][below(lm)] = f;
+        __builtin_amdgcn_wave_barrier();
+        const unsigned long long was = k2;
+        constexpr int kAhead = 8 / kSide;
+        for (int32_t e0 = 0; e0 < n; e0 += kAhead * kSide) {
+          Units u[kAhead];
+#pragma unroll
+          for (int i = 0; i < kAhead; ++i) {
+            const int32_t e = e0 + i * kSide;
+            u[i] = load_leaf(leaves[g][min(e, n - 1)], leaves[g][min(e + 1, n - 1)]);
+          }
+#pragma unroll
+          for (int i = 0; i < kAhead; ++i)
+            if (e0 + i * kSide < n) eval(u[i], e0 + i * kSide + 1 < n);
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (bits(k2 < was) != 0) tighten();
+      }
+    }
+    if (q == 0 && a.m <= kSmallM)   // (the host goes back to the scan for a while)
+      __hip_atomic_store(a.mail, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  // the least key of the group, then the least of the others
+  const unsigned long long best1 = min_group<L>(k1);
+  k2 = min_group<L>(k1 == best1 ? k2 : k1);
+  k1 = best1;
+  // Fewer than two distances are numbers (their keys are above all others): as in the scans, a
+  // small batch has no such unit for an answer, and in a larger one a signal that is no number
+  // has the two of lowest index.
+  constexpr unsigned long long kInfinite = 0x7f800000ffffffffull;
+  if (k2 > kInfinite) {
+    const bool none = k1 > kInfinite;
+    if (a.m <= kSmallM) {
+      k2 = kNone;
+      if (none) k1 = kNone;
+    } else if (none) {
+      k1 &= ~0xffffffffull;
+      k2 = k1 | 1u;
+    }
   }
 
   const int32_t bw = static_cast<int32_t>(static_cast<uint32_t>(k1));
@@ -400,15 +418,14 @@ hipError_t launch_pruned_gather(const GatherArgs& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t slots, int32_t n_max, int par,
-                                const float* sig, int32_t m,
-                                int32_t* winner, int32_t* second, float* d1, float* d2,
-                                const ClaimArgs* claim, hipStream_t st, LaunchEvents ev) {
+hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t slots, int32_t n_max,
+                                int par, const float* sig, int32_t m, int32_t* winner,
+                                int32_t* second, float* d1, float* d2, const ClaimArgs* claim,
+                                int32_t* mail, hipStream_t st, LaunchEvents ev) {
   if (n < 2 || m < 1) return hipErrorInvalidValue;
-  const PrunedArgs a{b.pq, b.leaf, b.top, b.sup + par * sup_words(n_max), n, (slots + kLeaf - 1) / kLeaf,
-                     (slots + kTop - 1) / kTop,
-                     b.off_u, b.bb, sig, m, winner, second, d1, d2,
-                     claim ? *claim : ClaimArgs{}, claim ? 1 : 0};
+  const PrunedArgs a{b.pq, b.leaf, b.top, b.sup + par * sup_words(n_max),
+                     (slots + kLeaf - 1) / kLeaf, (slots + kTop - 1) / kTop, b.off_u, b.bb, sig, m,
+                     winner, second, d1, d2, claim ? *claim : ClaimArgs{}, claim ? 1 : 0, mail};
   auto go = [&](auto k, int lanes) {
     const int per = kBlock / lanes;
     launch_with(k, dim3((m + per - 1) / per), dim3(kBlock), st, ev, a);

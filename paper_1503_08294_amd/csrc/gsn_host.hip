@@ -163,6 +163,11 @@ constexpr int32_t kSmallRun = 8;
 // A new order is due once more than one unit in this many joined at its end (a growing run of 1.5 M
 // signals: the search 8.7 us an iteration, new orders 0.7; 20.8 with one every 64 finds).
 constexpr int kAppendedPart = 16;
+// The search leaves out little for a hard signal (find_pruned.hip), and the few workgroups of a
+// small batch take long over one: once a search has reported one, the next kScanRun small finds
+// take the scan, whose time does not depend on the signals; then the search is tried again.  (64
+// signals at the centre of 100,000 units on a sphere: 227 us a search, 15 a scan.)
+constexpr int32_t kScanRun = 64;
 constexpr int kDefaultGrab = 4;        // batches per grab of the dynamic scan
 constexpr int kDefaultGridRounds = 6;  // before any update has reported back
 // Grid-wide rounds of the greedy lock-set resolve: one while the last workgroup has a thread per
@@ -192,6 +197,7 @@ struct gsn_net {
   bool staged;
   bool grew;
   bool searched;     // the last find took the pruned search
+  int32_t scan_left; // small finds that take the scan instead of it
   bool foreign;      // a caller recorded a staged find or an update: its graph may run at any
                      // time and rewrite the records or move the units, so each find makes its
                      // own records (the unit order stays: a recorded find has its own)
@@ -223,7 +229,7 @@ struct gsn_net {
     uint8_t* accepted;
     int32_t n;
     int cur, dpar, wpar, stage_parity, sup_parity;
-    bool rebuild_first, staged, grew;
+    bool rebuild_first, staged, grew, scan;
     int32_t slots, appended, small_run;
     int tune_split, tune_variant, tune_grab, tune_rebucket, grid_rounds;
     // the host state the loop leaves
@@ -242,6 +248,7 @@ struct gsn_net {
   hipStream_t cap_stream;
   bool capturing;
   int loop_rebuild;   // -1, or the unit-order decision (0/1) of the next staged find
+  bool loop_scan;     // its small finds take the scan
 };
 
 namespace {
@@ -479,6 +486,7 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   net->staged = false;
   net->grew = false;
   net->searched = false;
+  net->scan_left = 0;
   net->foreign = false;
   net->timing = false;
   net->timing_mask = (1u << GSN_T_COUNT) - 1;
@@ -495,6 +503,7 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   net->cap_stream = nullptr;
   net->capturing = false;
   net->loop_rebuild = -1;
+  net->loop_scan = false;
   net->feedback = nullptr;
   // one pinned allocation: the feedback word, then the growth mailbox
   constexpr size_t kMailAt = 64;
@@ -574,6 +583,17 @@ bool caller_records(const gsn_net* net, hipStream_t st) {
   return cs != hipStreamCaptureStatusNone;
 }
 
+// Whether the next small finds take the scan in place of the search (a report that comes late
+// only changes which one runs, never the result).
+bool scan_due(gsn_net* net) {
+  volatile int32_t* hard = &net->mail->hard;
+  if (*hard != 0) {
+    *hard = 0;
+    net->scan_left = kScanRun;
+  }
+  return net->scan_left > 0;
+}
+
 // gsn_find_winners; with claim not null the merge of the staged scans also makes the
 // lock-set claims of every signal, and *claimed says whether it did (the direct scan's
 // merge does not).
@@ -594,7 +614,8 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
   // A small batch takes the search too where its records are at hand, or after enough finds of
   // the same positions or, in an iteration, enough iterations on the same units.
   const bool small = m <= gsn::kSmallM;
-  const bool may_search = cfg.variant == 6 && net->tune_variant == 0 && !net->foreign;
+  bool may_search = cfg.variant == 6 && net->tune_variant == 0 && !net->foreign;
+  if (may_search) may_search = !(net->capturing ? net->loop_scan : scan_due(net));
   if (may_search) {
     int32_t& run = claim ? net->small_run : net->still;
     run = std::min(run + 1, kSmallRun);
@@ -615,6 +636,7 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
     net->foreign = true;
   }
   net->searched = cfg.variant == 7 && !net->foreign;
+  if (small && net->scan_left > 0 && !net->capturing) --net->scan_left;
   TimedRegion all(net, GSN_T_FIND, st);
   hipError_t e;
   if (cfg.variant == 6) {
@@ -668,7 +690,7 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
     if (e == hipSuccess && cfg.variant == 7) {
       TimedRegion scan(net, GSN_T_FIND_SCAN, st);
       e = gsn::launch_pruned_search(sb, net->n, slots, net->p.n_max, boxes, sig, m, winner,
-                                    second, d1, d2, claim, st);
+                                    second, d1, d2, claim, &net->mail_dev->hard, st);
       scan.end();
       if (claimed) *claimed = claim != nullptr;
     } else if (e == hipSuccess) {
@@ -980,6 +1002,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   if (net->n < 2) return GSN_E_INVAL;
   if (m > 0 && (!sigs || !winner || !second || !d1 || !d2 || !accepted)) return GSN_E_INVAL;
   hipStream_t st = as_stream(stream);
+  const bool scan = m <= gsn::kSmallM && scan_due(net);
   // the unit order is rebuilt at the first iteration if the usual rule would rebuild it
   // anywhere inside the loop (after that the usual rule applies, from a fresh count)
   const int variant =
@@ -994,8 +1017,10 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     return g.sigs == sigs && g.m == m && g.count == count && g.winner == winner &&
            g.second == second && g.d1 == d1 && g.d2 == d2 && g.accepted == accepted &&
            g.n == net->n && g.cur == net->cur && g.dpar == net->dpar && g.wpar == net->wpar &&
-           g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity && g.rebuild_first == rebuild_first && g.staged == net->staged && g.grew == net->grew && g.slots == net->slots && g.appended == net->appended &&
-           g.small_run == net->small_run &&
+           g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity &&
+           g.rebuild_first == rebuild_first && g.staged == net->staged &&
+           g.grew == net->grew && g.scan == scan && g.slots == net->slots &&
+           g.appended == net->appended && g.small_run == net->small_run &&
            g.tune_split == net->tune_split && g.tune_variant == net->tune_variant &&
            g.tune_grab == net->tune_grab && g.tune_rebucket == net->tune_rebucket &&
            g.grid_rounds == net->grid_rounds;
@@ -1018,6 +1043,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.rebuild_first = rebuild_first;
     g.staged = net->staged;
     g.grew = net->grew;
+    g.scan = scan;
     g.slots = net->slots;
     g.appended = net->appended;
     g.small_run = net->small_run;
@@ -1037,6 +1063,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     if (hipStreamBeginCapture(net->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
       return GSN_E_HIP;
     net->capturing = true;
+    net->loop_scan = scan;
     net->loop_rebuild = rebuild_first ? 1 : 0;
     int rc = GSN_OK;
     for (int32_t k = 0; k < count && rc == GSN_OK; ++k)
@@ -1103,6 +1130,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   }
   hit->used = ++net->graph_clock;
   if (hipGraphLaunch(hit->exec, st) != hipSuccess) return GSN_E_HIP;
+  if (scan) net->scan_left = std::max(net->scan_left - count, 0);
   net->cur = hit->cur_after;
   net->dpar = hit->dpar_after;
   net->wpar = hit->wpar_after;
@@ -1340,6 +1368,8 @@ int gsn_import(gsn_net* net, int32_t n, const float* xyz, const float* err, int3
     net->grew = false;
     net->small_run = 0;
     net->still = 0;
+    net->mail->hard = 0;
+    net->scan_left = 0;
   } catch (const std::bad_alloc&) {
     return GSN_E_CAPACITY;
   }

@@ -525,10 +525,12 @@ GatherArgs pruned_gather_args(const DevState& s, const StageBufs& b, int32_t n, 
 hipError_t launch_stage_order(const DevState& s, const StageBufs& b, int32_t n, int32_t n_max,
                               hipStream_t st);
 hipError_t launch_pruned_gather(const GatherArgs& g, hipStream_t st);
-hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t slots, int32_t n_max, int par,
-                                const float* sig, int32_t m,
-                                int32_t* winner, int32_t* second, float* d1, float* d2,
-                                const ClaimArgs* claim, hipStream_t st, LaunchEvents ev = {});
+// mail: a host word (device address) set to 1 by a hard signal (find_pruned.hip) of a batch of up
+// to kSmallM.
+hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t slots, int32_t n_max,
+                                int par, const float* sig, int32_t m, int32_t* winner,
+                                int32_t* second, float* d1, float* d2, const ClaimArgs* claim,
+                                int32_t* mail, hipStream_t st, LaunchEvents ev = {});
 
 // The survivor tables of the one-pass winner-lock update (launch_winner_local) of parity par.
 struct WinnerTables {
@@ -625,9 +627,10 @@ hipError_t launch_init(const DevState& s, int cur, int32_t n0, int32_t n_max,
 // buffer that is not current: u and v in col[cur ^ 1], the ages in age[cur ^ 1].
 hipError_t launch_export_edges(const DevState& s, int cur, int32_t n, int32_t edges,
                                hipStream_t st);
-// Host words that growth and the schedule wait for, written by a device kernel.
+// Host words written by device kernels: what growth and the schedule wait for, and whether the
+// search met a hard signal in a small batch.
 struct GrowMail {
-  int32_t orphans, inserted, kept, pad;
+  int32_t orphans, inserted, kept, hard;
   unsigned long long window;
 };
 hipError_t launch_grow_report(const DevState& s, GrowMail* mail, hipStream_t st);

@@ -319,15 +319,21 @@ def test_recorded_finds_and_changes_of_the_order(variant, places):
     assert pair.net.check() == 0
 
 
+@pytest.mark.parametrize("n,holes", [(1_000, False), (1_000, True), (5_000, False), (5_000, True)])
 @pytest.mark.parametrize("m", [7, 64, 256, 257, 700])
-def test_signals_that_are_not_numbers(m):
+def test_signals_that_are_not_numbers(n, holes, m):
     """A signal with a NaN: a small batch refuses it (no winner, GSN_E_INVAL from the update) in
     its first call as in the later ones, which take the search; a larger one names the two units
-    of lowest index, as the scans do.  An infinite signal ties all units, so the lowest indices
-    win.  The other signals of the batch are unaffected."""
+    of lowest index, as the scans do, also with empty places in the unit order.  An infinite
+    signal ties all units, so the lowest indices win.  The other signals of the batch are
+    unaffected."""
     from paper_1503_08294_amd import gsn
     rng = np.random.default_rng(m)
-    pair = Pair(rng.standard_normal((3, 5_000)).astype(np.float32), m_max=700, eps_b=0.2)
+    pair = Pair(rng.standard_normal((3, n)).astype(np.float32), m_max=700, e_max=8 * n, eps_b=0.2,
+                eps_n=0.05, max_age=1 if holes else 50)
+    if holes:
+        assert_iter_equal(*pair.iterate(rng.standard_normal((3, 300)).astype(np.float32)))
+        prune(pair, rng, n // 10, least=2)
     sig = rng.standard_normal((3, m)).astype(np.float32)
     sig[0, 2], sig[2, 4], sig[1, 5] = np.nan, -np.nan, np.inf
     bad = [2, 4]
@@ -348,3 +354,83 @@ def test_signals_that_are_not_numbers(m):
             assert not acc[bad].any(), call
             assert pair.net.check() == gsn.GSN_E_INVAL, call
         assert np.isfinite(pair.net.export()["xyz"].numpy()).all()
+
+
+def centre_batch(n, m, hard, seed):
+    """Units and signals on a sphere, `hard` of the signals at its centre instead, where every
+    unit is about equally far and no box can be left out."""
+    rng = np.random.default_rng(seed)
+    units = rng.standard_normal((3, n)).astype(np.float32)
+    units /= np.linalg.norm(units, axis=0, keepdims=True)
+    units[:, n // 2:n // 2 + 40] = units[:, :40]    # ties by index
+    sig = rng.standard_normal((3, m)).astype(np.float32)
+    sig /= np.linalg.norm(sig, axis=0, keepdims=True)
+    at = rng.permutation(m)[:hard]
+    sig[:, at] *= np.float32(1e-7)
+    sig[:, at[:hard // 8]] = 0.0
+    return units, np.ascontiguousarray(sig)
+
+
+@pytest.mark.parametrize("n,m,hard", [(140_003, 300, 3), (140_003, 300, 300), (131_072, 257, 9),
+                                      (3_000, 8_200, 700), (140_003, 8_193, 40), (9_000, 64, 5),
+                                      (9_000, 256, 256), (70_001, 1, 1)])
+def test_hard_signals(n, m, hard):
+    """Signals for which the boxes leave out little, alone and among others in their workgroup,
+    over more than one round of its list of blocks (131,072 units)."""
+    units, sig = centre_batch(n, m, hard, n + m)
+    pair = Pair(units, m_max=m)
+    want = pair.orc.find_winners(sig)
+    dev = pair.to_dev(sig)
+    for call in range(12):   # (small batches: the scan, the search, and the scan again)
+        g = [x.cpu().numpy() for x in pair.net.find_winners(dev)]
+        assert_find_equal(g, want, f"call {call}")
+
+
+def test_hard_signals_of_small_batches_in_loops():
+    """Iterations and recorded loops of small batches go back to the scan after hard signals and
+    to the search after a while, with the same results."""
+    units = centre_batch(5_000, 1, 1, 90)[0]
+    pair = Pair(units, m_max=40, eps_b=0.01, eps_n=0.001)
+    for block in range(30):
+        hard = 40 if block % 7 == 3 else 0
+        sigs = np.stack([centre_batch(100, 40, hard, 100 * block + k)[1] for k in range(5)])
+        g = [x.cpu().numpy() for x in pair.net.iterate_loop(pair.to_dev(sigs))]
+        for s in sigs:
+            o = pair.orc.iterate(s, 0, 0, False)
+        assert_iter_equal(g, o, f"block {block}")
+        assert_iter_equal(*pair.iterate(sigs[0]), f"block {block} eager")
+        pair.compare_state(f"block {block}")
+    assert pair.net.check() == 0
+
+
+def test_time_of_hard_signals():
+    """One signal at the centre of a sphere of 200,000 units holds up a batch of 16,384 by less
+    than a scan of every pair (0.73 against 1.17 ms; a walk of its boxes one after another
+    took 1.45), and small batches of such signals settle within a few times the small scan's time
+    (2 times; 40 with the walk)."""
+    import torch
+    from paper_1503_08294_amd import gsn
+
+    def time_of(pair, dev, variant, calls):
+        pair.net.tune(gsn.GSN_TUNE_VARIANT, variant)
+        for _ in range(calls):
+            pair.net.find_winners(dev)
+        best = []
+        for _ in range(3):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(calls):
+                pair.net.find_winners(dev)
+            b.record()
+            torch.cuda.synchronize()
+            best.append(a.elapsed_time(b) / calls)
+        return min(best)
+
+    units, sig = centre_batch(200_000, 16_384, 1, 7)
+    pair = Pair(units, m_max=16_384)
+    dev = pair.to_dev(sig)
+    assert time_of(pair, dev, 0, 10) < 0.9 * time_of(pair, dev, 4, 10)
+    units, sig = centre_batch(100_000, 64, 64, 8)
+    pair = Pair(units, m_max=64)
+    dev = pair.to_dev(sig)
+    assert time_of(pair, dev, 0, 150) < 8 * time_of(pair, dev, 6, 150)
