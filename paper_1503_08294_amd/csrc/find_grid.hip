@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kQueryBlock) void gx_query(
     shift[gr][q] = a - (inc - len);
   }
   if (q == kRowsOf) first[gr][kRowsOf] = inc;
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_fence();
   int32_t f[kRowsOf + 1];
 #pragma unroll
   for (int r = 0; r <= kRowsOf; ++r) f[r] = first[gr][r];

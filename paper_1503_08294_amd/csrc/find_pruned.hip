@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
         }
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
     const int32_t mt = min(nt, kMostTops);
 
     // their leaves that pass, and the nearest of them
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
         nl += count(b);
       }
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
     many = nt > kMostTops || nl > kMostLeaves;
     if (attempt == kTries || (!many && nl <= kFewLeaves)) break;
 
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
         const Bits lm = bits(pass);
         const int32_t n = count(lm);
         if (pass) leaves[g][below(lm)] = f;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_fence();
         const unsigned long long was = k2;
         constexpr int kAhead = 8 / kSide;
         for (int32_t e0 = 0; e0 < n; e0 += kAhead * kSide) {
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
           for (int i = 0; i < kAhead; ++i)
             if (e0 + i * kSide < n) eval(u[i], e0 + i * kSide + 1 < n);
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_fence();
         if (bits(k2 < was) != 0) tighten();
       }
     }

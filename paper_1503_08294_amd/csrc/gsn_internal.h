@@ -99,6 +99,14 @@ __device__ __forceinline__ unsigned long long signal_key(float d1, int32_t j, in
   return (static_cast<unsigned long long>(__float_as_uint(d1)) << 32) | lo;
 }
 
+// What a wave's lanes wrote to LDS before it, they may read from each other after it (one wave's
+// accesses run in order; this keeps the compiler to that order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // The two nearest as packed keys (bits(d) << 32) | index, whose unsigned order is the
 // lexicographic one of (d, index) for d >= +0; kNone in an empty place.
 constexpr unsigned long long kNone = ~0ull;
