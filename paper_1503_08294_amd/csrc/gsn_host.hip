@@ -668,7 +668,7 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
       if (e == hipSuccess && gather) {
         e = gsn::launch_pruned_gather(
             gsn::pruned_gather_args(net->s, sb, net->n, slots, net->p.n_max, boxes), st);
-        net->staged = !net->foreign;
+        net->staged = e == hipSuccess && !net->foreign;
       }
     } else {
       e = gsn::launch_stage(net->s, sb, net->n, net->p.n_max, sig, m, rebucket,
@@ -1009,9 +1009,12 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
       m > 0 ? gsn::find_config(net->n, m, net->cus, net->tune_split, net->tune_variant).variant
             : 0;
   const bool rebuild_first = order_due(net, variant, m, count);
-  // (small batches decide at the first iteration whether they take the search)
+  // (small batches decide at the first iteration whether they take the search; the iterations
+  // count once, whether they are recorded now or replayed)
+  const int32_t small_run0 = net->small_run;
   if (m > 0 && m <= gsn::kSmallM)
     net->small_run = std::min<int32_t>(net->small_run + count, kSmallRun);
+  const int32_t small_run = net->small_run;
   using LoopGraph = gsn_net::LoopGraph;
   auto same = [&](const LoopGraph& g) {
     return g.sigs == sigs && g.m == m && g.count == count && g.winner == winner &&
@@ -1020,7 +1023,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
            g.stage_parity == net->stage_parity && g.sup_parity == net->sup_parity &&
            g.rebuild_first == rebuild_first && g.staged == net->staged &&
            g.grew == net->grew && g.scan == scan && g.slots == net->slots &&
-           g.appended == net->appended && g.small_run == net->small_run &&
+           g.appended == net->appended && g.small_run == small_run &&
            g.tune_split == net->tune_split && g.tune_variant == net->tune_variant &&
            g.tune_grab == net->tune_grab && g.tune_rebucket == net->tune_rebucket &&
            g.grid_rounds == net->grid_rounds;
@@ -1046,7 +1049,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     g.scan = scan;
     g.slots = net->slots;
     g.appended = net->appended;
-    g.small_run = net->small_run;
+    g.small_run = small_run;
     g.tune_split = net->tune_split; g.tune_variant = net->tune_variant;
     g.tune_grab = net->tune_grab; g.tune_rebucket = net->tune_rebucket;
     g.grid_rounds = net->grid_rounds;
@@ -1054,14 +1057,16 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     // launches go into the graph
     const int cur0 = net->cur, dpar0 = net->dpar, wpar0 = net->wpar, sp0 = net->stage_parity;
     const int up0 = net->sup_parity;
-    const bool staged0 = net->staged, grew0 = net->grew;
-    const int32_t slots0 = net->slots, appended0 = net->appended;
+    const bool staged0 = net->staged, grew0 = net->grew, searched0 = net->searched;
+    const int32_t slots0 = net->slots, appended0 = net->appended, still0 = net->still;
     const int64_t small0 = net->small_signals;
     const int phase0 = net->phase;
     const int32_t bn0 = net->bucket_n, f0 = net->finds_since_bucket;
     (void)hipGetLastError();
-    if (hipStreamBeginCapture(net->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
+    if (hipStreamBeginCapture(net->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+      net->small_run = small_run0;
       return GSN_E_HIP;
+    }
     net->capturing = true;
     net->loop_scan = scan;
     net->loop_rebuild = rebuild_first ? 1 : 0;
@@ -1087,9 +1092,12 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
       net->sup_parity = up0;
       net->staged = staged0;
       net->grew = grew0;
+      net->searched = searched0;
       net->slots = slots0;
       net->appended = appended0;
       net->small_signals = small0;
+      net->small_run = small_run0;
+      net->still = still0;
       net->phase = phase0;
       net->bucket_n = bn0; net->finds_since_bucket = f0;
       (void)hipGetLastError();
@@ -1113,9 +1121,12 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     net->sup_parity = up0;
     net->staged = staged0;
     net->grew = grew0;
+    net->searched = searched0;
     net->slots = slots0;
     net->appended = appended0;
     net->small_signals = small0;
+    net->small_run = small_run;
+    net->still = still0;
     net->bucket_n = bn0; net->finds_since_bucket = f0;
     if (net->graphs.size() >= GSN_GRAPH_CACHE) {
       size_t old = 0;
@@ -1129,7 +1140,10 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
     ++net->loop_records;
   }
   hit->used = ++net->graph_clock;
-  if (hipGraphLaunch(hit->exec, st) != hipSuccess) return GSN_E_HIP;
+  if (hipGraphLaunch(hit->exec, st) != hipSuccess) {
+    net->small_run = small_run0;
+    return GSN_E_HIP;
+  }
   if (scan) net->scan_left = std::max(net->scan_left - count, 0);
   net->cur = hit->cur_after;
   net->dpar = hit->dpar_after;
@@ -1138,6 +1152,7 @@ int gsn_iterate_loop(gsn_net* net, const float* sigs, int32_t m, int32_t count,
   net->sup_parity = hit->sup_parity_after;
   net->staged = hit->staged_after && !net->foreign;
   net->grew = false;
+  net->still = 0;
   net->slots = hit->slots_after;
   net->appended = hit->appended_after;
   net->small_signals = hit->rebuilt ? hit->small_after : net->small_signals + hit->small_delta;

@@ -128,3 +128,38 @@ def test_loop_of_empty_batches_decays_the_errors():
             pair.orc.iterate(np.zeros((3, 0), np.float32), 0, 0, False)
         pair.compare_state(f"empty loop call {call}")
     assert pair.net.check() == 0
+
+
+def test_recordings_of_single_iterations_and_new_orders():
+    """Loops of one iteration meet every pairing of the buffer parities with a new unit order
+    (every seventh call) after a few calls: the cache holds them all."""
+    from paper_1503_08294_amd import gsn
+    rng = np.random.default_rng(12)
+    m = 600
+    pair = Pair(rng.standard_normal((3, 4_000)).astype(np.float32), m_max=m, eps_b=0.2)
+    pair.net.tune(gsn.GSN_TUNE_REBUCKET, 7)
+    sigs = rng.standard_normal((60, 3, m)).astype(np.float32)
+    dev = pair.to_dev(sigs[:1])
+    for t in range(60):
+        dev.copy_(pair.to_dev(sigs[t:t + 1]))
+        g = [x.cpu().numpy() for x in pair.net.iterate_loop(dev)]
+        assert_iter_equal(g, pair.orc.iterate(sigs[t], 0, 0, False), f"call {t}")
+    pair.compare_state("end")
+    # the first call, then two parities with a new order and two without
+    assert pair.net.stat(gsn.GSN_STAT_LOOP_RECORDS) <= 5
+
+
+def test_a_replay_leaves_the_state_of_a_recording():
+    """Loops of small batches count their iterations once, whether recorded or replayed: after an
+    import the same calls replay the same graphs."""
+    import torch
+    from paper_1503_08294_amd import gsn
+    rng = np.random.default_rng(13)
+    units = rng.standard_normal((3, 2_000)).astype(np.float32)
+    pair = Pair(units, m_max=64)
+    dev = pair.to_dev(rng.standard_normal((3, 3, 64)).astype(np.float32))
+    for call in range(4):
+        pair.net.import_state(torch.from_numpy(units))
+        for _ in range(2):
+            pair.net.iterate_loop(dev)
+    assert pair.net.stat(gsn.GSN_STAT_LOOP_RECORDS) == 2
