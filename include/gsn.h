@@ -37,6 +37,14 @@
  *           same on every run and for every launch configuration (see gsn_tune), and
  *           equal, element by element, to the sequential definition of each step.
  * Threads.  A handle serves one host thread at a time.
+ * Graphs.   Async calls may be captured into a HIP graph of the caller's.  A captured find of
+ *           more than 256 signals, or of a staged scan (GSN_TUNE_VARIANT 2-5), makes its own
+ *           spatial order of the units at every replay, so it searches the units of that moment;
+ *           their number must be that of the capture.  A captured iteration also depends on
+ *           which internal buffer set is current: capture an even number of iterations, and
+ *           replay them after an even number of others, with no growth between.  After such a
+ *           capture the handle's own finds gather the units anew each time, and its batches of
+ *           up to 256 signals always take the unit-parallel scan.
  */
 #ifndef GSN_H
 #define GSN_H
@@ -341,10 +349,13 @@ void gsn_destroy(gsn_net* net);
  *   GSN_TUNE_VARIANT  find-winners kernel: 0 = automatic (up to 256 signals the unit-parallel
  *                     scan, 6; above, the search that leaves out blocks of units whose
  *                     bounding box lies farther than the second nearest, unless
- *                     GSN_TUNE_SPLIT asks for chunks: then 4; smaller batches take that
- *                     search too once gsn_iterate has run several of them on the same units),
- *                     1 = direct scan of every
- *                     distance, 2 = screened scan with the screen on the vector unit,
+ *                     GSN_TUNE_SPLIT asks for chunks: then 4.  Smaller batches take that search
+ *                     too where its records of the units are at hand, after several iterations
+ *                     of small batches on the same units, and after several of their finds with
+ *                     no update between, but not for a while after a signal for which it could
+ *                     leave out little.  The search cannot be asked for),
+ *                     1 = direct scan of every distance,
+ *                     2 = screened scan with the screen on the vector unit,
  *                     3 = screened scan with the screen on the matrix cores in binary32,
  *                     4 = the same screen on the matrix cores in split binary16, 5 = variant
  *                     4 with the unit batches dealt out dynamically (every wave takes

@@ -19,7 +19,7 @@
 namespace gsn {
 namespace {
 
-constexpr int kGroupLanes = 32;            // lanes per signal (27 cubes, 5 idle)
+constexpr int kGroupLanes = 32;            // lanes per signal, which share the 27 cubes' units
 constexpr int kQueryBlock = 256;           // 8 signals per workgroup
 constexpr int kFallbackBlocks = 256;
 constexpr int kScanPart = 4 * kBlock;      // cubes per workgroup of the scan
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kQueryBlock) void gx_query(
     int32_t* __restrict__ second, float* __restrict__ d1, float* __restrict__ d2,
     int32_t* __restrict__ fb_list, int32_t* __restrict__ nfb) {
   constexpr int kRowsOf = 9;
-  __shared__ int32_t first[kQueryBlock / kGroupLanes][kRowsOf + 1];   // unit number of a row's first
+  __shared__ int32_t first[kQueryBlock / kGroupLanes][kRowsOf + 1];   // number of a row's first
   __shared__ int32_t shift[kQueryBlock / kGroupLanes][kRowsOf];       // sorted slot - unit number
   const int32_t gt = blockIdx.x * kQueryBlock + threadIdx.x;
   const int32_t j = gt / kGroupLanes;

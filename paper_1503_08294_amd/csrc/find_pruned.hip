@@ -280,7 +280,8 @@ __global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
         const bool pass = k + u * kRows < mt && f[u] < a.nleaf && f[u] != skip &&
                           !(lb[u] > bound);
         // (of the first few there is no need: most signals have no more)
-        if ((nl > kNearFrom || attempt > 1) && pass && f[u] != tried) near = min(near, pack_key(lb[u], f[u]));
+        if ((nl > kNearFrom || attempt > 1) && pass && f[u] != tried)
+          near = min(near, pack_key(lb[u], f[u]));
         const Bits b = bits(pass);
         const int32_t at = nl + below(b);
         if (pass && at < kMostLeaves) leaves[g][at] = f[u];

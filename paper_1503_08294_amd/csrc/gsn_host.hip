@@ -155,10 +155,9 @@ using gsn::DevState;
 enum Phase { kReady = 0, kFound = 1, kResolved = 2, kAdapted = 3 };
 constexpr int kRebucketEvery = 64;     // default calls between rebuilds of the unit order
 // Iterations of small batches on the same units, or finds alone on units at rest, after which
-// they take the pruned search: its
-// order and records cost about 60 us once, and then an iteration of a recorded loop takes less
-// (64 signals on 100,000 units 18.3 us against 24.6, 256 19.4 against 41.9, one 15.1 against
-// 15.7; 256 on 1,000 units 16.4 against 18.0).
+// they take the pruned search: its order and records cost about 60 us once, and then an iteration
+// of a recorded loop takes less (64 signals on 100,000 units 18.3 us against 24.6, 256 19.4
+// against 41.9, one 15.1 against 15.7; 256 on 1,000 units 16.4 against 18.0).
 constexpr int32_t kSmallRun = 8;
 // A new order is due once more than one unit in this many joined at its end (a growing run of 1.5 M
 // signals: the search 8.7 us an iteration, new orders 0.7; 20.8 with one every 64 finds).
@@ -734,7 +733,8 @@ int update_impl(gsn_net* net, const float* sig, int32_t m, const int32_t* winner
   }
   // The update moves units.  Its last launch gathers them for the next search if this find took
   // the search and the next one is due to use the same units in the same order.
-  const bool ahead = net->searched && net->staged && !net->grew && m > 0 && gsn::update_gathers(net->n) &&
+  const bool ahead = net->searched && net->staged && !net->grew && m > 0 &&
+                     gsn::update_gathers(net->n) &&
                      (net->capturing || !order_due(net, 7, m, 1));
   net->staged = false;
   net->still = 0;

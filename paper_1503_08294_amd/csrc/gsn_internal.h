@@ -124,6 +124,9 @@ __device__ __forceinline__ void merge2(unsigned long long& a1, unsigned long lon
   a1 = lo;
 }
 
+struct FMin { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
+struct FMax { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+
 // the value of another lane of the same 16-lane row
 template <int CTRL>
 __device__ __forceinline__ unsigned long long row_move(unsigned long long v) {
@@ -658,7 +661,7 @@ struct GridBufs {
   int32_t* start;    // [cells + 1] first sorted slot of every cube
   int32_t* bsum;     // [cells / kBlock + 2]
   float4* sorted;    // [n_max] units by cube: (x, y, z, index bits)
-  int32_t* ucell;    // [n_max] cube of every unit
+  int32_t* ucell;    // [n_max] cube of every unit and its rank there (cube << 8 | rank)
   int32_t* fb_list;  // [m_max] signals that fell back to the exhaustive search
   int32_t* nfb;      // their count
 };

@@ -8,9 +8,6 @@
 
 namespace gsn {
 
-struct FMin { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
-struct FMax { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
-
 template <int CTRL, typename Op>
 __device__ __forceinline__ float row_step(float v, Op op) {
   return op(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf,

@@ -4,8 +4,8 @@
 // Unit order.  Units are counting-sorted by the Morton code of a 64^3 grid of cubes over their
 // bounding box, and every find call gathers the current positions into that order as
 // packed (x, y, z, |w|^2) records.  The order only affects speed (every unit is still
-// visited for every signal), so it is rebuilt only when the host asks for it: after the
-// network changed size or indices, and periodically as units drift.
+// visited for every signal), so it is rebuilt only when the host asks for it: after the units
+// were replaced or too many joined or left, and periodically as units drift.
 // Signal order.  Signals are counting-sorted into the same grid on every call, so that a
 // wave owns signals that are near each other.
 // Seed.  For every signal, the exact direct-form distances to a window of sorted units
@@ -83,9 +83,6 @@ __device__ void block_reduce4(float v[4], Op op) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) v[k] = op(v[k], red[ww][k]);
 }
-
-struct FMin { __device__ float operator()(float a, float b) const { return fminf(a, b); } };
-struct FMax { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 
 // every histogram, offset and cursor array cleared; accumulators at their identities
 __global__ __launch_bounds__(kBlock) void st_init(StageBufs b, int32_t supw) {
