@@ -328,8 +328,7 @@ def copy_calibration(nbytes: int, reps: int):
 
 
 
-EXHAUSTIVE = 4    # the scan that visits every pair, for batches of more than SMALL_M signals
-SMALL_M = 256     # (up to it the library's own choice is exhaustive)
+EXHAUSTIVE = 6    # the scans that visit every pair: sm_scan up to SMALL_M signals, fh_scan above
 SCREEN = "f16-split MFMA screen, exact f32 direct-form recheck"
 DTYPE = "f16-split MFMA screen + f32 recheck"
 LATE_WINDOW = (81, 100)      # iterations timed on the grown network (stated run: 100)
@@ -345,10 +344,8 @@ def lock_modes(gsn, args):
 def tune(gsn, net, args):
     """Launch-configuration knobs from the command line (results never depend on them)."""
     # the metric counts evaluated signal-unit pairs, so batches that would take the search that
-    # leaves units out are timed with the exhaustive scan
-    variant = args.variant or (EXHAUSTIVE if net.params.m_max > SMALL_M else 0)
-    if variant:
-        net.tune(gsn.GSN_TUNE_VARIANT, variant)
+    # leaves units out (small ones too, after a few iterations) are timed with the exhaustive scan
+    net.tune(gsn.GSN_TUNE_VARIANT, args.variant or EXHAUSTIVE)
     if args.split:
         net.tune(gsn.GSN_TUNE_SPLIT, args.split)
     if args.grab:
