@@ -127,8 +127,10 @@ constexpr int kNearLeaves = 8;   // nearest leaves evaluated before another try
 constexpr int kMostTops = 32;
 constexpr int kTries = 4;
 
+// (With more than 80 scalar registers fewer waves run side by side: 8,192 signals on 50,000 units
+// 14.4 us instead of 13.2.)
 template <int L>
-__global__ __launch_bounds__(kBlock) void pr_search(PrunedArgs a) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void pr_search(PrunedArgs a) {
   static_assert(L == 32 || L == 64, "two or four rows of 16 lanes");
   static_assert(kFan == 16, "one row of lanes tests the boxes of a node");
   constexpr int kGroups = kBlock / L;
@@ -431,9 +433,11 @@ hipError_t launch_pruned_search(const StageBufs& b, int32_t n, int32_t slots, in
     const int per = kBlock / lanes;
     launch_with(k, dim3((m + per - 1) / per), dim3(kBlock), st, ev, a);
   };
-  // A wave per signal while the batch leaves waves free (8,192 signals, 50,000 units: 13.8 us
-  // against 14.7), two signals a wave beyond (16,384 signals, 200,000 units: 17.0 against 20.8;
-  // 65,536 signals, 100,000 units: 41.5 against 42.0).
+  // A wave per signal while the batch leaves waves free (2,048 signals on 50,000 units 5.8 us
+  // against 6.2 with two signals a wave, on 100,000 6.5 against 9.2; 4,096 on 200,000 7.5 against
+  // 7.8), two signals a wave beyond (16,384 on 200,000 15.9 against 12.8, 65,536 on 100,000 48.4
+  // against 31.4).  Between the two it depends on the units: 8,192 on 50,000 take 9.9 against 8.9
+  // at rest, 13.2 against 13.7 in a network that is pruned and grows.
   if (m <= kWideBatch) go(pr_search<64>, 64);
   else go(pr_search<32>, 32);
   return hipGetLastError();

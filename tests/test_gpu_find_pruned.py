@@ -373,6 +373,7 @@ def centre_batch(n, m, hard, seed):
 
 @pytest.mark.parametrize("n,m,hard", [(140_003, 300, 3), (140_003, 300, 300), (131_072, 257, 9),
                                       (3_000, 8_200, 700), (140_003, 8_193, 40), (9_000, 64, 5),
+                                      (3_000, 8_192, 300),
                                       (9_000, 256, 256), (70_001, 1, 1)])
 def test_hard_signals(n, m, hard):
     """Signals for which the boxes leave out little, alone and among others in their workgroup,
