@@ -160,8 +160,12 @@ constexpr int kRebucketEvery = 64;     // default calls between rebuilds of the 
 // against 41.9, one 15.1 against 15.7; 256 on 1,000 units 16.4 against 18.0).
 constexpr int32_t kSmallRun = 8;
 // A new order is due once more than one unit in this many joined at its end (a growing run of 1.5 M
-// signals: the search 8.7 us an iteration, new orders 0.7; 20.8 with one every 64 finds).
+// signals: the search 8.7 us an iteration, new orders 0.7; 20.8 with one every 64 finds), or more
+// than kAppendedMost.  Their leaves span the network, so nearly every signal visits them all: 32
+// leaves still fit its lists without another try, 160 took the search from 11 to 73 us (a run from
+// 2 to 116,080 units 0.274 s without this bound, 0.263 with 2,048, 0.243 with 1,024 and with 512).
 constexpr int kAppendedPart = 16;
+constexpr int32_t kAppendedMost = 1024;
 // The search leaves out little for a hard signal (find_pruned.hip), and the few workgroups of a
 // small batch take long over one: once a search has reported one, the next kScanRun small finds
 // take the scan, whose time does not depend on the signals; then the search is tried again.  (64
@@ -566,7 +570,9 @@ bool order_due(const gsn_net* net, int variant, int32_t m, int64_t count) {
   if (net->bucket_n != net->n) return true;
   if (variant >= 2 && variant <= 5 && net->slots != net->n) return true;
   // units appended far from their place are in the way of every signal
-  if (static_cast<int64_t>(net->appended) * kAppendedPart > net->n) return true;
+  if (static_cast<int64_t>(net->appended) * kAppendedPart > net->n ||
+      net->appended > kAppendedMost)
+    return true;
   if (m > gsn::kSmallM) return net->finds_since_bucket + count > net->tune_rebucket;
   return net->small_signals + m * count > std::max(net->n, 64 * gsn::kSmallM);
 }
