@@ -20,11 +20,12 @@
 // Search.  L lanes of a wave per signal.  The leaf around the signal's cell gives B; the lanes
 // test the outermost boxes, then the tops and the leaves of those that pass, each list
 // compacted in LDS, and evaluate the units of the leaves that pass (about six of 32 units on a
-// surface).  The kernel is bound by the vector unit for many signals (about 210 instructions a
-// signal) and by the chain of seven dependent loads for few.  At 200,000 units and 16,384
-// signals an iteration's search takes 16.5 us with its claims (and 3.7 more in the rewrite that
-// gathers for it), where staging, the exhaustive screen on the matrix cores and its merge took
-// 125; at 100,000 and 65,536, 35.5 us where they took 231.  What it took: boxes in three levels
+// surface).  The kernel is bound by the vector unit for many signals (554 instructions a wave of
+// two signals at 100,000 units and 65,536 signals, 83% of the issue cycles) and by the chain of
+// seven dependent loads for few (waves wait 64% of their cycles at 37,501 and 2,999).  At 200,000
+// units and 16,384 signals an iteration's search takes 16.5 us with its claims (and 3.7 more in
+// the rewrite that gathers for it), where staging, the exhaustive screen on the matrix cores and
+// its merge took 125; at 100,000 and 65,536, 36.6 us where they took 231.  What it took: boxes in three levels
 // with leaves of 32 units (88 us with 64 and two levels), cells in cubes, 64 a side (32 a side
 // fitted to the box: a quarter more leaves), and the tries below, without which the few signals
 // with a poor first bound (one unit in their cell, the next in Morton order far off) held up
