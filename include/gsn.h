@@ -37,10 +37,11 @@
  *           same on every run and for every launch configuration (see gsn_tune), and
  *           equal, element by element, to the sequential definition of each step.
  * Threads.  A handle serves one host thread at a time.
- * Graphs.   Async calls may be captured into a HIP graph of the caller's.  A captured find of
- *           more than 256 signals, or of a staged scan (GSN_TUNE_VARIANT 2-5), makes its own
- *           spatial order of the units at every replay, so it searches the units of that moment;
- *           their number must be that of the capture.  A captured iteration also depends on
+ * Graphs.   Async calls may be captured into a HIP graph of the caller's.  Captured finds of
+ *           more than 256 signals, or of a staged scan (GSN_TUNE_VARIANT 2-5), make their own
+ *           spatial order of the units at every replay (the first on a stream for those that
+ *           follow on it), so they search the units of that moment; their number must be that
+ *           of the capture.  A captured iteration also depends on
  *           which internal buffer set is current: capture an even number of iterations, and
  *           replay them after an even number of others, with no growth between.  After such a
  *           capture the handle's own finds gather the units anew each time, and its batches of

@@ -204,6 +204,12 @@ struct gsn_net {
   bool foreign;      // a caller recorded a staged find or an update: its graph may run at any
                      // time and rewrite the records or move the units, so each find makes its
                      // own records (the unit order stays: a recorded find has its own)
+  // the order that the finds of a caller's recording share: which recording, on which stream,
+  // for how many units, the finds since it was made, and their sets of counts and boxes
+  unsigned long long rec_id;
+  hipStream_t rec_stream;
+  int32_t rec_n, rec_finds;
+  int rec_hist, rec_sup;
   bool timing;
   uint32_t timing_mask;  // timers that record while timing is on (bit GSN_T_*)
   int32_t bucket_n;            // units in the spatial order (-1: none, or not these units)
@@ -491,6 +497,12 @@ int gsn_create(const gsn_params* params, void* workspace, size_t workspace_bytes
   net->searched = false;
   net->scan_left = 0;
   net->foreign = false;
+  net->rec_id = 0;
+  net->rec_stream = nullptr;
+  net->rec_n = 0;
+  net->rec_finds = 0;
+  net->rec_hist = 0;
+  net->rec_sup = 0;
   net->timing = false;
   net->timing_mask = (1u << GSN_T_COUNT) - 1;
   net->bucket_n = -1;
@@ -577,15 +589,37 @@ bool order_due(const gsn_net* net, int variant, int32_t m, int64_t count) {
   return net->small_signals + m * count > std::max(net->n, 64 * gsn::kSmallM);
 }
 
-// Whether the caller, not gsn_iterate_loop, records the launches on st into a graph.
-bool caller_records(const gsn_net* net, hipStream_t st) {
+// Whether the caller, not gsn_iterate_loop, records the launches on st into a graph; id (not
+// null) receives which recording it is (0 if that cannot be told).
+bool caller_records(const gsn_net* net, hipStream_t st, unsigned long long* id = nullptr) {
   if (net->capturing) return false;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return cs != hipStreamCaptureStatusNone;
+  if (cs == hipStreamCaptureStatusNone) return false;
+  if (id && hipStreamGetCaptureInfo(st, &cs, id) != hipSuccess) {
+    (void)hipGetLastError();
+    *id = 0;
+  }
+  return true;
+}
+
+// Whether a find that a caller records must make the order of its recording: the launches of one
+// recording on one stream run in turn at every replay, so its later finds of as many units use
+// the order of the first, for as many finds as an order of the handle's would serve.
+bool recorded_order_due(gsn_net* net, unsigned long long id, hipStream_t st) {
+  const bool due = id == 0 || id != net->rec_id || st != net->rec_stream ||
+                   net->rec_n != net->n || net->rec_finds >= net->tune_rebucket;
+  if (due) {
+    net->rec_id = id;
+    net->rec_stream = st;
+    net->rec_n = net->n;
+    net->rec_finds = 0;
+  }
+  ++net->rec_finds;
+  return due;
 }
 
 // Whether the next small finds take the scan in place of the search (a report that comes late
@@ -630,8 +664,9 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
   // launches run later and perhaps often, so they may not rely on records or an order that
   // are in place now, and leave the handle's account of them alone: they make an order of their
   // own, in places of their own (the handle's has other units and empty places by then), at
-  // each replay.
-  bool recorded = cfg.variant != 6 && cfg.variant >= 2 && caller_records(net, st);
+  // each replay (once for the finds of one recording).
+  unsigned long long rec_id = 0;
+  bool recorded = cfg.variant != 6 && cfg.variant >= 2 && caller_records(net, st, &rec_id);
   if (recorded && may_search) {
     cfg.variant = 6;   // the scan that needs neither
     recorded = false;
@@ -658,15 +693,18 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
     gsn::StageBufs sb = gsn::carve_stage(net->s.scr, net->p.n_max, net->p.m_max);
     if (recorded) sb.pidx = sb.rpidx;
     // the unit order is rebuilt when the network changed and every kRebucketEvery calls
-    bool rebucket = recorded || order_due(net, cfg.variant, m, 1);
+    bool rebucket =
+        recorded ? recorded_order_due(net, rec_id, st) : order_due(net, cfg.variant, m, 1);
     if (net->loop_rebuild >= 0) {  // the first staged find of a recorded loop
       rebucket = net->loop_rebuild == 1;
       net->loop_rebuild = -1;
     }
-    const int32_t slots = rebucket ? net->n : net->slots;
+    const int32_t slots = rebucket || recorded ? net->n : net->slots;
     const bool gather = cfg.variant == 7 && (rebucket || !net->staged);
-    if (gather && !rebucket) net->sup_parity ^= 1;   // (a new order leaves every set empty)
-    const int boxes = recorded ? gsn::kRecordedSet : net->sup_parity;
+    // successive gathers alternate between two sets of boxes (a new order leaves every set empty)
+    int& sup = recorded ? net->rec_sup : net->sup_parity;
+    if (gather && !rebucket) sup ^= 1;
+    const int boxes = recorded ? gsn::kRecordedSet + sup : sup;
     if (cfg.variant == 7) {
       e = rebucket ? gsn::launch_stage_order(net->s, sb, net->n, net->p.n_max, st)
                    : hipSuccess;
@@ -676,9 +714,10 @@ int find_impl(gsn_net* net, const float* sig, int32_t m, int32_t* winner, int32_
         net->staged = e == hipSuccess && !net->foreign;
       }
     } else {
+      int& hist = recorded ? net->rec_hist : net->stage_parity;
       e = gsn::launch_stage(net->s, sb, net->n, net->p.n_max, sig, m, rebucket,
-                            recorded ? gsn::kRecordedSet : net->stage_parity, cfg.variant, st);
-      if (!recorded) net->stage_parity ^= 1;
+                            recorded ? gsn::kRecordedSet + hist : hist, cfg.variant, st);
+      hist ^= 1;
       if (rebucket) net->staged = false;   // a new order, gathered for the scans alone
     }
     if (!recorded) {

@@ -419,17 +419,18 @@ __device__ __forceinline__ float unord(int32_t b) {
 }
 
 // Signal histograms and outer boxes: two sets that successive calls take in turn, each clearing
-// the other, and one for the finds that a caller recorded, cleared by the order these make.
-constexpr int kStageSets = 3;
+// the other, and two for the finds that a caller recorded, which start from the order that the
+// first of them makes (a new order clears every set).
+constexpr int kStageSets = 4;
 constexpr int kRecordedSet = 2;
-__host__ __device__ constexpr int stage_next(int par) { return par == 0 ? 1 : 0; }
+__host__ __device__ constexpr int stage_next(int par) { return par ^ 1; }
 
 struct StageBufs {
   float4* pu;       // [ceil64(n_max)] units in bucket order: (x, y, z, |w|^2); slots from n
                     // to the end of the last batch hold stale values
   int32_t* pidx;    // [ceil64(n_max)] original index of every sorted slot (same padding)
-  int32_t* rpidx;   // [ceil64(n_max)] the order of finds that a caller recorded, made anew by
-                    // each of them
+  int32_t* rpidx;   // [ceil64(n_max)] the order of finds that a caller recorded, made anew at
+                    // every replay
   int32_t* ukey;    // [n_max] bucket of every unit at the last bucketing
   int32_t* skey;    // [m_max] bucket of every signal
   int32_t* sperm;   // [m_max] original index of the signal at every sorted position

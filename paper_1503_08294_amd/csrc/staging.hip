@@ -160,8 +160,8 @@ __global__ __launch_bounds__(kBlock) void st_hist_units(const float* __restrict_
 // it, in two launches of kBuckets / kScanPart workgroups: each sums its part, then each scans
 // its part from the sum of the parts before it.  The second also resets the bounding-box
 // accumulators, and clears every set of signal histograms and outer boxes: successive calls
-// alternate between two of each and clear the other, but a find that a caller recorded uses its
-// own set at each replay and relies on the order it makes first.
+// alternate between two of each and clear the other, but the finds that a caller recorded use
+// the same ones at each replay and rely on the order that the first of them makes.
 constexpr int kScanPart = 4 * kBlock;
 constexpr int kScanParts = kBuckets / kScanPart;
 static_assert(kScanParts == kBlock, "a thread per part");

@@ -475,3 +475,71 @@ def test_time_and_result_with_many_appended_units():
     fresh, found = best_time()
     assert_find_equal(found, pair.orc.find_winners(sig), "after an import")
     assert appended < 2 * fresh, (appended, fresh)
+
+
+@pytest.mark.parametrize("variant", [0, 4])
+def test_recordings_of_several_iterations_and_finds(variant):
+    """The finds of one recording share the order that its first find makes (and make another
+    after GSN_TUNE_REBUCKET of them), each recording its own: two graphs recorded one after the
+    other on the same stream, of six iterations and of three finds, replayed several times in a
+    row and in turn, with eager calls between."""
+    import torch
+    from paper_1503_08294_amd import gsn
+    rng = np.random.default_rng(50)
+    n, m = 4_000, 500
+    pair = Pair(rng.standard_normal((3, n)).astype(np.float32), n_max=n + 64, m_max=m, eps_b=0.4,
+                eps_n=0.1, max_age=30)
+    pair.net.tune(gsn.GSN_TUNE_VARIANT, variant)
+    pair.net.tune(gsn.GSN_TUNE_REBUCKET, 4)
+
+    def batch():
+        return rng.standard_normal((3, m)).astype(np.float32)
+
+    for _ in range(2):
+        assert_iter_equal(*pair.iterate(batch()))
+    runs = [pair.to_dev(batch()) for _ in range(6)]
+    finds = [pair.to_dev(batch()) for _ in range(3)]
+    outs = [tuple(torch.empty_like(x[:m]) for x in (pair.net.buf.winner, pair.net.buf.second,
+                                                    pair.net.buf.d1, pair.net.buf.d2))
+            for _ in finds]
+    torch.cuda.synchronize()
+    graphs = [torch.cuda.CUDAGraph() for _ in range(2)]
+    with torch.cuda.graph(graphs[0], capture_error_mode="thread_local"):
+        for s in runs:
+            pair.net.iterate(s)
+    with torch.cuda.graph(graphs[1], capture_error_mode="thread_local"):
+        for s, out in zip(finds, outs):
+            for a, b in zip(out, pair.net.find_winners(s)):
+                a.copy_(b)
+
+    def run():
+        new = [batch() for _ in runs]
+        for s, b in zip(runs, new):
+            s.copy_(pair.to_dev(b))
+        graphs[0].replay()
+        torch.cuda.synchronize()
+        for b in new:
+            pair.orc.iterate(b, 0, 0, False)
+
+    def find(where):
+        new = [batch() for _ in finds]
+        for s, b in zip(finds, new):
+            s.copy_(pair.to_dev(b))
+        graphs[1].replay()
+        torch.cuda.synchronize()
+        for k, (b, out) in enumerate(zip(new, outs)):
+            assert_find_equal([x.cpu().numpy() for x in out], pair.orc.find_winners(b),
+                              f"{where} find {k}")
+
+    find("alone")   # (nothing of the other recording has run)
+    for t in range(3):
+        for again in range(t + 1):
+            run()
+        find(f"{t} first")
+        assert_find_equal(*pair.find(batch()), f"{t} eager find")
+        for k in range(2):
+            assert_iter_equal(*pair.iterate(batch()), f"{t} eager {k}")
+        for again in range(2):
+            find(f"{t} again {again}")
+        pair.compare_state(f"{t}")
+    assert pair.net.check() == 0
