@@ -25,11 +25,11 @@
 // seven dependent loads for few (waves wait 64% of their cycles at 37,501 and 2,999).  At 200,000
 // units and 16,384 signals an iteration's search takes 16.5 us with its claims (and 3.7 more in
 // the rewrite that gathers for it), where staging, the exhaustive screen on the matrix cores and
-// its merge took 125; at 100,000 and 65,536, 36.6 us where they took 231.  What it took: boxes in three levels
-// with leaves of 32 units (88 us with 64 and two levels), cells in cubes, 64 a side (32 a side
-// fitted to the box: a quarter more leaves), and the tries below, without which the few signals
-// with a poor first bound (one unit in their cell, the next in Morton order far off) held up
-// four launches in ten by 12 to 40 us.  16 lanes a signal measured 26.3 and 43.6 us (when 32
+// its merge took 125; at 100,000 and 65,536, 36.6 us where they took 231.  What it took: boxes in
+// three levels with leaves of 32 units (88 us with 64 and two levels), cells in cubes, 64 a side
+// (32 a side fitted to the box: a quarter more leaves), and the tries below, without which the few
+// signals with a poor first bound (one unit in their cell, the next in Morton order far off) held
+// up four launches in ten by 12 to 40 us.  16 lanes a signal measured 26.3 and 43.6 us (when 32
 // measured 20.6 and 42.1), 8 and 4 lanes more.
 #include <type_traits>
 
@@ -131,7 +131,8 @@ constexpr int kTries = 4;
 // (With more than 80 scalar registers fewer waves run side by side: 8,192 signals on 50,000 units
 // 14.4 us instead of 13.2.)
 template <int L>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void pr_search(PrunedArgs a) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void pr_search(
+    PrunedArgs a) {
   static_assert(L == 32 || L == 64, "two or four rows of 16 lanes");
   static_assert(kFan == 16, "one row of lanes tests the boxes of a node");
   constexpr int kGroups = kBlock / L;

@@ -581,9 +581,10 @@ namespace {
 bool order_due(const gsn_net* net, int variant, int32_t m, int64_t count) {
   if (net->bucket_n != net->n) return true;
   if (variant >= 2 && variant <= 5 && net->slots != net->n) return true;
-  // units appended far from their place are in the way of every signal
-  if (static_cast<int64_t>(net->appended) * kAppendedPart > net->n ||
-      net->appended > kAppendedMost)
+  // units appended far from their place are in the way of every signal of the search (a scan
+  // visits every unit anyway)
+  if (variant >= 6 && (static_cast<int64_t>(net->appended) * kAppendedPart > net->n ||
+                       net->appended > kAppendedMost))
     return true;
   if (m > gsn::kSmallM) return net->finds_since_bucket + count > net->tune_rebucket;
   return net->small_signals + m * count > std::max(net->n, 64 * gsn::kSmallM);
